@@ -16,70 +16,237 @@ namespace {
 // (B, F) partial pairs; every GPU the library runs on holds its own copy
 // until the process ends.
 constexpr int kScratchPairs = RFIM_NOALLOC_MAX_PARTIALS;
-constexpr int kMaxBlocks = 64;          // partials per replica at most
-constexpr int kSitesPerBlock = 8192;    // below this many sites a replica gets fewer blocks
+constexpr int kMaxBlocks = 1024;        // partials per replica at most
+constexpr int kThreads = 256;
+constexpr int kMinBlocks = 4096;        // workgroups of a large call: two rounds of 8 per CU
 constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) double scratch[2 * kScratchPairs];
 
+// v of the lane that the DPP control names, 0 where there is none or the row
+// is masked.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+
+// Sum over the wave, in lane 63: rows of 16 lanes by shifts of 1, 2, 4 and 8,
+// then row to row.  In registers; a butterfly of shuffles goes through the
+// LDS once per step (20.4 us a call at L = 64, R = 192 with it, 19.6 so).
 __device__ __forceinline__ double wave_total(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    v += dpp_or_zero<0x111, 0xF>(v);
+    v += dpp_or_zero<0x112, 0xF>(v);
+    v += dpp_or_zero<0x114, 0xF>(v);
+    v += dpp_or_zero<0x118, 0xF>(v);
+    v += dpp_or_zero<0x142, 0xA>(v);
+    v += dpp_or_zero<0x143, 0xC>(v);
     return v;
 }
 
-// Block r * nb + b: sites [b * chunk, min(N, (b + 1) * chunk)) of replica r.
-// B counts each bond once through its forward partner along x, y and z
-// (periodic); F = sum f_i s_i in FP64.  Per thread in site order, then the
-// wave's butterfly, then the four waves in order: the same sum on every
-// call.
-__global__ __launch_bounds__(256) void site_energy_partials(int L, int nb, long long N, long long chunk,
-                                                            const int8_t *__restrict__ spins,
-                                                            const float *__restrict__ fields,
-                                                            double *__restrict__ part) {
-    const int b = (int)(blockIdx.x % (unsigned)nb), r = (int)(blockIdx.x / (unsigned)nb);
-    const int8_t *s = spins + (size_t)r * (size_t)N;
-    const long long i0 = (long long)b * chunk;
-    const long long i1 = min(N, i0 + chunk);
-    const long long LL = (long long)L * L;
-    double bsum = 0.0, fsum = 0.0;
-    for (long long i = i0 + threadIdx.x; i < i1; i += 256) {
-        const int x = (int)(i % L);
-        const int y = (int)((i / L) % L);
-        const int z = (int)(i / LL);
-        const long long ix = x + 1 == L ? i - (L - 1) : i + 1;
-        const long long iy = y + 1 == L ? i - (long long)(L - 1) * L : i + L;
-        const long long iz = z + 1 == L ? i - (long long)(L - 1) * LL : i + LL;
-        const int si = s[i];
-        bsum += (double)(si * ((int)s[ix] + (int)s[iy] + (int)s[iz]));
-        fsum += (double)fields[i] * (double)si;
+// V consecutive spins as W dwords (V = 16 or 4), or one spin.
+template <int V> struct Spins {
+    static constexpr int W = V == 16 ? 4 : 1;
+    int32_t w[W];
+};
+
+template <int V>
+__device__ __forceinline__ Spins<V> load_spins(const int8_t *p) {
+    Spins<V> v;
+    if constexpr (V == 16) {
+        const int4 q = *(const int4 *)p;
+        v.w[0] = q.x;
+        v.w[1] = q.y;
+        v.w[2] = q.z;
+        v.w[3] = q.w;
+    } else if constexpr (V == 4) {
+        v.w[0] = *(const int32_t *)p;
+    } else {
+        v.w[0] = *p;
     }
-    __shared__ double red[2][4];
-    const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
-    const double wb = wave_total(bsum), wf = wave_total(fsum);
-    if (lane == 0) {
-        red[0][wave] = wb;
-        red[1][wave] = wf;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        const double v = ((red[threadIdx.x][0] + red[threadIdx.x][1]) + red[threadIdx.x][2]) + red[threadIdx.x][3];
-        part[2 * ((size_t)r * nb + b) + threadIdx.x] = v;
+    return v;
+}
+
+// sum of s_q t_q over the V spins, added to acc (four int8 products per
+// instruction)
+template <int V>
+__device__ __forceinline__ int dot_spins(const Spins<V> &s, const Spins<V> &t, int acc) {
+    if constexpr (V == 1) {
+        return acc + s.w[0] * t.w[0];
+    } else {
+#pragma unroll
+        for (int w = 0; w < Spins<V>::W; ++w) acc = __builtin_amdgcn_sdot4(s.w[w], t.w[w], acc, false);
+        return acc;
     }
 }
 
-// E_r = -(J B_r) - (h F_r), the block partials added in block order.
-__global__ __launch_bounds__(256) void site_energy_totals(int R, int nb, double J, double h,
-                                                          const double *__restrict__ part, double *__restrict__ E) {
-    const int r = (int)(blockIdx.x * 256 + threadIdx.x);
-    if (r >= R) return;
-    const double *p = part + 2 * (size_t)r * nb;
-    double B = p[0], F = p[1];
-    for (int b = 1; b < nb; ++b) {
-        B += p[2 * b];
-        F += p[2 * b + 1];
+// Block (b, group g): sites [b * chunk, min(N, (b + 1) * chunk)) of replicas
+// g * RB .. g * RB + RB - 1 (chunk a multiple of V).  B counts each bond once
+// through its forward partner along x, y and z (periodic); F = sum f_i s_i in
+// FP64.  A thread takes V consecutive sites of a row at a time (V divides L)
+// and steps kThreads * V sites through the chunk, its coordinates carried
+// along without divisions; the field of those sites is read and converted
+// once for the RB replicas.  Per thread in site order, then the wave's
+// butterfly, then the four waves in order: the same sum on every call.
+// nb = 1 writes the energies themselves.
+//
+// Bound: load latency and the L1 (each spin row is read for its own sites and
+// as the forward row of two others); the spins are read from memory about
+// once.  L = 64, R = 192 (50 MB of spins): 19.6 us a call with the totals,
+// against 136 with one site per thread step and 64-bit divisions.
+template <int V, int RB>
+__global__ __launch_bounds__(kThreads) void site_energy_partials(int L, int R, int nb, int N, int chunk, double J,
+                                                                 double h, const int8_t *__restrict__ spins,
+                                                                 const float *__restrict__ fields,
+                                                                 double *__restrict__ part, double *__restrict__ E,
+                                                                 int remap) {
+    uint32_t blk = blockIdx.x;
+    // blocks go round-robin to the 8 XCDs: a contiguous range each keeps the
+    // forward planes in the same L2
+    if (remap) blk = (blk & 7u) * (gridDim.x >> 3) + (blk >> 3);
+    const int b = (int)(blk % (uint32_t)nb), r0 = (int)(blk / (uint32_t)nb) * RB;
+    const int i0 = b * chunk, i1 = min(N, i0 + chunk);
+    const int LL = L * L;
+    // coordinates of this thread's first unit, and of a step of kThreads units
+    int i = i0 + (int)threadIdx.x * V;
+    int x = i % L, y = (i / L) % L, z = i / LL;
+    const int step = kThreads * V, sx = step % L, sy = (step / L) % L, sz = step / LL;
+    int bsum[RB];
+    double fsum[RB];
+    const int8_t *sp[RB];
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+        bsum[q] = 0;
+        fsum[q] = 0.0;
+        sp[q] = spins + (size_t)min(r0 + q, R - 1) * (size_t)N;   // past the last: read again, not written
     }
-    E[r] = -(J * B) - (h * F);
+    for (; i < i1; i += step) {
+        const int ix = x + V == L ? i + V - L : i + V;
+        const int iy = y + 1 == L ? i - (L - 1) * L : i + L;
+        const int iz = z + 1 == L ? i - (L - 1) * LL : i + LL;
+        double f[V];
+        if constexpr (V >= 4) {
+#pragma unroll
+            for (int q = 0; q < V; q += 4) {
+                const float4 v = *(const float4 *)(fields + i + q);
+                f[q] = v.x;
+                f[q + 1] = v.y;
+                f[q + 2] = v.z;
+                f[q + 3] = v.w;
+            }
+        } else {
+            f[0] = fields[i];
+        }
+#pragma unroll
+        for (int q = 0; q < RB; ++q) {
+            const Spins<V> s = load_spins<V>(sp[q] + i);
+            const Spins<V> sy1 = load_spins<V>(sp[q] + iy), sz1 = load_spins<V>(sp[q] + iz);
+            Spins<V> sx1;
+            if constexpr (V == 1) {
+                sx1.w[0] = sp[q][ix];
+            } else {
+                // the V sites one further along the row
+                const int32_t next = *(const uint8_t *)(sp[q] + ix);
+#pragma unroll
+                for (int w = 0; w < Spins<V>::W; ++w) {
+                    const uint32_t hi = w + 1 < Spins<V>::W ? (uint32_t)s.w[w + 1 < Spins<V>::W ? w + 1 : 0] : (uint32_t)next;
+                    sx1.w[w] = (int32_t)__builtin_amdgcn_alignbyte(hi, (uint32_t)s.w[w], 1u);
+                }
+            }
+            bsum[q] = dot_spins<V>(s, sx1, dot_spins<V>(s, sy1, dot_spins<V>(s, sz1, bsum[q])));
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                const int si = V == 1 ? s.w[0] : (int)(int8_t)(s.w[k >> 2] >> (8 * (k & 3)));
+                fsum[q] = fma(f[k], (double)si, fsum[q]);   // the product is exact
+            }
+        }
+        x += sx;
+        y += sy;
+        z += sz;
+        if (x >= L) {
+            x -= L;
+            ++y;
+        }
+        if (y >= L) {
+            y -= L;
+            ++z;
+        }
+    }
+    __shared__ double red[2 * RB][4];
+    const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+        const double wb = (double)__ockl_wfred_add_i32(bsum[q]), wf = wave_total(fsum[q]);
+        if (lane == 63) {
+            red[2 * q][wave] = wb;
+            red[2 * q + 1][wave] = wf;
+        }
+    }
+    __syncthreads();
+    const int q = (int)threadIdx.x;
+    if (q >= RB || r0 + q >= R) return;
+    const double B = ((red[2 * q][0] + red[2 * q][1]) + red[2 * q][2]) + red[2 * q][3];
+    const double F = ((red[2 * q + 1][0] + red[2 * q + 1][1]) + red[2 * q + 1][2]) + red[2 * q + 1][3];
+    if (nb == 1) {
+        E[r0 + q] = -(J * B) - (h * F);
+    } else {
+        double *o = part + 2 * ((size_t)(r0 + q) * nb + b);
+        o[0] = B;
+        o[1] = F;
+    }
+}
+
+// E_r = -(J B_r) - (h F_r): one wave per replica, lane l adds blocks l,
+// l + 64, ... in order, then the butterfly.  (One thread per replica waited
+// for its nb loads one after another.)
+__global__ __launch_bounds__(kThreads) void site_energy_totals(int R, int nb, double J, double h,
+                                                               const double *__restrict__ part,
+                                                               double *__restrict__ E) {
+    const int r = (int)(blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)), lane = (int)threadIdx.x & 63;
+    if (r >= R) return;
+    const double2 *p = (const double2 *)part + (size_t)r * nb;
+    double B = 0.0, F = 0.0;
+    for (int b = lane; b < nb; b += 64) {
+        const double2 v = p[b];
+        B += v.x;
+        F += v.y;
+    }
+    B = wave_total(B);
+    F = wave_total(F);
+    if (lane == 63) E[r] = -(J * B) - (h * F);
+}
+
+// The blocks of a call: nb per group of RB replicas.
+struct Split {
+    int nb, chunk;
+};
+
+// Enough workgroups to fill the chip, but at least one step of every thread
+// in each, and no more partials than the scratch array and the totals take.
+Split split_sites(int N, int V, int groups, int R) {
+    const int unit = kThreads * V, units = (N + unit - 1) / unit;
+    int nb = std::min(units, (kMinBlocks + groups - 1) / groups);
+    nb = std::min(nb, std::min(kMaxBlocks, kScratchPairs / R));   // >= 1 since R <= kScratchPairs
+    const int per = (units + nb - 1) / nb;                        // whole steps: no idle threads inside one
+    return {(units + per - 1) / per, per * unit};
+}
+
+template <int V, int RB>
+hipError_t launch_energies(int L, int R, double J, double h, const int8_t *spins, const float *fields, double *part,
+                           double *E, hipStream_t s) {
+    const int N = L * L * L, groups = (R + RB - 1) / RB;
+    const Split sp = split_sites(N, V, groups, R);
+    const unsigned blocks = (unsigned)sp.nb * (unsigned)groups;
+    hipLaunchKernelGGL((site_energy_partials<V, RB>), dim3(blocks), dim3(kThreads), 0, s, L, R, sp.nb, N, sp.chunk, J,
+                       h, spins, fields, part, E, blocks % 8u == 0 ? 1 : 0);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess && sp.nb > 1) {
+        hipLaunchKernelGGL(site_energy_totals, dim3((unsigned)((R + 3) / 4)), dim3(kThreads), 0, s, R, sp.nb, J, h,
+                           (const double *)part, E);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 std::mutex g_mu;
@@ -117,22 +284,25 @@ extern "C" int rfim_energies_noalloc(int L, int R, double J, double h, const int
                                     kScratchPairs);
     if (!d_spins || !d_fields || !d_E) return rfim_host::set_error(RFIM_EINVAL, "NULL device pointer");
     if (!std::isfinite(J) || !std::isfinite(h)) return rfim_host::set_error(RFIM_EINVAL, "J and h must be finite");
-    const long long N = (long long)L * L * L;
-    int nb = (int)std::min<long long>(kMaxBlocks, std::max<long long>(1, N / kSitesPerBlock));
-    nb = std::min(nb, kScratchPairs / R);    // >= 1 since R <= kScratchPairs
-    const long long chunk = (N + nb - 1) / nb;
     double *part = nullptr;
     int rc = scratch_on_current_device(&part);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
-    hipLaunchKernelGGL(site_energy_partials, dim3((unsigned)(nb * R)), dim3(256), 0, s, L, nb, N, chunk, d_spins,
-                       d_fields, part);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(site_energy_totals, dim3((R + 255) / 256), dim3(256), 0, s, R, nb, J, h,
-                           (const double *)part, d_E);
-        e = hipGetLastError();
-    }
+    // Widest step that divides a row, where both arrays allow its loads.  Two
+    // replicas share a pass over the field (L = 64, R = 192: 19.6 us with two,
+    // 23 with one, 21-25 with four, 38 with eight, whose loads the registers
+    // no longer keep in flight).
+    const bool a16 = ((uintptr_t)d_fields & 15u) == 0;
+    hipError_t e;
+    if (L % 16 == 0 && a16 && ((uintptr_t)d_spins & 15u) == 0)
+        e = R >= 2 ? launch_energies<16, 2>(L, R, J, h, d_spins, d_fields, part, d_E, s)
+                   : launch_energies<16, 1>(L, R, J, h, d_spins, d_fields, part, d_E, s);
+    else if (L % 4 == 0 && a16 && ((uintptr_t)d_spins & 3u) == 0)
+        e = R >= 2 ? launch_energies<4, 2>(L, R, J, h, d_spins, d_fields, part, d_E, s)
+                   : launch_energies<4, 1>(L, R, J, h, d_spins, d_fields, part, d_E, s);
+    else
+        e = R >= 2 ? launch_energies<1, 2>(L, R, J, h, d_spins, d_fields, part, d_E, s)
+                   : launch_energies<1, 1>(L, R, J, h, d_spins, d_fields, part, d_E, s);
     if (e != hipSuccess) return rfim_host::set_error(RFIM_EDEVICE, "energy launch: %s", hipGetErrorString(e));
     return RFIM_OK;
 }

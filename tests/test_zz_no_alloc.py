@@ -60,3 +60,30 @@ def test_noalloc_energies_match_rfim_energies_gaussian(rfim_mod):
     refs, got = _run_two(rfim_mod, [(16, 9, "g", [42, 0], 25), (6, 3, "g", [42, 1], 10)])
     for E, G in zip(refs, got):
         assert np.allclose(G, E, rtol=1e-12, atol=1e-9), (G, E)
+
+
+@pytest.mark.parametrize("L,R,kind", [(2, 1, "b"), (6, 5, "g"), (12, 2, "b"), (16, 1, "g"), (20, 3, "g"), (34, 3, "b"),
+                                      (48, 5, "g"), (64, 3, "b")])
+@pytest.mark.parametrize("offset", [0, 1, 4])
+def test_noalloc_energies_every_width(rfim_mod, L, R, kind, offset):
+    """The steps of 16, 4 and 1 sites, odd replica counts and arrays that
+    start inside a 16-byte unit, against the roll formulation."""
+    import torch
+
+    from helpers import energy_numpy
+
+    N = L ** 3
+    f = W.bimodal_fields(L, [43, L]) if kind == "b" else W.gaussian_fields(L, [43, L])
+    s = W.random_spins(R, L, [44, L])
+    buf = torch.zeros(R * N + offset, dtype=torch.int8, device="cuda")
+    buf[offset:] = torch.from_numpy(s.reshape(-1)).cuda()
+    fbuf = torch.zeros(N + offset, dtype=torch.float32, device="cuda")
+    fbuf[offset:] = torch.from_numpy(f).cuda()
+    E = torch.full((R,), np.nan, dtype=torch.float64, device="cuda")
+    rfim_mod.rfim.rfim_energies_noalloc(L, R, J, H, buf[offset:], fbuf[offset:], E)
+    torch.cuda.synchronize()
+    want = np.array([energy_numpy(s[r], f, L, J, H)[0] for r in range(R)])
+    if kind == "b":
+        assert np.array_equal(E.cpu().numpy(), want)
+    else:
+        assert np.allclose(E.cpu().numpy(), want, rtol=1e-12, atol=1e-9)
