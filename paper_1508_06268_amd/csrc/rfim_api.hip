@@ -579,9 +579,8 @@ int bits_from_bytes(rfim *h) {
 }
 
 int compute_components(rfim *h) {
-    int rc;
-    if ((rc = bytes_from_bits(h))) return rc;
     Lattice lat = h->lattice();
+    lat.nblk = rfim_dev::energy_blocks(lat);
     HIPCHK(rfim_dev::launch_energy(lat, h->stream));
     HIPCHK(rfim_dev::launch_reduce(lat, h->d_B, h->d_F, h->d_M, h->stream));
     return RFIM_OK;

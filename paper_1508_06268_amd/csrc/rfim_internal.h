@@ -162,6 +162,10 @@ hipError_t launch_stream_sweep(const Launch &ln, int colour, int toff, int energ
 hipError_t launch_resident(const Launch &ln, int nsweep, int energy, hipStream_t s);
 // Any even L, one realization.
 hipError_t launch_generic_sweep(const Lattice &lat, int colour, int toff, hipStream_t s);
+// Energy partials of the state at rest, lat.nblk per replica, from the bytes
+// or, in bit storage, the bits; energy_blocks: the count for a reduction that
+// does not have to match the sweep's.
+int energy_blocks(const Lattice &lat);
 hipError_t launch_energy(const Lattice &lat, hipStream_t s);
 hipError_t launch_reduce(const Lattice &lat, int64_t *B, double *F, int64_t *M, hipStream_t s);
 // One exchange step for each of the n realizations in lats (device array).

@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "rfim_internal.h"
@@ -541,6 +542,12 @@ __device__ __forceinline__ uint32_t chunk_update_any(const Lattice &lat, const u
     return chunk_flip_any<KIND, NW>(lat, sthr, never, in, F4, g0, c1, r, beta, W, U, Wnew);
 }
 
+// f, negated where bit `bit` of `down` is set (the sign goes onto the FP32
+// value, so it costs a shift and one three-input operation).
+__device__ __forceinline__ double signed_field(float f, uint32_t down, int bit) {
+    return (double)__uint_as_float(__float_as_uint(f) ^ ((down << (31 - bit)) & 0x80000000u));
+}
+
 // Energy pieces of a chunk of colour-1 sites and the colour-0 sites of the
 // same pairs, from the final spins: every bond joins a colour-0 and a
 // colour-1 site, so B = sum over colour-1 sites of s_i n_i counts each bond
@@ -568,8 +575,8 @@ __device__ __forceinline__ void chunk_energy(const Lattice &lat, const uint32_t 
             const float a1[4] = {f1.x, f1.y, f1.z, f1.w}, a0[4] = {f0.x, f0.y, f0.z, f0.w};
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                fsum += ((S1[w] >> (8 * q)) & 1u) ? (double)a1[q] : -(double)a1[q];
-                fsum += ((S0[w] >> (8 * q)) & 1u) ? (double)a0[q] : -(double)a0[q];
+                fsum += signed_field(a1[q], ~S1[w], 8 * q);
+                fsum += signed_field(a0[q], ~S0[w], 8 * q);
             }
         }
     }
@@ -1099,6 +1106,39 @@ __device__ __forceinline__ void class_offsets(uint32_t u0, uint32_t u1, uint32_t
     for (int b = 0; b < 8; ++b) A[b] = x[b];
 }
 
+// sum of f_i s_i over the 32 sites of each of a wave's 64 consecutive words
+// (bits S, words w0..w0+63 of one colour whose fields start at f), added up
+// per lane in another order of the sites: float4 number 64k + lane of the
+// wave's 2048 fields belongs to word 8k + lane / 8, block lane % 8, whose bits
+// come from that word's lane.  Every load is one 1 KiB run; a thread reading
+// its own word's fields (128 B apart in the wave) made the energy half-sweep
+// of L = 64, R = 128 take 12.5 us against 7.3 without energies, 10.7 so.
+__device__ __forceinline__ double bits_field_sum(GAS const float *f, uint32_t w0, uint32_t S) {
+    const uint32_t lane = threadIdx.x & 63u;
+    GAS const f32x4 *f4 = (GAS const f32x4 *)f + (size_t)w0 * 8u + lane;
+    double sum = 0.0;
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) {
+        const f32x4 v = f4[64u * k];
+        const uint32_t down =
+            ~((uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * (8u * k + (lane >> 3))), (int)S) >> (lane & 7u));
+        sum += signed_field(v.x, down, 0);
+        sum += signed_field(v.y, down, 8);
+        sum += signed_field(v.z, down, 16);
+        sum += signed_field(v.w, down, 24);
+    }
+    return sum;
+}
+
+// Aligned neighbours of a word's 32 sites (up if s = +1, 6 - up if s = -1)
+// from the three planes of the up count.
+__device__ __forceinline__ int bits_aligned(uint32_t U0, uint32_t U1, uint32_t U2, uint32_t S) {
+    const uint32_t nS = ~S;
+    const int up_on = __popc(U0 & S) + 2 * __popc(U1 & S) + 4 * __popc(U2 & S);
+    const int up_off = __popc(U0 & nS) + 2 * __popc(U1 & nS) + 4 * __popc(U2 & nS);
+    return up_on + 6 * (32 - __popc(S)) - up_off;
+}
+
 constexpr int kBitsThreads = 256;
 
 // Word i of a colour's bit array, addressed as a wave-uniform base plus a
@@ -1106,6 +1146,30 @@ constexpr int kBitsThreads = 256;
 // address; i < 2^30 at every L that bit storage takes).
 __device__ __forceinline__ uint32_t bits_word(GAS const uint32_t *base, uint32_t i) {
     return *(GAS const uint32_t *)((GAS const char *)base + (i << 2));
+}
+
+// The other colour's word W at word w of colour c's index space and the up
+// count of the six neighbours of w's 32 sites in three bit planes.
+__device__ __forceinline__ void bits_up_counts(const Lattice &lat, GAS const uint32_t *oth, uint32_t w, uint32_t c,
+                                               uint32_t &W, uint32_t &U0, uint32_t &U1, uint32_t &U2) {
+    const uint32_t L = (uint32_t)lat.L, l = (uint32_t)lat.log2L;
+    const uint32_t lrw = l - 6u, rw_ = 1u << lrw;
+    const uint32_t p = (c + (w >> lrw) + (w >> (lrw + l))) & 1u;
+    const uint32_t xm = rw_ - 1u, ym = (L - 1u) << lrw, zm = ym << l;
+    W = bits_word(oth, w);
+    const uint32_t Wn = bits_word(oth, ((w + 2u * p - 1u) & xm) | (w & ~xm));
+    const uint32_t Wyp = bits_word(oth, ((w + rw_) & ym) | (w & ~ym));
+    const uint32_t Wym = bits_word(oth, ((w - rw_) & ym) | (w & ~ym));
+    const uint32_t Wzp = bits_word(oth, ((w + (rw_ << l)) & zm) | (w & ~zm));
+    const uint32_t Wzm = bits_word(oth, ((w - (rw_ << l)) & zm) | (w & ~zm));
+    const uint32_t Wx = p ? ((W >> 8) | ((W << 23) & 0x7F000000u) | (Wn << 31))
+                          : ((W << 8) | ((W >> 23) & 0x000000FEu) | (Wn >> 31));
+    const uint32_t s1 = xor3(W, Wx, Wyp), c1 = maj3(W, Wx, Wyp);
+    const uint32_t s2 = xor3(Wym, Wzp, Wzm), c2 = maj3(Wym, Wzp, Wzm);
+    const uint32_t c3 = s1 & s2;
+    U0 = s1 ^ s2;
+    U1 = xor3(c1, c2, c3);
+    U2 = maj3(c1, c2, c3);
 }
 
 // Flip bits of one word of the bit sweep (its 32 sites, eight Philox
@@ -1243,10 +1307,7 @@ __global__ __launch_bounds__(kBitsThreads) void sweep_bits(Lattice lat0, const L
         // B counts each bond once through the colour-1 sites: sum of
         // s_i n_i = 2 K - 6 with K the aligned neighbours (up if s = +1,
         // 6 - up if s = -1).
-        const uint32_t nS = ~Snew;
-        const int up_on = __popc(U0 & Snew) + 2 * __popc(U1 & Snew) + 4 * __popc(U2 & Snew);
-        const int up_off = __popc(U0 & nS) + 2 * __popc(U1 & nS) + 4 * __popc(U2 & nS);
-        const int ksum = up_on + 6 * (32 - __popc(Snew)) - up_off;
+        const int ksum = bits_aligned(U0, U1, U2, Snew);
         const int upsum = __popc(Snew) + __popc(W);
         int eqsum = 0;
         double fsum = 0.0;
@@ -1254,14 +1315,8 @@ __global__ __launch_bounds__(kBitsThreads) void sweep_bits(Lattice lat0, const L
             const uint32_t F0 = gptr(lat.fbw)[w];
             eqsum = __popc(~(Snew ^ F)) + __popc(~(W ^ F0));
         } else {
-            GAS const float *f1 = gptr(lat.fraw) + lat.half + 32u * w;
-            GAS const float *f0 = gptr(lat.fraw) + 32u * w;
-#pragma unroll 8
-            for (uint32_t i = 0; i < 32; ++i) {
-                const uint32_t q = bit_of_index(i);
-                fsum += ((Snew >> q) & 1u) ? (double)f1[i] : -(double)f1[i];
-                fsum += ((W >> q) & 1u) ? (double)f0[i] : -(double)f0[i];
-            }
+            const uint32_t w0 = w & ~63u;
+            fsum = bits_field_sum(gptr(lat.fraw) + lat.half, w0, Snew) + bits_field_sum(gptr(lat.fraw), w0, W);
         }
         block_partial<KIND>(gptr(lat.part) + ((size_t)gb * lat.pstride + r) * 3, 32, ksum, upsum, eqsum, fsum);
     }
@@ -1306,57 +1361,127 @@ __global__ __launch_bounds__(256) void unpack_bits_kernel(Lattice lat) {
 }
 
 // ---------------------------------------------------------------------
-// Energy partials (Eq. 1).  Every bond joins a colour-0 and a colour-1
-// site, so B = sum over colour-1 sites of s_i n_i counts each bond once;
-// F and M run over both colours.  Grid (nblk, R); fixed reduction order.
+// Energy partials (Eq. 1) of a state at rest, for the calls that read
+// energies and for the sweeps that do not write partials themselves.  Every
+// bond joins a colour-0 and a colour-1 site, so B = sum over colour-1 sites
+// of s_i n_i counts each bond once; F and M run over both colours.  Grid
+// (nblk, R); fixed reduction order.
+//
+// Bound: memory (one byte, or one bit, per spin, once).  L = 64, R = 192 in
+// bits: 5.3 us; L = 128, R = 64: 9.8 us.  Both were unpacked to bytes first
+// and then read one site per step with divisions by L (126 and 336 us).
 // ---------------------------------------------------------------------
-__global__ __launch_bounds__(256) void energy_kernel(Lattice lat) {
-    const int G = lat.half >> 2;
-    const int r = blockIdx.y;
-    const int L = lat.L;
-    const uint8_t *s0 = lat.spins + (size_t)r * lat.N;
-    const uint8_t *s1 = s0 + lat.half;
-    long long bsum = 0, msum = 0;
+
+// x / d for x < 2^31 by a multiplication (d >= 2): with 2^s < d <= 2^(s+1)
+// and mul = floor(2^(32+s) / d) + 1, mul d exceeds 2^(32+s) by at most d, so
+// the quotient is exact while x d < 2^(32+s), that is x < 2^31.
+struct FastDiv {
+    uint32_t mul, shift, d;
+};
+
+FastDiv fast_div(uint32_t d) {
+    uint32_t s = 0;
+    while ((2u << s) < d) ++s;
+    return FastDiv{d < 2 ? 0u : (uint32_t)((1ull << (32 + s)) / d) + 1u, s, d};
+}
+
+__device__ __forceinline__ uint32_t div_by(uint32_t x, const FastDiv &f) {
+    return f.d == 1u ? x : __umulhi(x, f.mul) >> f.shift;
+}
+
+// Rows of whole dwords (L a multiple of 8 NW): chunks as in the sweeps.
+template <int KIND, int NW>
+__global__ __launch_bounds__(256) void energy_rows(Lattice lat, FastDiv by_row, FastDiv by_l) {
+    const uint32_t r = blockIdx.y, L = (uint32_t)lat.L, Lh = L >> 1, half = (uint32_t)lat.half, plane = L * Lh;
+    GAS const uint8_t *s0 = gptr((const uint8_t *)lat.spins) + (size_t)r * lat.N;
+    GAS const uint8_t *s1 = s0 + half;
+    GAS const uint8_t *fbits = gptr(lat.fbits);
+    GAS const float *fraw = gptr(lat.fraw);
+    int ksum = 0, upsum = 0, eqsum = 0, n = 0;
     double fsum = 0.0;
-    for (int g = blockIdx.x * 256 + threadIdx.x; g < G; g += lat.nblk * 256) {
-        for (int q = 0; q < 4; ++q) {
-            const int j = 4 * g + q;
-            const int i0 = 2 * j;
-            const int x0 = i0 % L, y = (i0 / L) % L, z = i0 / (L * L);
-            const int x = x0 + (((x0 + y + z) & 1) ^ 1);   // the colour-1 site of pair j
-            const int xp = x + 1 == L ? 0 : x + 1, xm = x == 0 ? L - 1 : x - 1;
-            const int yp = y + 1 == L ? 0 : y + 1, ym = y == 0 ? L - 1 : y - 1;
-            const int zp = z + 1 == L ? 0 : z + 1, zm = z == 0 ? L - 1 : z - 1;
-            const int up = s0[(xp + L * (y + L * z)) >> 1] + s0[(xm + L * (y + L * z)) >> 1] +
-                           s0[(x + L * (yp + L * z)) >> 1] + s0[(x + L * (ym + L * z)) >> 1] +
-                           s0[(x + L * (y + L * zp)) >> 1] + s0[(x + L * (y + L * zm)) >> 1];
-            const int b1 = s1[j], b0 = s0[j];
-            const int sp1 = 2 * b1 - 1, sp0 = 2 * b0 - 1;
-            bsum += sp1 * (2 * up - 6);
-            msum += sp1 + sp0;
-            if (lat.kind == 0) {
-                const int f1 = (lat.fbits[lat.half + j] >> 1) - 1, f0 = (lat.fbits[j] >> 1) - 1;
-                fsum += (double)(f1 * sp1 + f0 * sp0);
+    for (uint32_t j0 = 4u * NW * (blockIdx.x * 256u + threadIdx.x); j0 < half; j0 += 4u * NW * 256u * gridDim.x, ++n) {
+        const uint32_t row = div_by(j0, by_row), m0 = j0 - row * Lh;
+        const uint32_t z = div_by(row, by_l), y = row - z * L;
+        Chunk c;
+        c.p = (1u + y + z) & 1u;
+        c.jxw = j0 - m0 + (c.p ? (m0 + 4u * NW == Lh ? 0u : m0 + 4u * NW) : (m0 == 0u ? Lh : m0) - 4u);
+        c.jyp = y + 1u == L ? j0 + Lh - plane : j0 + Lh;
+        c.jym = y == 0u ? j0 - Lh + plane : j0 - Lh;
+        c.jzp = z + 1u == L ? j0 + plane - half : j0 + plane;
+        c.jzm = z == 0u ? j0 - plane + half : j0 - plane;
+        uint32_t S1[NW], W[NW], U[NW], F1[NW];
+        load_words<NW>(s1, j0, S1);
+        if (KIND == 0) load_words<NW>(fbits + half, j0, F1);
+        neighbour_counts<NW>(s0, j0, c, W, U);
+        chunk_energy<KIND, NW>(lat, S1, W, U, F1, fbits, fraw + half, fraw, j0, ksum, upsum, eqsum, fsum);
+    }
+    block_partial<KIND>(gptr(lat.part) + ((size_t)blockIdx.x * lat.pstride + r) * 3, 4 * NW * n, ksum, upsum, eqsum,
+                        fsum);
+}
+
+// Any even L: four consecutive pairs per step, which may lie in two rows.
+template <int KIND>
+__global__ __launch_bounds__(256) void energy_sites(Lattice lat, FastDiv by_row, FastDiv by_l) {
+    const uint32_t r = blockIdx.y, L = (uint32_t)lat.L, Lh = L >> 1, half = (uint32_t)lat.half, plane = L * Lh;
+    GAS const uint8_t *s0 = gptr((const uint8_t *)lat.spins) + (size_t)r * lat.N;
+    GAS const uint8_t *s1 = s0 + half;
+    int ksum = 0, upsum = 0, eqsum = 0, n = 0;
+    double fsum = 0.0;
+    for (uint32_t j0 = 4u * (blockIdx.x * 256u + threadIdx.x); j0 < half; j0 += 4u * 256u * gridDim.x, ++n) {
+        uint32_t row = div_by(j0, by_row), m = j0 - row * Lh;
+        uint32_t z = div_by(row, by_l), y = row - z * L;
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+            const uint32_t j = j0 + q;
+            const uint32_t jx = ((1u + y + z) & 1u) ? (m + 1u == Lh ? j + 1u - Lh : j + 1u) : (m == 0u ? j + Lh - 1u : j - 1u);
+            const int w = s0[j];
+            const int up = w + s0[jx] + s0[y + 1u == L ? j + Lh - plane : j + Lh] + s0[y == 0u ? j - Lh + plane : j - Lh] +
+                           s0[z + 1u == L ? j + plane - half : j + plane] + s0[z == 0u ? j - plane + half : j - plane];
+            const int b1 = s1[j];
+            ksum += b1 ? up : 6 - up;
+            upsum += b1 + w;
+            if (KIND == 0) {
+                eqsum += (gptr(lat.fbits)[half + j] >> 2) == b1;
+                eqsum += (gptr(lat.fbits)[j] >> 2) == w;
             } else {
-                fsum += (double)lat.fraw[lat.half + j] * (double)sp1;
-                fsum += (double)lat.fraw[j] * (double)sp0;
+                const double f1 = gptr(lat.fraw)[half + j], f0 = gptr(lat.fraw)[j];
+                fsum += b1 ? f1 : -f1;
+                fsum += w ? f0 : -f0;
+            }
+            if (++m == Lh) {
+                m = 0;
+                if (++y == L) {
+                    y = 0;
+                    ++z;
+                }
             }
         }
     }
-    __shared__ double red[3][4];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const double vb = wave_sum((double)bsum), vm = wave_sum((double)msum), vf = wave_sum(fsum);
-    if (lane == 0) {
-        red[0][wave] = vb;
-        red[1][wave] = vf;
-        red[2][wave] = vm;
+    block_partial<KIND>(gptr(lat.part) + ((size_t)blockIdx.x * lat.pstride + r) * 3, 4 * n, ksum, upsum, eqsum, fsum);
+}
+
+// Bit storage: a thread takes whole words of colour 1, as the bit sweep's
+// energy pass does (W1 is a multiple of the threads of the grid's row).
+template <int KIND>
+__global__ __launch_bounds__(256) void energy_bits(Lattice lat) {
+    const uint32_t r = blockIdx.y, W1 = (uint32_t)lat.N >> 6;
+    GAS const uint32_t *b0 = gptr((const uint32_t *)lat.bits) + (size_t)r * 2u * W1, *b1 = b0 + W1;
+    int ksum = 0, upsum = 0, eqsum = 0, n = 0;
+    double fsum = 0.0;
+    for (uint32_t w = blockIdx.x * 256u + threadIdx.x; w < W1; w += 256u * gridDim.x, ++n) {
+        const uint32_t S = bits_word(b1, w);
+        uint32_t W, U0, U1, U2;
+        bits_up_counts(lat, b0, w, 1u, W, U0, U1, U2);
+        ksum += bits_aligned(U0, U1, U2, S);
+        upsum += __popc(S) + __popc(W);
+        if (KIND == 0) {
+            eqsum += __popc(~(S ^ bits_word(gptr(lat.fbw) + W1, w))) + __popc(~(W ^ bits_word(gptr(lat.fbw), w)));
+        } else {
+            const uint32_t w0 = w & ~63u;
+            fsum += bits_field_sum(gptr(lat.fraw) + lat.half, w0, S) + bits_field_sum(gptr(lat.fraw), w0, W);
+        }
     }
-    __syncthreads();
-    if (threadIdx.x < 3) {
-        const double v = ((red[threadIdx.x][0] + red[threadIdx.x][1]) + red[threadIdx.x][2]) +
-                         red[threadIdx.x][3];
-        lat.part[((size_t)blockIdx.x * lat.pstride + r) * 3 + threadIdx.x] = v;
-    }
+    block_partial<KIND>(gptr(lat.part) + ((size_t)blockIdx.x * lat.pstride + r) * 3, 32 * n, ksum, upsum, eqsum, fsum);
 }
 
 __device__ __forceinline__ double energy_of(const Lattice &lat, double B, double F) {
@@ -1868,8 +1993,37 @@ hipError_t launch_unpack_bits(const Lattice &lat, hipStream_t s) {
     return hipGetLastError();
 }
 
+int energy_blocks(const Lattice &lat) {
+    // a step of every thread in each block, 64 blocks at most (the arena
+    // holds at least 64 partials per replica)
+    const int unit = lat.bits ? 256 * 32 : 256 * 4 * (lat.L % 32 == 0 ? 4 : 1);
+    return std::min(64, (lat.half + unit - 1) / unit);
+}
+
 hipError_t launch_energy(const Lattice &lat, hipStream_t s) {
-    hipLaunchKernelGGL(energy_kernel, dim3(lat.nblk, lat.R), dim3(256), 0, s, lat);
+    const dim3 grid((unsigned)lat.nblk, (unsigned)lat.R), block(256);
+    const FastDiv by_row = fast_div((uint32_t)lat.L / 2u), by_l = fast_div((uint32_t)lat.L);
+    if (lat.bits) {
+        if (lat.kind == 0)
+            hipLaunchKernelGGL(energy_bits<0>, grid, block, 0, s, lat);
+        else
+            hipLaunchKernelGGL(energy_bits<1>, grid, block, 0, s, lat);
+    } else if (lat.L % 32 == 0) {
+        if (lat.kind == 0)
+            hipLaunchKernelGGL((energy_rows<0, 4>), grid, block, 0, s, lat, by_row, by_l);
+        else
+            hipLaunchKernelGGL((energy_rows<1, 4>), grid, block, 0, s, lat, by_row, by_l);
+    } else if (lat.L % 8 == 0) {
+        if (lat.kind == 0)
+            hipLaunchKernelGGL((energy_rows<0, 1>), grid, block, 0, s, lat, by_row, by_l);
+        else
+            hipLaunchKernelGGL((energy_rows<1, 1>), grid, block, 0, s, lat, by_row, by_l);
+    } else {
+        if (lat.kind == 0)
+            hipLaunchKernelGGL(energy_sites<0>, grid, block, 0, s, lat, by_row, by_l);
+        else
+            hipLaunchKernelGGL(energy_sites<1>, grid, block, 0, s, lat, by_row, by_l);
+    }
     return hipGetLastError();
 }
 
