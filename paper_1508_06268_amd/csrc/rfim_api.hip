@@ -792,6 +792,8 @@ int sweep_impl(rfim *h, int64_t n, int every) {
                 HIPCHK(rfim_dev::launch_stream_sweep(ln, 0, q, 0, h->stream));
                 HIPCHK(rfim_dev::launch_stream_sweep(ln, 1, q, fused && q == m - 1, h->stream));
             }
+        } else if (rfim_dev::generic_resident(h->L)) {
+            HIPCHK(rfim_dev::launch_generic_resident(lat, m, fused ? 1 : 0, h->stream));
         } else {
             for (int q = 0; q < m; ++q) {
                 HIPCHK(rfim_dev::launch_generic_sweep(lat, 0, q, h->stream));

@@ -160,7 +160,15 @@ hipError_t launch_stream_sweep(const Launch &ln, int colour, int toff, int energ
 // Resident: nsweep whole sweeps in one launch (energy != 0: also the
 // energy partials of the final state).
 hipError_t launch_resident(const Launch &ln, int nsweep, int energy, hipStream_t s);
-// Any even L, one realization.
+// Other even L, one realization: half-sweeps (any L), or, up to
+// kGenericResidentMaxL, whole sweeps of LDS-resident replicas with the energy
+// partials of the final state.  Resident is the faster form while one
+// workgroup sweeps a replica in less time than two launches take: us a sweep
+// at R = 32, resident against half-sweeps, 3.9 and 8.0 at L = 24, 10.5 and
+// 10.2 at L = 28, 21 and 11 at L = 36.
+constexpr int kGenericResidentMaxL = 24;
+bool generic_resident(int L);
+hipError_t launch_generic_resident(const Lattice &lat, int nsweep, int energy, hipStream_t s);
 hipError_t launch_generic_sweep(const Lattice &lat, int colour, int toff, hipStream_t s);
 // Energy partials of the state at rest, lat.nblk per replica, from the bytes
 // or, in bit storage, the bits; energy_blocks: the count for a reduction that

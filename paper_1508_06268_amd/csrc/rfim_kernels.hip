@@ -138,52 +138,6 @@ __global__ __launch_bounds__(256) void init_kernel(Lattice lat, int r0) {
 }
 
 // ---------------------------------------------------------------------
-// Half-sweep, any even L: one thread per four consecutive sublattice
-// sites j = 4g..4g+3 of colour c (one Philox block), each site located
-// and its six neighbours gathered individually.
-// ---------------------------------------------------------------------
-template <int KIND>
-__global__ __launch_bounds__(256) void sweep_generic(Lattice lat, int colour, int toff) {
-    const int G = lat.half >> 2;
-    const int g = blockIdx.x * 256 + threadIdx.x;
-    const int r = blockIdx.y;
-    if (g >= G) return;
-    const uint32_t t = (uint32_t)(lat.ctrs[0] + (uint64_t)toff);
-    const Words w = philox10((uint32_t)g, 2u * t + (uint32_t)colour, (uint32_t)r,
-                             (kTagSweep << 28) | lat.rho, lat.key0, lat.key1);
-    const int slot = lat.r2t[r];
-    const int L = lat.L;
-    uint8_t *own = lat.spins + (size_t)r * lat.N + (size_t)colour * lat.half;
-    const uint8_t *oth = lat.spins + (size_t)r * lat.N + (size_t)(1 - colour) * lat.half;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int j = 4 * g + q;
-        const int i0 = 2 * j;
-        const int x0 = i0 % L, y = (i0 / L) % L, z = i0 / (L * L);
-        const int x = x0 + (((x0 + y + z) & 1) ^ colour);
-        const int xp = x + 1 == L ? 0 : x + 1, xm = x == 0 ? L - 1 : x - 1;
-        const int yp = y + 1 == L ? 0 : y + 1, ym = y == 0 ? L - 1 : y - 1;
-        const int zp = z + 1 == L ? 0 : z + 1, zm = z == 0 ? L - 1 : z - 1;
-        const int up = oth[(xp + L * (y + L * z)) >> 1] + oth[(xm + L * (y + L * z)) >> 1] +
-                       oth[(x + L * (yp + L * z)) >> 1] + oth[(x + L * (ym + L * z)) >> 1] +
-                       oth[(x + L * (y + L * zp)) >> 1] + oth[(x + L * (y + L * zm)) >> 1];
-        const int b = own[j];
-        const uint32_t u = word_at(w, q);
-        bool accept;
-        if (KIND == 0) {
-            const int f = lat.fbits[(size_t)colour * lat.half + j] >> 2;
-            const int idx = (up << 2) | (b << 1) | f;
-            const uint32_t *tab = lat.thr + slot * 32;
-            accept = u <= tab[idx] && !((tab[31] >> idx) & 1u);
-        } else {
-            const float a = -2.0f * 1.44269504088896341f * lat.betaf[slot];
-            accept = cont_accept((float)up, lat.fhf[(size_t)colour * lat.half + j], 2.0f * lat.Jf, a, b != 0, u);
-        }
-        if (accept) own[j] = (uint8_t)(b ^ 1);
-    }
-}
-
-// ---------------------------------------------------------------------
 // Half-sweep, L = 2^l >= 8, on one chunk of NW x 4 consecutive sublattice
 // sites of one row (NW Philox blocks): the spin bytes, the six neighbour
 // words and the field bytes are NW-dword loads, and the neighbour counts of
@@ -279,6 +233,68 @@ __device__ __forceinline__ Chunk chunk_geometry(uint32_t j0, uint32_t colour, ui
     c.jzp = (j0 + zstep) & jmask;
     c.jzm = (j0 - zstep) & jmask;
     return c;
+}
+
+// x / d for x < 2^31 by a multiplication (d >= 2): with 2^s < d <= 2^(s+1)
+// and mul = floor(2^(32+s) / d) + 1, mul d exceeds 2^(32+s) by at most d, so
+// the quotient is exact while x d < 2^(32+s), that is x < 2^31.
+struct FastDiv {
+    uint32_t mul, shift, d;
+};
+
+FastDiv fast_div(uint32_t d) {
+    uint32_t s = 0;
+    while ((2u << s) < d) ++s;
+    return FastDiv{d < 2 ? 0u : (uint32_t)((1ull << (32 + s)) / d) + 1u, s, d};
+}
+
+__device__ __forceinline__ uint32_t div_by(uint32_t x, const FastDiv &f) {
+    return f.d == 1u ? x : __umulhi(x, f.mul) >> f.shift;
+}
+
+// The geometry of a chunk when L is any multiple of 8 NW.
+template <int NW>
+__device__ __forceinline__ Chunk row_chunk(uint32_t j0, uint32_t colour, uint32_t L, const FastDiv &by_row,
+                                           const FastDiv &by_l) {
+    const uint32_t Lh = L >> 1, plane = L * Lh, half = L * plane;
+    const uint32_t row = div_by(j0, by_row), m0 = j0 - row * Lh;
+    const uint32_t z = div_by(row, by_l), y = row - z * L;
+    Chunk c;
+    c.p = (colour + y + z) & 1u;
+    c.jxw = j0 - m0 + (c.p ? (m0 + 4u * NW == Lh ? 0u : m0 + 4u * NW) : (m0 == 0u ? Lh : m0) - 4u);
+    c.jyp = y + 1u == L ? j0 + Lh - plane : j0 + Lh;
+    c.jym = y == 0u ? j0 - Lh + plane : j0 - Lh;
+    c.jzp = z + 1u == L ? j0 + plane - half : j0 + plane;
+    c.jzm = z == 0u ? j0 - plane + half : j0 - plane;
+    return c;
+}
+
+// Up counts of four consecutive pairs of any even L, which may lie in two
+// rows, one per byte; W = the other colour's sites of the same pairs.
+template <class P>
+__device__ __forceinline__ uint32_t site_counts(P oth, uint32_t j0, uint32_t W, uint32_t colour, uint32_t L,
+                                                const FastDiv &by_row, const FastDiv &by_l) {
+    const uint32_t Lh = L >> 1, plane = L * Lh, half = L * plane;
+    const uint32_t row = div_by(j0, by_row);
+    uint32_t m = j0 - row * Lh, z = div_by(row, by_l), y = row - z * L, U = W;
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+        const uint32_t j = j0 + q;
+        const uint32_t jx =
+            ((colour + y + z) & 1u) ? (m + 1u == Lh ? j + 1u - Lh : j + 1u) : (m == 0u ? j + Lh - 1u : j - 1u);
+        const uint32_t up = (uint32_t)oth[jx] + oth[y + 1u == L ? j + Lh - plane : j + Lh] +
+                            oth[y == 0u ? j - Lh + plane : j - Lh] + oth[z + 1u == L ? j + plane - half : j + plane] +
+                            oth[z == 0u ? j - plane + half : j - plane];
+        U += up << (8u * q);
+        if (++m == Lh) {
+            m = 0;
+            if (++y == L) {
+                y = 0;
+                ++z;
+            }
+        }
+    }
+    return U;
 }
 
 // The other-colour words around a chunk: the chunk's own pair words W, the
@@ -674,6 +690,134 @@ __global__ __launch_bounds__(256) void sweep_pow2(Lattice lat0, const Lattice *_
         block_partial<KIND>(gptr(lat.part) + ((size_t)gb * lat.pstride + r) * 3, 4 * NW, ksum, upsum, eqsum,
                             fsum);
     }
+}
+
+// ---------------------------------------------------------------------
+// Other even L (not a power of two, or below 8): four consecutive sublattice
+// sites j0..j0+3 (one Philox block) of colour c, their spins one dword.  With
+// ROWS (L a multiple of 8) they lie in one row and the neighbours are dwords,
+// as in the chunks above; otherwise the neighbours are gathered as bytes.
+// Returns the flips, one bit per byte; W and U are the other colour's sites
+// of the same pairs and the up counts.
+// ---------------------------------------------------------------------
+template <int KIND, bool ROWS, class P, class PB, class PF>
+__device__ __forceinline__ uint32_t any_flips(const Lattice &lat, const FastDiv &by_row, const FastDiv &by_l,
+                                              const uint32_t *sthr, uint32_t never, float a, P oth, PB fb_own,
+                                              PF hf_own, uint32_t j0, uint32_t Wown, uint32_t colour, uint32_t c1,
+                                              uint32_t r) {
+    uint32_t W[1], U[1], F4[1] = {0u};
+    f32x4 hf = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (KIND == 0)
+        load_words<1>(fb_own, j0, F4);
+    else
+        hf = *(typename rebind_ptr<PF, const f32x4>::type)(hf_own + j0);
+    if (ROWS) {
+        neighbour_counts<1>(oth, j0, row_chunk<1>(j0, colour, (uint32_t)lat.L, by_row, by_l), W, U);
+    } else {
+        load_words<1>(oth, j0, W);
+        U[0] = site_counts(oth, j0, W[0], colour, (uint32_t)lat.L, by_row, by_l);
+    }
+    const Words rw = philox10(j0 >> 2, c1, r, (kTagSweep << 28) | lat.rho, lat.key0, lat.key1);
+    if (KIND == 0)
+        return never != 0u ? bimodal_flips<true>(sthr, U[0], Wown, F4[0], rw, never)
+                           : bimodal_flips<false>(sthr, U[0], Wown, F4[0], rw, never);
+    const float h[4] = {hf.x, hf.y, hf.z, hf.w};
+    uint32_t fl = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float up = (float)((U[0] >> (8 * q)) & 0xFFu);
+        if (cont_accept(up, h[q], 2.0f * lat.Jf, a, ((Wown >> (8 * q)) & 1u) != 0, word_at(rw, q))) fl |= 1u << (8 * q);
+    }
+    return fl;
+}
+
+// Half-sweep, one thread per block of four sites, grid (blocks, R).
+// L = 48, R = 32, +-1 fields: 5.5 us a launch against 12.3 with a division
+// per coordinate and site, byte neighbours and the table read from memory;
+// about 4 us of it are the launch.
+template <int KIND, bool ROWS>
+__global__ __launch_bounds__(256) void sweep_generic(Lattice lat, FastDiv by_row, FastDiv by_l, int colour, int toff) {
+    __shared__ __align__(16) uint32_t sthr[32];
+    const uint32_t r = blockIdx.y, half = (uint32_t)lat.half, col = (uint32_t)colour;
+    const uint32_t j0 = 4u * (blockIdx.x * 256u + threadIdx.x);
+    GAS uint8_t *own = gptr(lat.spins) + (size_t)r * lat.N + (size_t)col * half;
+    GAS const uint8_t *oth = gptr((const uint8_t *)lat.spins) + (size_t)r * lat.N + (size_t)(1u - col) * half;
+    const int slot = gptr(lat.r2t)[r];
+    const uint32_t t = (uint32_t)(gptr(lat.ctrs)[0] + (uint64_t)toff);
+    uint32_t never = 0;
+    float a = 0.0f;
+    if (KIND == 0) {
+        if (threadIdx.x < 32u) sthr[threadIdx.x] = gptr(lat.thr)[slot * 32 + threadIdx.x];
+        __syncthreads();
+        never = __builtin_amdgcn_readfirstlane(sthr[31]);
+    } else {
+        a = -2.0f * 1.44269504088896341f * gptr(lat.betaf)[slot];
+    }
+    if (j0 >= half) return;
+    uint32_t Wown[1];
+    load_words<1>(own, j0, Wown);
+    const uint32_t fl = any_flips<KIND, ROWS>(lat, by_row, by_l, sthr, never, a, oth, gptr(lat.fbits) + (size_t)col * half,
+                                              gptr(lat.fhf) + (size_t)col * half, j0, Wown[0], col, 2u * t + col, r);
+    if (fl) *(GAS uint32_t *)(own + j0) = Wown[0] ^ fl;
+}
+
+// Resident form (L <= kGenericResidentMaxL): one workgroup holds one
+// replica's spins in LDS for `nsweep` whole sweeps and writes the energy
+// partial of the final state, as sweep_resident does for powers of two.
+template <int KIND, bool ROWS>
+__global__ __launch_bounds__(1024) void sweep_generic_resident(Lattice lat, FastDiv by_row, FastDiv by_l, int nsweep,
+                                                                int energy) {
+    extern __shared__ uint4 lds_raw[];
+    __shared__ __align__(16) uint32_t sthr[32];
+    uint8_t *sp = (uint8_t *)lds_raw;                  // [2][half]
+    uint32_t *lds1 = (uint32_t *)lds_raw;
+    const uint32_t r = blockIdx.x, half = (uint32_t)lat.half, words = (uint32_t)lat.N >> 2;
+    const int slot = gptr(lat.r2t)[r];
+    // N is a multiple of 8: whole dwords
+    GAS uint32_t *home = (GAS uint32_t *)(gptr(lat.spins) + (size_t)r * lat.N);
+    for (uint32_t q = threadIdx.x; q < words; q += blockDim.x) lds1[q] = home[q];
+    if (KIND == 0 && threadIdx.x < 32u) sthr[threadIdx.x] = gptr(lat.thr)[slot * 32 + threadIdx.x];
+    const float a = KIND == 1 ? -2.0f * 1.44269504088896341f * gptr(lat.betaf)[slot] : 0.0f;
+    const uint32_t t0 = (uint32_t)gptr(lat.ctrs)[0];
+    GAS const uint8_t *fbits = gptr(lat.fbits);
+    GAS const float *fhf = gptr(lat.fhf), *fraw = gptr(lat.fraw);
+    __syncthreads();
+    const uint32_t never = KIND == 0 ? __builtin_amdgcn_readfirstlane(sthr[31]) : 0u;
+    for (int sw = 0; sw < nsweep; ++sw) {
+        for (uint32_t col = 0; col < 2; ++col) {
+            uint8_t *own = sp + col * half;
+            const uint8_t *oth = sp + (1u - col) * half;
+            const uint32_t c1 = 2u * (t0 + (uint32_t)sw) + col;
+            for (uint32_t j0 = 4u * threadIdx.x; j0 < half; j0 += 4u * blockDim.x) {
+                uint32_t Wown[1];
+                load_words<1>((const uint8_t *)own, j0, Wown);
+                const uint32_t fl =
+                    any_flips<KIND, ROWS>(lat, by_row, by_l, sthr, never, a, oth, fbits + (size_t)col * half,
+                                          fhf + (size_t)col * half, j0, Wown[0], col, c1, r);
+                if (fl) *(uint32_t *)(own + j0) = Wown[0] ^ fl;
+            }
+            __syncthreads();
+        }
+    }
+    if (energy) {
+        int ksum = 0, upsum = 0, eqsum = 0, n = 0;
+        double fsum = 0.0;
+        const uint8_t *s0 = sp, *s1 = sp + half;
+        for (uint32_t j0 = 4u * threadIdx.x; j0 < half; j0 += 4u * blockDim.x, ++n) {
+            uint32_t S1[1], W[1], U[1], F1[1];
+            load_words<1>(s1, j0, S1);
+            if (KIND == 0) load_words<1>(fbits + half, j0, F1);
+            if (ROWS) {
+                neighbour_counts<1>(s0, j0, row_chunk<1>(j0, 1u, (uint32_t)lat.L, by_row, by_l), W, U);
+            } else {
+                load_words<1>(s0, j0, W);
+                U[0] = site_counts(s0, j0, W[0], 1u, (uint32_t)lat.L, by_row, by_l);
+            }
+            chunk_energy<KIND, 1>(lat, S1, W, U, F1, fbits, fraw + half, fraw, j0, ksum, upsum, eqsum, fsum);
+        }
+        block_partial<KIND>(gptr(lat.part) + (size_t)r * 3, 4 * n, ksum, upsum, eqsum, fsum);
+    }
+    for (uint32_t q = threadIdx.x; q < words; q += blockDim.x) home[q] = lds1[q];
 }
 
 // Resident sweeps (L = 2^l <= 32): one workgroup holds one replica's spins
@@ -1372,27 +1516,10 @@ __global__ __launch_bounds__(256) void unpack_bits_kernel(Lattice lat) {
 // and then read one site per step with divisions by L (126 and 336 us).
 // ---------------------------------------------------------------------
 
-// x / d for x < 2^31 by a multiplication (d >= 2): with 2^s < d <= 2^(s+1)
-// and mul = floor(2^(32+s) / d) + 1, mul d exceeds 2^(32+s) by at most d, so
-// the quotient is exact while x d < 2^(32+s), that is x < 2^31.
-struct FastDiv {
-    uint32_t mul, shift, d;
-};
-
-FastDiv fast_div(uint32_t d) {
-    uint32_t s = 0;
-    while ((2u << s) < d) ++s;
-    return FastDiv{d < 2 ? 0u : (uint32_t)((1ull << (32 + s)) / d) + 1u, s, d};
-}
-
-__device__ __forceinline__ uint32_t div_by(uint32_t x, const FastDiv &f) {
-    return f.d == 1u ? x : __umulhi(x, f.mul) >> f.shift;
-}
-
 // Rows of whole dwords (L a multiple of 8 NW): chunks as in the sweeps.
 template <int KIND, int NW>
 __global__ __launch_bounds__(256) void energy_rows(Lattice lat, FastDiv by_row, FastDiv by_l) {
-    const uint32_t r = blockIdx.y, L = (uint32_t)lat.L, Lh = L >> 1, half = (uint32_t)lat.half, plane = L * Lh;
+    const uint32_t r = blockIdx.y, L = (uint32_t)lat.L, half = (uint32_t)lat.half;
     GAS const uint8_t *s0 = gptr((const uint8_t *)lat.spins) + (size_t)r * lat.N;
     GAS const uint8_t *s1 = s0 + half;
     GAS const uint8_t *fbits = gptr(lat.fbits);
@@ -1400,15 +1527,7 @@ __global__ __launch_bounds__(256) void energy_rows(Lattice lat, FastDiv by_row, 
     int ksum = 0, upsum = 0, eqsum = 0, n = 0;
     double fsum = 0.0;
     for (uint32_t j0 = 4u * NW * (blockIdx.x * 256u + threadIdx.x); j0 < half; j0 += 4u * NW * 256u * gridDim.x, ++n) {
-        const uint32_t row = div_by(j0, by_row), m0 = j0 - row * Lh;
-        const uint32_t z = div_by(row, by_l), y = row - z * L;
-        Chunk c;
-        c.p = (1u + y + z) & 1u;
-        c.jxw = j0 - m0 + (c.p ? (m0 + 4u * NW == Lh ? 0u : m0 + 4u * NW) : (m0 == 0u ? Lh : m0) - 4u);
-        c.jyp = y + 1u == L ? j0 + Lh - plane : j0 + Lh;
-        c.jym = y == 0u ? j0 - Lh + plane : j0 - Lh;
-        c.jzp = z + 1u == L ? j0 + plane - half : j0 + plane;
-        c.jzm = z == 0u ? j0 - plane + half : j0 - plane;
+        const Chunk c = row_chunk<NW>(j0, 1u, L, by_row, by_l);
         uint32_t S1[NW], W[NW], U[NW], F1[NW];
         load_words<NW>(s1, j0, S1);
         if (KIND == 0) load_words<NW>(fbits + half, j0, F1);
@@ -1422,40 +1541,20 @@ __global__ __launch_bounds__(256) void energy_rows(Lattice lat, FastDiv by_row, 
 // Any even L: four consecutive pairs per step, which may lie in two rows.
 template <int KIND>
 __global__ __launch_bounds__(256) void energy_sites(Lattice lat, FastDiv by_row, FastDiv by_l) {
-    const uint32_t r = blockIdx.y, L = (uint32_t)lat.L, Lh = L >> 1, half = (uint32_t)lat.half, plane = L * Lh;
+    const uint32_t r = blockIdx.y, half = (uint32_t)lat.half;
     GAS const uint8_t *s0 = gptr((const uint8_t *)lat.spins) + (size_t)r * lat.N;
     GAS const uint8_t *s1 = s0 + half;
+    GAS const uint8_t *fbits = gptr(lat.fbits);
+    GAS const float *fraw = gptr(lat.fraw);
     int ksum = 0, upsum = 0, eqsum = 0, n = 0;
     double fsum = 0.0;
     for (uint32_t j0 = 4u * (blockIdx.x * 256u + threadIdx.x); j0 < half; j0 += 4u * 256u * gridDim.x, ++n) {
-        uint32_t row = div_by(j0, by_row), m = j0 - row * Lh;
-        uint32_t z = div_by(row, by_l), y = row - z * L;
-#pragma unroll
-        for (uint32_t q = 0; q < 4; ++q) {
-            const uint32_t j = j0 + q;
-            const uint32_t jx = ((1u + y + z) & 1u) ? (m + 1u == Lh ? j + 1u - Lh : j + 1u) : (m == 0u ? j + Lh - 1u : j - 1u);
-            const int w = s0[j];
-            const int up = w + s0[jx] + s0[y + 1u == L ? j + Lh - plane : j + Lh] + s0[y == 0u ? j - Lh + plane : j - Lh] +
-                           s0[z + 1u == L ? j + plane - half : j + plane] + s0[z == 0u ? j - plane + half : j - plane];
-            const int b1 = s1[j];
-            ksum += b1 ? up : 6 - up;
-            upsum += b1 + w;
-            if (KIND == 0) {
-                eqsum += (gptr(lat.fbits)[half + j] >> 2) == b1;
-                eqsum += (gptr(lat.fbits)[j] >> 2) == w;
-            } else {
-                const double f1 = gptr(lat.fraw)[half + j], f0 = gptr(lat.fraw)[j];
-                fsum += b1 ? f1 : -f1;
-                fsum += w ? f0 : -f0;
-            }
-            if (++m == Lh) {
-                m = 0;
-                if (++y == L) {
-                    y = 0;
-                    ++z;
-                }
-            }
-        }
+        uint32_t S1[1], W[1], U[1], F1[1];
+        load_words<1>(s1, j0, S1);
+        load_words<1>(s0, j0, W);
+        if (KIND == 0) load_words<1>(fbits + half, j0, F1);
+        U[0] = site_counts(s0, j0, W[0], 1u, (uint32_t)lat.L, by_row, by_l);
+        chunk_energy<KIND, 1>(lat, S1, W, U, F1, fbits, fraw + half, fraw, j0, ksum, upsum, eqsum, fsum);
     }
     block_partial<KIND>(gptr(lat.part) + ((size_t)blockIdx.x * lat.pstride + r) * 3, 4 * n, ksum, upsum, eqsum, fsum);
 }
@@ -1724,6 +1823,7 @@ bool shape_valid(int L, int mode, int nw, int wg) {
 
 int blocks_per_replica(int L, int mode, int nw, int wg) {
     const bool pow2 = L >= 8 && (L & (L - 1)) == 0;
+    if (generic_resident(L)) return 1;
     if (!pow2) {
         const long long G = (long long)L * L * L / 8;
         long long nb = (G + 255) / 256;
@@ -1745,7 +1845,7 @@ int stream_blocks_per_replica(int L, int nw, int wg) {
 }
 
 bool fused_energy(const Lattice &lat) {
-    if (lat.log2L < 3) return false;
+    if (lat.log2L < 3) return generic_resident(lat.L);
     if (lat.mode >= 1) return true;
     const long long chunks = (long long)lat.N / 8 / lat.nw;
     return chunks <= (long long)lat.wg * kMaxFusedBlocks;
@@ -1875,14 +1975,40 @@ hipError_t launch_resident(const Launch &ln, int nsweep, int energy, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_generic_sweep(const Lattice &lat, int colour, int toff, hipStream_t s) {
+bool generic_resident(int L) { return L <= kGenericResidentMaxL && !(L >= 8 && (L & (L - 1)) == 0); }
+
+template <int KIND, bool ROWS>
+static void launch_generic_form(const Lattice &lat, int colour, int toff, int nsweep, int energy, hipStream_t s) {
+    const FastDiv by_row = fast_div((uint32_t)lat.L / 2u), by_l = fast_div((uint32_t)lat.L);
     const int G = lat.half >> 2;
-    dim3 grid((G + 255) / 256, lat.R);
+    if (nsweep > 0) {
+        const unsigned wg = (unsigned)std::min(1024, (G + 63) / 64 * 64);
+        hipLaunchKernelGGL((sweep_generic_resident<KIND, ROWS>), dim3((unsigned)lat.R), dim3(wg), (size_t)lat.N, s, lat,
+                           by_row, by_l, nsweep, energy);
+    } else {
+        hipLaunchKernelGGL((sweep_generic<KIND, ROWS>), dim3((unsigned)((G + 255) / 256), (unsigned)lat.R), dim3(256), 0,
+                           s, lat, by_row, by_l, colour, toff);
+    }
+}
+
+static hipError_t launch_generic(const Lattice &lat, int colour, int toff, int nsweep, int energy, hipStream_t s) {
+    const bool rows = lat.L % 8 == 0;
     if (lat.kind == 0)
-        hipLaunchKernelGGL(sweep_generic<0>, grid, dim3(256), 0, s, lat, colour, toff);
+        rows ? launch_generic_form<0, true>(lat, colour, toff, nsweep, energy, s)
+             : launch_generic_form<0, false>(lat, colour, toff, nsweep, energy, s);
     else
-        hipLaunchKernelGGL(sweep_generic<1>, grid, dim3(256), 0, s, lat, colour, toff);
+        rows ? launch_generic_form<1, true>(lat, colour, toff, nsweep, energy, s)
+             : launch_generic_form<1, false>(lat, colour, toff, nsweep, energy, s);
     return hipGetLastError();
+}
+
+hipError_t launch_generic_sweep(const Lattice &lat, int colour, int toff, hipStream_t s) {
+    return launch_generic(lat, colour, toff, 0, 0, s);
+}
+
+hipError_t launch_generic_resident(const Lattice &lat, int nsweep, int energy, hipStream_t s) {
+    if (nsweep < 1) return hipSuccess;
+    return launch_generic(lat, 0, 0, nsweep, energy, s);
 }
 
 int slab_sweeps_per_launch(int mode) { return mode >= 2 ? mode - 1 : 0; }
