@@ -104,7 +104,8 @@ typedef struct rfim_params {
  * library (create, rfim_set_measure, destroy).  A handle asks for one block
  * at create time (all its buffers), at most two more for its default
  * storage and shape (the bit arrays of handles that start in bits, the
- * second spin buffer of a slab shape), one when a slab shape is first set, two for
+ * second spin buffer of a slab shape or, at L not a power of two, of the
+ * slabs a handle of few replicas runs on), one when a slab shape is first set, two for
  * bit storage, and three when rfim_set_measure first turns the measurement
  * on.  A caching allocator (e.g. PyTorch's) can serve them. */
 typedef struct rfim_alloc {

@@ -192,6 +192,7 @@ struct rfim {
     double *d_F = nullptr;
     int nblk = 1;
     int mode = 0, nw = 0, wg = 0;   // launch shape (see rfim_set_launch_shape)
+    rfim_dev::BoxPlan box = {0, 0}; // boxes (L not a power of two), planes = 0: none
     // device copy of lattice() and the workgroup maps of the sweep launches
     Lattice lat_host;
     Lattice *d_lat = nullptr;
@@ -590,6 +591,32 @@ int compute_components(rfim *h) {
 // replicas start on a slab shape (rfim_create_ex).
 constexpr int kSlabDefaultMaxReplicas = 64;
 
+// Energy partials per replica of a handle in byte storage.
+int byte_partials(const rfim *h) {
+    if (h->box.planes) return (h->L + h->box.planes - 1) / h->box.planes;
+    return rfim_dev::blocks_per_replica(h->L, h->mode, h->nw, h->wg);
+}
+
+// Boxes of less than a replica need a second spin buffer; handles whose spins
+// take more than this keep half-sweeps (and so does one whose second buffer
+// cannot be had).
+constexpr size_t kBoxMaxBytes = (size_t)1 << 30;
+
+// Sets up boxes where they are the better form for the handle's capacity.
+int use_boxes(rfim *h) {
+    const rfim_dev::BoxPlan plan = rfim_dev::box_plan(h->L, h->R_cap);
+    if (!plan.planes) return RFIM_OK;
+    if (plan.planes < h->L) {               // slabs: not in place
+        if ((size_t)h->R_cap * h->N > kBoxMaxBytes) return RFIM_OK;
+        const int rc = dev_alloc(h, (void **)&h->d_spins_own, (size_t)h->R_cap * h->N);
+        if (rc) return rc;
+        h->d_spins_alt = h->d_spins_own;
+    }
+    h->box = plan;
+    h->nblk = byte_partials(h);
+    return sync_descriptor(h);
+}
+
 // Default launch shape: lattices up to L = 32 run LDS-resident (streaming
 // is launch-bound there), larger ones stream with four dwords per thread.
 // The autotuner in the Python package measures and overrides these.
@@ -751,7 +778,7 @@ int sweep_impl(rfim *h, int64_t n, int every) {
         int64_t to_next = every > 0 ? (int64_t)(every - (int64_t)(h->t % (uint64_t)every)) : remaining;
         const int m = (int)std::min<int64_t>(remaining, to_next);
         const bool exch = every > 0 && m == to_next;
-        const bool fused = exch && !tiled && (bitsm || rfim_dev::fused_energy(lat));
+        const bool fused = exch && !tiled && (bitsm || h->box.planes || rfim_dev::fused_energy(lat));
         if (bitsm) {
             for (int q = 0; q < m; ++q) {
                 const int e = fused && q == m - 1;
@@ -792,6 +819,18 @@ int sweep_impl(rfim *h, int64_t n, int every) {
                 HIPCHK(rfim_dev::launch_stream_sweep(ln, 0, q, 0, h->stream));
                 HIPCHK(rfim_dev::launch_stream_sweep(ln, 1, q, fused && q == m - 1, h->stream));
             }
+        } else if (h->box.planes) {
+            // as many launches as the plan's sweeps need, of about equal length
+            const bool whole = h->box.planes >= h->L;       // in place, any number of sweeps
+            for (int q = 0; q < m;) {
+                const int left = whole ? 1 : (m - q + h->box.sweeps - 1) / h->box.sweeps, ns = (m - q + left - 1) / left;
+                const int e = fused && q + ns == m;
+                HIPCHK(rfim_dev::launch_box(lat, h->d_spins, whole ? h->d_spins : h->d_spins_alt, h->box, ns, q, e,
+                                            h->stream));
+                if (!whole) std::swap(h->d_spins, h->d_spins_alt);
+                q += ns;
+            }
+            h->lat_host = h->lattice();
         } else if (rfim_dev::generic_resident(h->L)) {
             HIPCHK(rfim_dev::launch_generic_resident(lat, m, fused ? 1 : 0, h->stream));
         } else {
@@ -877,6 +916,10 @@ rfim_t *rfim_create_ex(const rfim_params_t *params, const rfim_alloc_t *alloc, v
     // keeps the resident shape
     if (h->kind == 1 && h->L == 32 && h->R_cap <= kSlabDefaultMaxReplicas &&
         rfim_set_launch_shape(h, 3, 4, 1024) != RFIM_OK) {
+        (void)hipGetLastError();
+        g_error.clear();
+    }
+    if (use_boxes(h) != RFIM_OK) {
         (void)hipGetLastError();
         g_error.clear();
     }
@@ -1184,7 +1227,7 @@ int rfim_set_launch_shape(rfim_t *h, int mode, int nw, int wg) {
     h->mode = mode;
     h->nw = nw;
     h->wg = wg;
-    h->nblk = rfim_dev::blocks_per_replica(h->L, mode, nw, wg);
+    h->nblk = byte_partials(h);
     return sync_descriptor(h);
 }
 

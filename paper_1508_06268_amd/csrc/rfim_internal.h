@@ -160,15 +160,27 @@ hipError_t launch_stream_sweep(const Launch &ln, int colour, int toff, int energ
 // Resident: nsweep whole sweeps in one launch (energy != 0: also the
 // energy partials of the final state).
 hipError_t launch_resident(const Launch &ln, int nsweep, int energy, hipStream_t s);
-// Other even L, one realization: half-sweeps (any L), or, up to
-// kGenericResidentMaxL, whole sweeps of LDS-resident replicas with the energy
-// partials of the final state.  Resident is the faster form while one
-// workgroup sweeps a replica in less time than two launches take: us a sweep
-// at R = 32, resident against half-sweeps, 3.9 and 8.0 at L = 24, 10.5 and
-// 10.2 at L = 28, 21 and 11 at L = 36.
-constexpr int kGenericResidentMaxL = 24;
+// Other even L, one realization: half-sweeps (any L), or whole sweeps of
+// LDS-resident replicas with the energy partials of the final state: for L = 4
+// and the small L whose planes do not split into whole Philox blocks (L % 4 ==
+// 2; the others have boxes, below), as long as one workgroup sweeps a replica
+// in less time than two launches take (us a sweep at R = 32, resident against
+// half-sweeps: 2.8 and 7.8 at L = 10; about even at L = 26).
+constexpr int kGenericResidentMaxL = 22;
 bool generic_resident(int L);
 hipError_t launch_generic_resident(const Lattice &lat, int nsweep, int energy, hipStream_t s);
+// Boxes (L a multiple of 4, not a power of two): slabs of `planes` planes, up
+// to `sweeps` whole sweeps a launch, from src to dst (a second spin buffer).
+// box_plan: the split for R replicas, planes = 0 where half-sweeps or the
+// resident form are the better one.
+constexpr int kMaxBoxSlabs = 64;            // one energy partial each
+constexpr int kBoxMaxL = 88;                // a plane's blocks within one workgroup's threads
+struct BoxPlan {
+    int planes, sweeps;
+};
+BoxPlan box_plan(int L, int R);
+hipError_t launch_box(const Lattice &lat, const uint8_t *src, uint8_t *dst, const BoxPlan &plan, int nsweep, int toff,
+                      int energy, hipStream_t s);
 hipError_t launch_generic_sweep(const Lattice &lat, int colour, int toff, hipStream_t s);
 // Energy partials of the state at rest, lat.nblk per replica, from the bytes
 // or, in bit storage, the bits; energy_blocks: the count for a reduction that

@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 
 #include "rfim_internal.h"
 
@@ -697,51 +698,90 @@ __global__ __launch_bounds__(256) void sweep_pow2(Lattice lat0, const Lattice *_
 // sites j0..j0+3 (one Philox block) of colour c, their spins one dword.  With
 // ROWS (L a multiple of 8) they lie in one row and the neighbours are dwords,
 // as in the chunks above; otherwise the neighbours are gathered as bytes.
-// Returns the flips, one bit per byte; W and U are the other colour's sites
-// of the same pairs and the up counts.
 // ---------------------------------------------------------------------
-template <int KIND, bool ROWS, class P, class PB, class PF>
-__device__ __forceinline__ uint32_t any_flips(const Lattice &lat, const FastDiv &by_row, const FastDiv &by_l,
-                                              const uint32_t *sthr, uint32_t never, float a, P oth, PB fb_own,
-                                              PF hf_own, uint32_t j0, uint32_t Wown, uint32_t colour, uint32_t c1,
-                                              uint32_t r) {
-    uint32_t W[1], U[1], F4[1] = {0u};
+
+// What a site's field contributes: the +-1 field bits of the block, or its
+// four continuous fields.
+template <int KIND> struct BlockField {
+    uint32_t F4 = 0u;
     f32x4 hf = {0.0f, 0.0f, 0.0f, 0.0f};
+};
+
+template <int KIND, class PB, class PF>
+__device__ __forceinline__ BlockField<KIND> block_field(PB fb_own, PF hf_own, uint32_t j0) {
+    BlockField<KIND> f;
     if (KIND == 0)
-        load_words<1>(fb_own, j0, F4);
+        f.F4 = *(typename rebind_ptr<PB, const uint32_t>::type)(fb_own + j0);
     else
-        hf = *(typename rebind_ptr<PF, const f32x4>::type)(hf_own + j0);
-    if (ROWS) {
-        neighbour_counts<1>(oth, j0, row_chunk<1>(j0, colour, (uint32_t)lat.L, by_row, by_l), W, U);
-    } else {
-        load_words<1>(oth, j0, W);
-        U[0] = site_counts(oth, j0, W[0], colour, (uint32_t)lat.L, by_row, by_l);
-    }
-    const Words rw = philox10(j0 >> 2, c1, r, (kTagSweep << 28) | lat.rho, lat.key0, lat.key1);
+        f.hf = *(typename rebind_ptr<PF, const f32x4>::type)(hf_own + j0);
+    return f;
+}
+
+// The flips of a block, one bit per byte, from its up counts.
+template <int KIND>
+__device__ __forceinline__ uint32_t block_flips(const Lattice &lat, const uint32_t *sthr, uint32_t never, float a,
+                                                const BlockField<KIND> &f, uint32_t U, uint32_t Wown, uint32_t g,
+                                                uint32_t c1, uint32_t r) {
+    const Words rw = philox10(g, c1, r, (kTagSweep << 28) | lat.rho, lat.key0, lat.key1);
     if (KIND == 0)
-        return never != 0u ? bimodal_flips<true>(sthr, U[0], Wown, F4[0], rw, never)
-                           : bimodal_flips<false>(sthr, U[0], Wown, F4[0], rw, never);
-    const float h[4] = {hf.x, hf.y, hf.z, hf.w};
+        return never != 0u ? bimodal_flips<true>(sthr, U, Wown, f.F4, rw, never)
+                           : bimodal_flips<false>(sthr, U, Wown, f.F4, rw, never);
+    const float h[4] = {f.hf.x, f.hf.y, f.hf.z, f.hf.w};
     uint32_t fl = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const float up = (float)((U[0] >> (8 * q)) & 0xFFu);
+        const float up = (float)((U >> (8 * q)) & 0xFFu);
         if (cont_accept(up, h[q], 2.0f * lat.Jf, a, ((Wown >> (8 * q)) & 1u) != 0, word_at(rw, q))) fl |= 1u << (8 * q);
     }
     return fl;
 }
 
+// The same for a block of a whole replica in LDS, its neighbours gathered.
+template <int KIND, class P, class PB, class PF>
+__device__ __forceinline__ uint32_t any_flips(const Lattice &lat, const FastDiv &by_row, const FastDiv &by_l,
+                                              const uint32_t *sthr, uint32_t never, float a, P oth, PB fb_own,
+                                              PF hf_own, uint32_t j0, uint32_t Wown, uint32_t colour, uint32_t c1,
+                                              uint32_t r) {
+    const BlockField<KIND> f = block_field<KIND>(fb_own, hf_own, j0);
+    uint32_t W[1];
+    load_words<1>(oth, j0, W);
+    const uint32_t U = site_counts(oth, j0, W[0], colour, (uint32_t)lat.L, by_row, by_l);
+    return block_flips<KIND>(lat, sthr, never, a, f, U, Wown, j0 >> 2, c1, r);
+}
+
 // Half-sweep, one thread per block of four sites, grid (blocks, R).
-// L = 48, R = 32, +-1 fields: 5.5 us a launch against 12.3 with a division
+// L = 48, R = 32, +-1 fields: 4.5 us a launch against 12.3 with a division
 // per coordinate and site, byte neighbours and the table read from memory;
-// about 4 us of it are the launch.
+// about 3.5 us of it are the launch.  L = 80, R = 32: 11 us (12.2 without the
+// XCD ranges; several replicas per thread were no faster).
 template <int KIND, bool ROWS>
-__global__ __launch_bounds__(256) void sweep_generic(Lattice lat, FastDiv by_row, FastDiv by_l, int colour, int toff) {
+__global__ __launch_bounds__(256) void sweep_generic(Lattice lat, FastDiv by_row, FastDiv by_l, FastDiv by_blocks, int colour,
+                                                     int toff) {
     __shared__ __align__(16) uint32_t sthr[32];
-    const uint32_t r = blockIdx.y, half = (uint32_t)lat.half, col = (uint32_t)colour;
-    const uint32_t j0 = 4u * (blockIdx.x * 256u + threadIdx.x);
+    // a contiguous range of blocks for each of the 8 XCDs (ids go round-robin
+    // to them), so that the planes above and below are in its L2
+    const uint32_t per = gridDim.x >> 3;
+    const uint32_t blk = blockIdx.x < 8u * per ? (blockIdx.x & 7u) * per + (blockIdx.x >> 3) : blockIdx.x;
+    const uint32_t r = div_by(blk, by_blocks), half = (uint32_t)lat.half, col = (uint32_t)colour;
+    const uint32_t j0 = 4u * ((blk - r * by_blocks.d) * 256u + threadIdx.x);
     GAS uint8_t *own = gptr(lat.spins) + (size_t)r * lat.N + (size_t)col * half;
     GAS const uint8_t *oth = gptr((const uint8_t *)lat.spins) + (size_t)r * lat.N + (size_t)(1u - col) * half;
+    // the block's loads go out first, the slot's table behind them (its two
+    // round trips overlap theirs)
+    const bool in = j0 < half;
+    const uint32_t j = in ? j0 : 0u;
+    const BlockField<KIND> f = block_field<KIND>(gptr(lat.fbits) + (size_t)col * half, gptr(lat.fhf) + (size_t)col * half, j);
+    const uint32_t Wown = *(GAS const uint32_t *)(own + j);
+    Around<1> ar;
+    Chunk c;
+    uint32_t U[1];
+    if (ROWS) {
+        c = row_chunk<1>(j, col, (uint32_t)lat.L, by_row, by_l);
+        load_around<1>(oth, j, c, ar);
+    } else {
+        U[0] = site_counts(oth, j, *(GAS const uint32_t *)(oth + j), col, (uint32_t)lat.L, by_row, by_l);
+    }
+    __builtin_amdgcn_sched_barrier(0);
     const int slot = gptr(lat.r2t)[r];
     const uint32_t t = (uint32_t)(gptr(lat.ctrs)[0] + (uint64_t)toff);
     uint32_t never = 0;
@@ -753,18 +793,16 @@ __global__ __launch_bounds__(256) void sweep_generic(Lattice lat, FastDiv by_row
     } else {
         a = -2.0f * 1.44269504088896341f * gptr(lat.betaf)[slot];
     }
-    if (j0 >= half) return;
-    uint32_t Wown[1];
-    load_words<1>(own, j0, Wown);
-    const uint32_t fl = any_flips<KIND, ROWS>(lat, by_row, by_l, sthr, never, a, oth, gptr(lat.fbits) + (size_t)col * half,
-                                              gptr(lat.fhf) + (size_t)col * half, j0, Wown[0], col, 2u * t + col, r);
-    if (fl) *(GAS uint32_t *)(own + j0) = Wown[0] ^ fl;
+    if (ROWS) neighbour_sums<1>(c, ar, U);
+    const uint32_t fl = block_flips<KIND>(lat, sthr, never, a, f, U[0], Wown, j >> 2, 2u * t + col, r);
+    if (in && fl) *(GAS uint32_t *)(own + j0) = Wown ^ fl;
 }
 
-// Resident form (L <= kGenericResidentMaxL): one workgroup holds one
-// replica's spins in LDS for `nsweep` whole sweeps and writes the energy
-// partial of the final state, as sweep_resident does for powers of two.
-template <int KIND, bool ROWS>
+// Resident form (small L whose colour-planes do not hold whole blocks): one
+// workgroup holds one replica's spins in LDS for `nsweep` whole sweeps and
+// writes the energy partial of the final state, as sweep_resident does for
+// powers of two.
+template <int KIND>
 __global__ __launch_bounds__(1024) void sweep_generic_resident(Lattice lat, FastDiv by_row, FastDiv by_l, int nsweep,
                                                                 int energy) {
     extern __shared__ uint4 lds_raw[];
@@ -792,7 +830,7 @@ __global__ __launch_bounds__(1024) void sweep_generic_resident(Lattice lat, Fast
                 uint32_t Wown[1];
                 load_words<1>((const uint8_t *)own, j0, Wown);
                 const uint32_t fl =
-                    any_flips<KIND, ROWS>(lat, by_row, by_l, sthr, never, a, oth, fbits + (size_t)col * half,
+                    any_flips<KIND>(lat, by_row, by_l, sthr, never, a, oth, fbits + (size_t)col * half,
                                           fhf + (size_t)col * half, j0, Wown[0], col, c1, r);
                 if (fl) *(uint32_t *)(own + j0) = Wown[0] ^ fl;
             }
@@ -807,17 +845,167 @@ __global__ __launch_bounds__(1024) void sweep_generic_resident(Lattice lat, Fast
             uint32_t S1[1], W[1], U[1], F1[1];
             load_words<1>(s1, j0, S1);
             if (KIND == 0) load_words<1>(fbits + half, j0, F1);
-            if (ROWS) {
-                neighbour_counts<1>(s0, j0, row_chunk<1>(j0, 1u, (uint32_t)lat.L, by_row, by_l), W, U);
-            } else {
-                load_words<1>(s0, j0, W);
-                U[0] = site_counts(s0, j0, W[0], 1u, (uint32_t)lat.L, by_row, by_l);
-            }
+            load_words<1>(s0, j0, W);
+            U[0] = site_counts(s0, j0, W[0], 1u, (uint32_t)lat.L, by_row, by_l);
             chunk_energy<KIND, 1>(lat, S1, W, U, F1, fbits, fraw + half, fraw, j0, ksum, upsum, eqsum, fsum);
         }
         block_partial<KIND>(gptr(lat.part) + (size_t)r * 3, 4 * n, ksum, upsum, eqsum, fsum);
     }
     for (uint32_t q = threadIdx.x; q < words; q += blockDim.x) home[q] = lds1[q];
+}
+
+// The place of a block in its colour-plane (byte d of it, its four sites in
+// one row with ROWS, else in up to two) and the bytes of its neighbours there:
+// computed once per thread, which keeps the place for a whole launch.
+template <bool ROWS> struct Place {
+    static constexpr int S = ROWS ? 1 : 4;      // sites with offsets of their own
+    uint32_t d, y[S], xl[S], xr[S], yp[S], ym[S];
+};
+
+template <bool ROWS>
+__device__ __forceinline__ Place<ROWS> place_of(uint32_t d, uint32_t L, const FastDiv &by_row) {
+    const uint32_t Lh = L >> 1, plane = L * Lh, n = ROWS ? 4u : 1u;
+    Place<ROWS> p;
+    p.d = d;
+    uint32_t y = div_by(d, by_row), m = d - y * Lh;
+#pragma unroll
+    for (int q = 0; q < Place<ROWS>::S; ++q) {
+        const uint32_t j = d + (uint32_t)q;
+        p.y[q] = y;
+        p.xl[q] = m == 0u ? j + Lh - n : j - n;
+        p.xr[q] = m + n == Lh ? j + n - Lh : j + n;
+        p.yp[q] = y + 1u == L ? j + Lh - plane : j + Lh;
+        p.ym[q] = y == 0u ? j + plane - Lh : j - Lh;
+        if (!ROWS && ++m == Lh) {
+            m = 0;
+            ++y;                        // a plane holds whole blocks: y stays below L
+        }
+    }
+    return p;
+}
+
+// Up counts of a block from the other colour's plane in LDS and its two
+// neighbour planes; par = (colour + z) mod 2, W the block's other-colour sites.
+template <bool ROWS>
+__device__ __forceinline__ uint32_t plane_counts(const uint8_t *oth, const uint8_t *zp, const uint8_t *zm,
+                                                 const Place<ROWS> &p, uint32_t par, uint32_t &W) {
+    W = *(const uint32_t *)(oth + p.d);
+    const uint32_t Wz = *(const uint32_t *)(zp + p.d) + *(const uint32_t *)(zm + p.d);
+    if (ROWS) {
+        const uint32_t right = (par + p.y[0]) & 1u;
+        const uint32_t Wx = *(const uint32_t *)(oth + (right ? p.xr[0] : p.xl[0]));
+        // as in neighbour_sums: the row shifted by one site
+        const uint32_t Xs = __builtin_amdgcn_perm(Wx, W, right ? 0x04030201u : 0x02010007u);
+        return W + Xs + Wz + *(const uint32_t *)(oth + p.yp[0]) + *(const uint32_t *)(oth + p.ym[0]);
+    } else {
+        uint32_t U = W + Wz;
+#pragma unroll
+        for (int q = 0; q < Place<ROWS>::S; ++q)
+            U += ((uint32_t)oth[((par + p.y[q]) & 1u) ? p.xr[q] : p.xl[q]] + oth[p.yp[q]] + oth[p.ym[q]]) << (8 * q);
+        return U;
+    }
+}
+
+// Boxes (L a multiple of 4, so that a colour-plane holds whole blocks): a
+// replica is cut along z into slabs of `np` planes (the last may be thinner),
+// one workgroup each, and a launch runs `nsweep` whole sweeps in LDS on the
+// slab and 2 nsweep halo planes on each side, which it recomputes instead of
+// waiting for its neighbours, as sweep_slabs does; half-sweep s updates the
+// planes [s + 1, P - 1 - s) of the box.  Reads `src`, writes `dst`.  A plane
+// may appear twice in a box thicker than L - 1: both copies take the same
+// updates from the same inputs as far as their halo reaches.  WHOLE: the box
+// is the whole replica, periodic in z, without halo planes (any nsweep).
+//
+// A thread keeps one place of the plane and takes every G-th of the active
+// planes (blockDim = G blocks-per-plane).  Bound by instruction issue (104
+// VALU instructions per block of four sites with whole-dword rows; 160 with
+// the place worked out for every block) and, for thin slabs, by the launch
+// and the staging: box_plan weighs them.  us a sweep, boxes against
+// half-sweep launches (resident form at L = 24): L = 24, R = 32 3.3 and 3.9;
+// L = 40, R = 32 6.0 and 8.4, R = 256 13.2 and 23.8; L = 48, R = 32 8.6 and
+// 9.2; L = 52, R = 64 15.6 and 35.
+template <int KIND, bool ROWS, bool WHOLE>
+__global__ __launch_bounds__(1024) void sweep_box(Lattice lat, FastDiv by_row, FastDiv by_plane, FastDiv by_slab,
+                                                   const uint8_t *__restrict__ src, uint8_t *__restrict__ dst, int np_,
+                                                   int nsweep, int toff, int energy) {
+    extern __shared__ uint4 lds_raw[];
+    __shared__ __align__(16) uint32_t sthr[32];
+    uint8_t *box = (uint8_t *)lds_raw;                       // [P][2][plane]
+    const uint32_t L = (uint32_t)lat.L, half = (uint32_t)lat.half;
+    const uint32_t plane = L * (L >> 1), bpp = plane >> 2;   // bytes and blocks per colour-plane
+    const uint32_t r = div_by(blockIdx.x, by_slab), sl = blockIdx.x - r * by_slab.d;
+    const uint32_t z0 = sl * (uint32_t)np_;
+    const uint32_t np = min((uint32_t)np_, L - z0);
+    const uint32_t H = WHOLE ? 0u : 2u * (uint32_t)nsweep, P = np + 2u * H;
+    GAS const uint8_t *rsrc = gptr(src) + (size_t)r * lat.N;
+    const int slot = gptr(lat.r2t)[r];
+    const uint32_t t0 = (uint32_t)(gptr(lat.ctrs)[0] + (uint64_t)toff);
+    GAS const uint8_t *fbits = gptr(lat.fbits);
+    GAS const float *fhf = gptr(lat.fhf), *fraw = gptr(lat.fraw);
+    // plane b of the box is plane z0 - H + b of the lattice (H <= L)
+    auto z_of = [&](uint32_t b) {
+        if (WHOLE) return b;
+        uint32_t z = z0 + L - H + b;
+        z -= z >= L ? L : 0u;
+        return z - (z >= L ? L : 0u);
+    };
+    const uint32_t pg = div_by(threadIdx.x, by_plane), G = blockDim.x / bpp;   // this thread's first plane, planes per step
+    const Place<ROWS> place = place_of<ROWS>(4u * (threadIdx.x - pg * bpp), L, by_row);
+    // stage the box: the thread's block of its planes, both colours
+    for (uint32_t b = pg; b < P; b += G) {
+        const uint32_t at = z_of(b) * plane + place.d;
+#pragma unroll
+        for (uint32_t c = 0; c < 2; ++c)
+            *(uint32_t *)(box + (2u * b + c) * plane + place.d) = *(GAS const uint32_t *)(rsrc + c * half + at);
+    }
+    if (KIND == 0 && threadIdx.x < 32u) sthr[threadIdx.x] = gptr(lat.thr)[slot * 32 + threadIdx.x];
+    const float a = KIND == 1 ? -2.0f * 1.44269504088896341f * gptr(lat.betaf)[slot] : 0.0f;
+    __syncthreads();
+    const uint32_t never = KIND == 0 ? __builtin_amdgcn_readfirstlane(sthr[31]) : 0u;
+    for (uint32_t st = 0; st < 2u * (uint32_t)nsweep; ++st) {
+        const uint32_t c = st & 1u, c1 = 2u * (t0 + (st >> 1)) + c;
+        const uint32_t b0 = WHOLE ? 0u : st + 1u, b1 = WHOLE ? P : P - 1u - st;
+        // (two or three planes of a thread at a time, their Philox chains
+        // interleaved, were slower: the loop is bound by instruction issue)
+        for (uint32_t b = b0 + pg; b < b1; b += G) {
+            const uint32_t z = z_of(b), j0 = z * plane + place.d;
+            const BlockField<KIND> f = block_field<KIND>(fbits + (size_t)c * half, fhf + (size_t)c * half, j0);
+            uint8_t *own = box + (2u * b + c) * plane + place.d;
+            const uint8_t *oth = box + (2u * b + 1u - c) * plane;
+            const uint8_t *zp = WHOLE && b + 1u == P ? oth - 2u * (P - 1u) * plane : oth + 2u * plane;
+            const uint8_t *zm = WHOLE && b == 0u ? oth + 2u * (P - 1u) * plane : oth - 2u * plane;
+            const uint32_t Wown = *(const uint32_t *)own;
+            uint32_t W;
+            const uint32_t U = plane_counts<ROWS>(oth, zp, zm, place, c + z, W);
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t fl = block_flips<KIND>(lat, sthr, never, a, f, U, Wown, j0 >> 2, c1, r);
+            *(uint32_t *)own = Wown ^ fl;
+        }
+        __syncthreads();
+    }
+    if (energy) {
+        int ksum = 0, upsum = 0, eqsum = 0, cnt = 0;
+        double fsum = 0.0;
+        for (uint32_t k = pg; k < np; k += G, ++cnt) {
+            const uint32_t b = H + k, j0 = (z0 + k) * plane + place.d;
+            const uint8_t *oth = box + 2u * b * plane;
+            const uint8_t *zp = WHOLE && b + 1u == P ? box : oth + 2u * plane;
+            const uint8_t *zm = WHOLE && b == 0u ? oth + 2u * (P - 1u) * plane : oth - 2u * plane;
+            uint32_t S1[1], W[1], U[1], F1[1] = {0u};
+            S1[0] = *(const uint32_t *)(oth + plane + place.d);
+            U[0] = plane_counts<ROWS>(oth, zp, zm, place, 1u + z0 + k, W[0]);
+            if (KIND == 0) load_words<1>(fbits + half, j0, F1);
+            chunk_energy<KIND, 1>(lat, S1, W, U, F1, fbits, fraw + half, fraw, j0, ksum, upsum, eqsum, fsum);
+        }
+        block_partial<KIND>(gptr(lat.part) + ((size_t)sl * lat.pstride + r) * 3, 4 * cnt, ksum, upsum, eqsum, fsum);
+    }
+    GAS uint8_t *rdst = gptr(dst) + (size_t)r * lat.N;
+    for (uint32_t k = pg; k < np; k += G) {
+#pragma unroll
+        for (uint32_t c = 0; c < 2; ++c)
+            *(GAS uint32_t *)(rdst + c * half + (z0 + k) * plane + place.d) =
+                *(const uint32_t *)(box + (2u * (H + k) + c) * plane + place.d);
+    }
 }
 
 // Resident sweeps (L = 2^l <= 32): one workgroup holds one replica's spins
@@ -1975,30 +2163,30 @@ hipError_t launch_resident(const Launch &ln, int nsweep, int energy, hipStream_t
     return hipGetLastError();
 }
 
-bool generic_resident(int L) { return L <= kGenericResidentMaxL && !(L >= 8 && (L & (L - 1)) == 0); }
+bool generic_resident(int L) { return L <= kGenericResidentMaxL && (L % 4 == 2 || L == 4); }
 
-template <int KIND, bool ROWS>
-static void launch_generic_form(const Lattice &lat, int colour, int toff, int nsweep, int energy, hipStream_t s) {
+template <int KIND>
+static void launch_generic_kind(const Lattice &lat, int colour, int toff, int nsweep, int energy, hipStream_t s) {
     const FastDiv by_row = fast_div((uint32_t)lat.L / 2u), by_l = fast_div((uint32_t)lat.L);
     const int G = lat.half >> 2;
-    if (nsweep > 0) {
-        const unsigned wg = (unsigned)std::min(1024, (G + 63) / 64 * 64);
-        hipLaunchKernelGGL((sweep_generic_resident<KIND, ROWS>), dim3((unsigned)lat.R), dim3(wg), (size_t)lat.N, s, lat,
-                           by_row, by_l, nsweep, energy);
-    } else {
-        hipLaunchKernelGGL((sweep_generic<KIND, ROWS>), dim3((unsigned)((G + 255) / 256), (unsigned)lat.R), dim3(256), 0,
-                           s, lat, by_row, by_l, colour, toff);
-    }
+    const unsigned nb = (unsigned)((G + 255) / 256);
+    if (nsweep > 0)
+        hipLaunchKernelGGL((sweep_generic_resident<KIND>), dim3((unsigned)lat.R),
+                           dim3((unsigned)std::min(1024, (G + 63) / 64 * 64)), (size_t)lat.N, s, lat, by_row, by_l, nsweep,
+                           energy);
+    else if (lat.L % 8 == 0)
+        hipLaunchKernelGGL((sweep_generic<KIND, true>), dim3(nb * (unsigned)lat.R), dim3(256), 0, s, lat, by_row, by_l,
+                           fast_div(nb), colour, toff);
+    else
+        hipLaunchKernelGGL((sweep_generic<KIND, false>), dim3(nb * (unsigned)lat.R), dim3(256), 0, s, lat, by_row, by_l,
+                           fast_div(nb), colour, toff);
 }
 
 static hipError_t launch_generic(const Lattice &lat, int colour, int toff, int nsweep, int energy, hipStream_t s) {
-    const bool rows = lat.L % 8 == 0;
     if (lat.kind == 0)
-        rows ? launch_generic_form<0, true>(lat, colour, toff, nsweep, energy, s)
-             : launch_generic_form<0, false>(lat, colour, toff, nsweep, energy, s);
+        launch_generic_kind<0>(lat, colour, toff, nsweep, energy, s);
     else
-        rows ? launch_generic_form<1, true>(lat, colour, toff, nsweep, energy, s)
-             : launch_generic_form<1, false>(lat, colour, toff, nsweep, energy, s);
+        launch_generic_kind<1>(lat, colour, toff, nsweep, energy, s);
     return hipGetLastError();
 }
 
@@ -2009,6 +2197,86 @@ hipError_t launch_generic_sweep(const Lattice &lat, int colour, int toff, hipStr
 hipError_t launch_generic_resident(const Lattice &lat, int nsweep, int energy, hipStream_t s) {
     if (nsweep < 1) return hipSuccess;
     return launch_generic(lat, 0, 0, nsweep, energy, s);
+}
+
+size_t box_lds_bytes(int L, int planes) { return (size_t)planes * (size_t)L * (size_t)L; }   // both colours
+
+// Microseconds of a sweep, from measurements on gfx950 at L = 20 .. 96 and
+// R = 8 .. 300 (within about 15 % of them): a launch of boxes costs 5 us, the
+// planes staged and written back at 16 KB/us a CU, and 0.18 us for every
+// block of a wave and SIMD (0.25 where neighbours are gathered as bytes); a
+// half-sweep launch 3.3 us and 0.49 (1.4) us per 2^20 sites of all replicas.
+static double box_cost(int L, long long R, int np, int K) {
+    const long long bpp = (long long)L * L / 8, slabs = (L + np - 1) / np;
+    const bool whole = slabs == 1;
+    const long long P = whole ? L : np + 4 * K, G = std::min(1024 / bpp, whole ? P : P - 2);
+    const double wgs = std::ceil((double)(R * slabs) / 256.0);         // a CU's workgroups
+    const double waves = std::ceil(wgs * (double)((G * bpp + 63) / 64) / 4.0);
+    double steps = 0.0;
+    for (int st = 0; st < 2 * K; ++st) {
+        const long long active = whole ? L : P - 2 - 2 * st;
+        steps += (double)((active + G - 1) / G);
+    }
+    return (5.0 + (double)(P + np) * (double)(L * L) * wgs / 16000.0 + (L % 8 ? 0.25 : 0.18) * waves * steps) / K;
+}
+
+static double half_sweeps_cost(int L, long long R) {
+    return 2.0 * (3.3 + (L % 8 ? 1.4 : 0.49) * (double)R * L * L * L / 1048576.0);
+}
+
+BoxPlan box_plan(int L, int R) {
+    BoxPlan best = {0, 0};
+    if (L % 4 != 0 || L < 12 || L > kBoxMaxL || (L & (L - 1)) == 0) return best;
+    double cost = half_sweeps_cost(L, R);
+    for (int np = 1; np <= L; ++np) {
+        const bool whole = np == L;
+        if ((L + np - 1) / np > kMaxBoxSlabs) continue;
+        // a whole replica runs any number of sweeps in a launch: as many as
+        // an exchange interval has; ten stand for it here
+        for (int K = whole ? 10 : 1; K <= (whole ? 10 : 8); ++K) {
+            if (!whole && 4 * K >= L) break;
+            if (box_lds_bytes(L, whole ? L : np + 4 * K) > 65536) break;
+            const double c = box_cost(L, R, np, K);
+            if (c < cost) {
+                best = {np, K};
+                cost = c;
+            }
+        }
+    }
+    return best;
+}
+
+template <int KIND, bool ROWS>
+static void launch_box_form(const Lattice &lat, const uint8_t *src, uint8_t *dst, int np, int nsweep, int toff, int energy,
+                            hipStream_t s) {
+    const uint32_t L = (uint32_t)lat.L, slabs = (L + (uint32_t)np - 1u) / (uint32_t)np, bpp = L * L / 8u;
+    const bool whole = slabs == 1u;
+    const uint32_t active = whole ? L : (uint32_t)(np + 4 * nsweep - 2);     // planes of the largest half-sweep
+    const dim3 grid((unsigned)lat.R * slabs), block(bpp * std::min(1024u / bpp, active));
+    const FastDiv by_row = fast_div(L / 2u), by_plane = fast_div(bpp), by_slab = fast_div(slabs);
+    if (whole)
+        hipLaunchKernelGGL((sweep_box<KIND, ROWS, true>), grid, block, box_lds_bytes(lat.L, lat.L), s, lat, by_row, by_plane,
+                           by_slab, src, dst, np, nsweep, toff, energy);
+    else
+        hipLaunchKernelGGL((sweep_box<KIND, ROWS, false>), grid, block, box_lds_bytes(lat.L, np + 4 * nsweep), s, lat,
+                           by_row, by_plane, by_slab, src, dst, np, nsweep, toff, energy);
+}
+
+hipError_t launch_box(const Lattice &lat, const uint8_t *src, uint8_t *dst, const BoxPlan &plan, int nsweep, int toff,
+                      int energy, hipStream_t s) {
+    const int np = plan.planes;
+    const bool whole = np >= lat.L;
+    if (np < 1 || nsweep < 1 || lat.L % 4 != 0 || lat.L > kBoxMaxL) return hipErrorInvalidValue;
+    if (!whole && (4 * nsweep >= lat.L || src == dst)) return hipErrorInvalidValue;
+    if (box_lds_bytes(lat.L, whole ? lat.L : np + 4 * nsweep) > 65536) return hipErrorInvalidValue;
+    const bool rows = lat.L % 8 == 0;
+    if (lat.kind == 0)
+        rows ? launch_box_form<0, true>(lat, src, dst, np, nsweep, toff, energy, s)
+             : launch_box_form<0, false>(lat, src, dst, np, nsweep, toff, energy, s);
+    else
+        rows ? launch_box_form<1, true>(lat, src, dst, np, nsweep, toff, energy, s)
+             : launch_box_form<1, false>(lat, src, dst, np, nsweep, toff, energy, s);
+    return hipGetLastError();
 }
 
 int slab_sweeps_per_launch(int mode) { return mode >= 2 ? mode - 1 : 0; }

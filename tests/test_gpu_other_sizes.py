@@ -1,6 +1,6 @@
 """Lattice sizes that are not powers of two (and L = 2, 4): the LDS-resident
-form, the streaming half-sweeps, rows of whole dwords and rows that end inside
-one.  +-1 fields follow the oracle bit for bit; of one sweep's decisions with
+form, boxes (slabs and whole replicas), the streaming half-sweeps, rows of
+whole dwords and rows that end inside one.  +-1 fields follow the oracle bit for bit; of one sweep's decisions with
 continuous fields at most one differs (they are FP32 on the device: about 1 in
 3e7)."""
 import numpy as np
@@ -12,13 +12,13 @@ from parity_util import assert_same_state, make_pair
 pytestmark = pytest.mark.gpu
 
 SIZES = [(2, 3), (4, 4), (6, 5), (10, 3), (12, 2), (14, 4), (18, 3), (20, 2), (22, 2), (24, 3), (26, 2), (28, 3), (36, 2),
-         (40, 3), (48, 2), (52, 2)]
+         (40, 3), (48, 2), (52, 2), (12, 40), (24, 30), (18, 33), (36, 25), (40, 25), (60, 1), (72, 1)]
 
 
 @pytest.mark.parametrize("L,R", SIZES)
 def test_chain_matches_oracle(rfim_mod, oracle_mod, L, R):
     f = W.bimodal_fields(L, [95, L])
-    T = W.linear_temps(R, 2.0, 2.0 + 0.002 * (R - 1) * (64 / L) ** 1.5)
+    T = W.linear_temps(R, 2.0, 2.0 + 0.002 * (R - 1) * (64 / L) ** 1.5) if R > 1 else np.array([2.0])
     g, o = make_pair(rfim_mod, oracle_mod, L, R, 1.0, 1.5, f, T, seed=L, R_cap=R + 2)
     for n, every in ((11, 4), (5, 7), (3, 0), (2, 1)):
         g.sweep(n, every)
