@@ -239,6 +239,10 @@ struct rfim {
         a.bits = bits_mode ? d_bits : nullptr;
         a.fbw = d_fbw;
         a.fhw = d_fhw;
+        const bool m = (measure & RFIM_MEASURE_FOURIER) != 0;
+        a.fpart = m ? d_fpart : nullptr;
+        a.trig = m ? d_trig : nullptr;
+        a.fobs = m ? d_fobs : nullptr;
         return a;
     }
 };
@@ -556,7 +560,7 @@ int reset_obs(rfim *h) {
 // After an exchange step: the Fourier sample of every replica, by slot.
 int measure_after_exchange(rfim *h, hipStream_t s) {
     if (!(h->measure & RFIM_MEASURE_FOURIER)) return RFIM_OK;
-    HIPCHK(rfim_dev::launch_fourier(h->lattice(), h->d_fpart, h->d_trig, h->d_fobs, s));
+    HIPCHK(rfim_dev::launch_fourier(h->lattice(), s));
     return RFIM_OK;
 }
 
@@ -1535,7 +1539,12 @@ struct rfim_batch {
     uint64_t t = 0, k = 0;
     hipGraphExec_t graph = nullptr;
     int graph_every = 0;
-    std::vector<int> graph_measure;     // items' measurement flags the graph was captured with
+    // the measured items' flags that the descriptors and the two maps of the
+    // Fourier launches were made for (batch_sync_measure)
+    std::vector<int> measured;
+    uint2 *d_fmap = nullptr;
+    size_t fmap_cap = 0;
+    int fchunks = 0, freplicas = 0, fmax_l = 0;
     // side streams for classes (and halves of large streaming classes) that
     // run concurrently within an exchange interval; events fork them from
     // and join them back into `stream`
@@ -1605,6 +1614,7 @@ void batch_free(rfim_batch *b) {
     if (b->graph) (void)hipGraphExecDestroy(b->graph);
     for (auto &c : b->classes)
         if (c.d_map) (void)hipFree(c.d_map);
+    if (b->d_fmap) (void)hipFree(b->d_fmap);
     if (b->d_lats) (void)hipFree(b->d_lats);
     for (rfim *h : b->items) {
         h->stream = nullptr;      // the batch owns the stream
@@ -1654,11 +1664,72 @@ int batch_build(rfim_batch *b) {
             HIPCHK(hipMemcpyAsync(c.d_map, map.data(), map.size() * sizeof(uint2), hipMemcpyHostToDevice, b->stream));
     }
     HIPCHK(hipStreamSynchronize(b->stream));
+    b->measured.clear();            // the items changed: the Fourier maps are made again
+    b->fchunks = b->freplicas = 0;
     if (b->graph) {
         HIPCHK(hipGraphExecDestroy(b->graph));
         b->graph = nullptr;
         b->graph_every = 0;
     }
+    return RFIM_OK;
+}
+
+// Descriptors and maps of the Fourier launches for the items' measurement
+// flags, when those changed since the last call (a captured interval is then
+// dropped).  Two launches measure every item of the batch.
+int batch_sync_measure(rfim_batch *b) {
+    const int n = (int)b->items.size();
+    std::vector<int> flags(n);
+    for (int i = 0; i < n; ++i) flags[i] = b->items[i]->measure;
+    if (flags == b->measured) return RFIM_OK;
+    if (b->measured.empty() && std::all_of(flags.begin(), flags.end(), [](int f) { return f == 0; })) {
+        b->measured = flags;        // nothing measured since the descriptors were made
+        return RFIM_OK;
+    }
+    std::vector<uint2> chunks, replicas;
+    int max_l = 0;
+    for (int i = 0; i < n; ++i) {
+        const rfim *h = b->items[i];
+        if (!(h->measure & RFIM_MEASURE_FOURIER)) continue;
+        max_l = std::max(max_l, h->L);
+        const int planes = rfim_dev::fourier_chunk_planes(h->L), nchunk = (h->L + planes - 1) / planes;
+        for (int r = 0; r < h->R; ++r) {
+            const uint32_t x = ((uint32_t)i << 16) | (uint32_t)r;
+            for (int c = 0; c < nchunk; ++c) chunks.push_back(make_uint2(x, ((uint32_t)planes << 16) | (uint32_t)c));
+            if (nchunk > 1) replicas.push_back(make_uint2(x, (uint32_t)nchunk));
+        }
+    }
+    HIPCHK(hipStreamSynchronize(b->stream));
+    if (b->graph) {
+        HIPCHK(hipGraphExecDestroy(b->graph));
+        b->graph = nullptr;
+        b->graph_every = 0;
+    }
+    const size_t need = chunks.size() + replicas.size();
+    if (need > b->fmap_cap) {
+        if (b->d_fmap) HIPCHK(hipFree(b->d_fmap));
+        b->d_fmap = nullptr;
+        b->fmap_cap = 0;
+        b->fchunks = b->freplicas = 0;
+        b->measured.clear();
+        hipError_t e = hipMalloc((void **)&b->d_fmap, need * sizeof(uint2));
+        if (e != hipSuccess) return fail(RFIM_ENOMEM, "hipMalloc(Fourier maps): %s", hipGetErrorString(e));
+        b->fmap_cap = need;
+    }
+    b->lats_host.resize(n);
+    for (int i = 0; i < n; ++i) b->lats_host[i] = b->items[i]->lattice();
+    HIPCHK(hipMemcpyAsync(b->d_lats, b->lats_host.data(), n * sizeof(Lattice), hipMemcpyHostToDevice, b->stream));
+    if (need) {
+        const size_t nc = chunks.size();
+        chunks.insert(chunks.end(), replicas.begin(), replicas.end());
+        HIPCHK(hipMemcpyAsync(b->d_fmap, chunks.data(), need * sizeof(uint2), hipMemcpyHostToDevice, b->stream));
+        chunks.resize(nc);
+    }
+    HIPCHK(hipStreamSynchronize(b->stream));
+    b->fchunks = (int)chunks.size();
+    b->freplicas = (int)replicas.size();
+    b->fmax_l = max_l;
+    b->measured = flags;
     return RFIM_OK;
 }
 
@@ -1855,10 +1926,8 @@ int batch_segment(rfim_batch *b, int m, bool exch) {
             if (!class_fused(b, c))
                 for (int i : c.members) HIPCHK(rfim_dev::launch_energy(b->items[i]->lattice(), b->stream));
         HIPCHK(rfim_dev::launch_exchange(b->d_lats, (int)b->items.size(), m, b->stream));
-        for (rfim *h : b->items) {
-            int rc;
-            if ((rc = measure_after_exchange(h, b->stream))) return rc;
-        }
+        HIPCHK(rfim_dev::launch_fourier_batch(b->d_lats, b->d_fmap, b->fchunks, b->d_fmap + b->fchunks, b->freplicas,
+                                              b->fmax_l, b->stream));
     } else {
         for (rfim *h : b->items) HIPCHK(rfim_dev::launch_advance(h->lattice(), m, b->stream));
     }
@@ -2073,18 +2142,15 @@ int rfim_batch_sweep(rfim_batch_t *b, int64_t n, int exchange_every) {
     if (b->t + (uint64_t)n > kMaxSweeps) return fail(RFIM_ECAP, "global sweep counter would pass 2^31-1");
     int64_t remaining = n;
     const int every = exchange_every;
+    const int rc0 = batch_sync_measure(b);
+    if (rc0) return rc0;
     while (remaining > 0) {
         const int64_t to_next = every > 0 ? (int64_t)(every - (int64_t)(b->t % (uint64_t)every)) : remaining;
         const int m = (int)std::min<int64_t>(remaining, to_next);
         const bool exch = every > 0 && m == to_next;
         int rc;
         if (exch && m == every && batch_prefers_graph(b, every)) {
-            std::vector<int> flags(b->items.size());
-            for (size_t q = 0; q < b->items.size(); ++q) flags[q] = b->items[q]->measure;
-            if (b->graph_every != every || b->graph_measure != flags) {
-                if ((rc = batch_capture(b, every))) return rc;
-                b->graph_measure = flags;
-            }
+            if (b->graph_every != every && (rc = batch_capture(b, every))) return rc;
             HIPCHK(hipGraphLaunch(b->graph, b->stream));
         } else if ((rc = batch_segment(b, m, exch))) {
             return rc;
@@ -2261,6 +2327,7 @@ void rfim_pool_destroy(rfim_pool_t *p) {
         b->own_stream = p->core.own_stream;
         b->d_lats = p->core.d_lats;
         b->classes = p->core.classes;
+        b->d_fmap = p->core.d_fmap;
         b->aux = p->core.aux;
         b->ev_join = p->core.ev_join;
         b->ev_fork = p->core.ev_fork;
@@ -2415,6 +2482,7 @@ int rfim_pool_step(rfim_pool_t *p, int quantum, int exchange_every) {
     int rc;
     if (p->dirty && (rc = pool_build(p))) return rc;
     if (p->core.items.empty()) return RFIM_OK;
+    if ((rc = batch_sync_measure(&p->core))) return rc;
     for (int q = 0; q < quantum / exchange_every; ++q) {
         if ((rc = batch_segment(&p->core, exchange_every, true))) return rc;
         for (rfim *h : p->core.items) {

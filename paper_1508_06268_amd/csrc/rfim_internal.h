@@ -73,6 +73,12 @@ struct Lattice {
     uint32_t *bits;
     const uint32_t *fbw;
     const float *fhw;
+    // Fourier measurement (null while it is off): fpart int32
+    // [R_cap][L][2L] scratch, trig double [2][L] = cos, sin of 2 pi v / L,
+    // fobs double [R_cap][2] = (count, sum F) by slot.
+    int32_t *fpart;
+    const double *trig;
+    double *fobs;
 };
 
 // Above this many workgroups per replica the streaming sweep does not write
@@ -191,10 +197,16 @@ hipError_t launch_reduce(const Lattice &lat, int64_t *B, double *F, int64_t *M, 
 // One exchange step for each of the n realizations in lats (device array).
 hipError_t launch_exchange(const Lattice *lats, int n, int tadv, hipStream_t s);
 hipError_t launch_advance(const Lattice &lat, int tadv, hipStream_t s);
-// Fourier observable of every replica, accumulated by slot (rfim_measure.hip):
-// part int32 [R_cap][L][2L] scratch, trig double [2][L] = cos, sin of
-// 2 pi v / L, fobs double [R_cap][2] = (count, sum F).
-hipError_t launch_fourier(const Lattice &lat, int32_t *part, const double *trig, double *fobs, hipStream_t s);
+// Fourier observable of every replica, accumulated by slot (rfim_measure.hip),
+// through the descriptor's fpart, trig and fobs.
+hipError_t launch_fourier(const Lattice &lat, hipStream_t s);
+// The same for the measured items of a batch: map entries x = (realization <<
+// 16) | replica with, in `chunks`, y = (planes per chunk << 16) | chunk
+// (fourier_chunk_planes(L) planes each) and, in `replicas` (those of more than
+// one chunk), y = the number of chunks.  L a power of two in [8, max_l].
+int fourier_chunk_planes(int L);
+hipError_t launch_fourier_batch(const Lattice *lats, const uint2 *chunks, int nchunks, const uint2 *replicas, int nreplicas,
+                                int max_l, hipStream_t s);
 
 }  // namespace rfim_dev
 
