@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <new>
 #include <queue>
@@ -124,6 +125,86 @@ void release_side_stream(hipStream_t side) {
         }
 }
 
+// Pinned host memory that kernels write results to and read inputs from, so
+// that a readout is one launch and one wait instead of a staged copy and a
+// wait for every array (15 to 20 us each).  Blocks are kept for the next call:
+// at most kPinnedKept of them, of at most kPinnedBlock bytes, and no more
+// than kPinnedIdle bytes once no handle is left.  A block belongs to one call
+// at a time, which has waited for its work when it gives the block back.
+constexpr size_t kPinnedBlock = 4u << 20, kPinnedIdle = 1u << 20;
+constexpr size_t kPinnedKept = 8;
+
+struct PinnedBlock {
+    void *p;
+    size_t bytes;
+};
+std::mutex g_pinned_mu;
+std::vector<PinnedBlock> g_pinned;
+size_t g_handles = 0;
+
+void note_handle(int step) {
+    std::lock_guard<std::mutex> lock(g_pinned_mu);
+    g_handles += (size_t)step;
+    if (g_handles != 0) return;
+    size_t kept = 0;
+    std::vector<PinnedBlock> keep;
+    for (const PinnedBlock &b : g_pinned) {
+        if (kept + b.bytes <= kPinnedIdle) {
+            kept += b.bytes;
+            keep.push_back(b);
+        } else {
+            (void)hipHostFree(b.p);
+        }
+    }
+    g_pinned.swap(keep);
+}
+
+class Pinned {
+  public:
+    Pinned() = default;
+    Pinned(const Pinned &) = delete;
+    Pinned &operator=(const Pinned &) = delete;
+    ~Pinned() {
+        if (!b_.p) return;
+        if (b_.bytes <= kPinnedBlock) {
+            std::lock_guard<std::mutex> lock(g_pinned_mu);
+            if (g_pinned.size() < kPinnedKept) {
+                g_pinned.push_back(b_);
+                return;
+            }
+        }
+        (void)hipHostFree(b_.p);
+    }
+    int get(size_t bytes) {
+        {
+            std::lock_guard<std::mutex> lock(g_pinned_mu);
+            size_t best = g_pinned.size();
+            for (size_t q = 0; q < g_pinned.size(); ++q)
+                if (g_pinned[q].bytes >= bytes && (best == g_pinned.size() || g_pinned[q].bytes < g_pinned[best].bytes))
+                    best = q;
+            if (best < g_pinned.size()) {
+                b_ = g_pinned[best];
+                g_pinned.erase(g_pinned.begin() + (long)best);
+                return RFIM_OK;
+            }
+        }
+        size_t want = 64u << 10;
+        while (want < bytes) want *= 2;
+        const hipError_t e = hipHostMalloc(&b_.p, want, hipHostMallocPortable);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            b_.p = nullptr;
+            return fail(RFIM_ENOMEM, "hipHostMalloc(%zu): %s", want, hipGetErrorString(e));
+        }
+        b_.bytes = want;
+        return RFIM_OK;
+    }
+    char *at(size_t off = 0) const { return (char *)b_.p + off; }
+
+  private:
+    PinnedBlock b_ = {nullptr, 0};
+};
+
 }  // namespace
 
 namespace rfim_host {
@@ -141,6 +222,10 @@ int set_error(int code, const char *fmt, ...) {
 }  // namespace rfim_host
 
 struct rfim {
+    rfim() { note_handle(1); }
+    ~rfim() { note_handle(-1); }
+    rfim(const rfim &) = delete;
+    rfim &operator=(const rfim &) = delete;
     // parameters
     int L = 0, N = 0, half = 0, R = 0, R_cap = 0, log2L = -1, kind = 0;
     double J = 0, h = 0;
@@ -373,17 +458,6 @@ int upload_tables(rfim *h) {
     return RFIM_OK;
 }
 
-// Natural site order <-> colour-split layout (index only, no arithmetic of
-// the method): site i of colour c goes to [c][i >> 1].
-template <class F>
-void for_each_site(int L, F f) {
-    const size_t N = (size_t)L * L * L;
-    for (size_t i = 0; i < N; ++i) {
-        const int x = (int)(i % L), y = (int)((i / L) % L), z = (int)(i / ((size_t)L * L));
-        f(i, (x + y + z) & 1, i >> 1);
-    }
-}
-
 // A handle's device buffers live in one allocation, in this order, each
 // piece on a 256-byte boundary (byte offsets; absent pieces have size 0).
 struct ArenaLayout {
@@ -474,21 +548,18 @@ int alloc_device(rfim *h) {
     return RFIM_OK;
 }
 
+// In natural order through pinned memory; the kernel lays them out (and forms
+// (float)(h h_i - 6 J) in FP64) on the device.
 int upload_fields(rfim *h) {
-    const size_t N = (size_t)h->N, half = N / 2;
-    if (h->kind == 0) {
-        std::vector<uint8_t> fb(N);
-        for_each_site(h->L, [&](size_t i, int c, size_t j) { fb[c * half + j] = h->fields[i] > 0.0f ? 4 : 0; });
-        HIPCHK(hipMemcpyAsync(h->d_fbits, fb.data(), N, hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipStreamSynchronize(h->stream));
-    } else {
-        std::vector<float> hf(N), raw(N);
-        for_each_site(h->L, [&](size_t i, int c, size_t j) {
-            raw[c * half + j] = h->fields[i];
-            hf[c * half + j] = (float)(h->h * (double)h->fields[i] - 6.0 * h->J);
-        });
-        HIPCHK(hipMemcpyAsync(h->d_fhf, hf.data(), N * 4, hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipMemcpyAsync(h->d_fraw, raw.data(), N * 4, hipMemcpyHostToDevice, h->stream));
+    const size_t N = (size_t)h->N, chunk = std::min(N, kPinnedBlock / sizeof(float));
+    Pinned buf;
+    int rc;
+    if ((rc = buf.get(chunk * sizeof(float)))) return rc;
+    const Lattice lat = h->lattice();
+    for (size_t i = 0; i < N; i += chunk) {
+        const size_t n = std::min(chunk, N - i);
+        std::memcpy(buf.at(), h->fields.data() + i, n * sizeof(float));
+        HIPCHK(rfim_dev::launch_fields_in(lat, i, n, (const float *)buf.at(), h->stream));
         HIPCHK(hipStreamSynchronize(h->stream));
     }
     return RFIM_OK;
@@ -564,32 +635,77 @@ int measure_after_exchange(rfim *h, hipStream_t s) {
     return RFIM_OK;
 }
 
+// Up to three device arrays to the host, one launch and one wait.  Arrays of
+// whole dwords.
+struct Fetch {
+    void *dst;
+    const void *src;
+    size_t bytes;
+};
+
+int fetch(rfim *h, std::initializer_list<Fetch> parts) {
+    size_t off[rfim_dev::CopyOut::kMax] = {}, total = 0;
+    int q = 0;
+    for (const Fetch &f : parts) {
+        off[q++] = total;
+        total += (f.bytes + 63) & ~(size_t)63;
+    }
+    Pinned buf;
+    int rc;
+    if ((rc = buf.get(total))) return rc;
+    rfim_dev::CopyOut c;
+    q = 0;
+    for (const Fetch &f : parts) {
+        c.src[q] = f.src;
+        c.dst[q] = buf.at(off[q]);
+        c.words[q] = (uint32_t)(f.bytes / 4);
+        ++q;
+    }
+    HIPCHK(rfim_dev::launch_copy_out(c, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
+    q = 0;
+    for (const Fetch &f : parts) std::memcpy(f.dst, buf.at(off[q++]), f.bytes);
+    return RFIM_OK;
+}
+
 int download_perm(rfim *h, std::vector<int32_t> &t2r) {
     t2r.resize(h->R);
-    HIPCHK(hipMemcpyAsync(t2r.data(), h->d_t2r, h->R * 4, hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
-    return RFIM_OK;
+    return fetch(h, {{t2r.data(), h->d_t2r, (size_t)h->R * 4}});
 }
 
-// Bit storage: bring the byte array up to date before code that reads it,
-// and the bits after code that wrote it.
-int bytes_from_bits(rfim *h) {
-    if (h->bits_mode) HIPCHK(rfim_dev::launch_unpack_bits(h->lattice(), h->stream));
-    return RFIM_OK;
-}
-
-int bits_from_bytes(rfim *h) {
-    if (h->bits_mode) HIPCHK(rfim_dev::launch_pack_bits(h->lattice(), h->stream));
-    return RFIM_OK;
-}
-
-int compute_components(rfim *h) {
+// Energies and magnetisations of the current state: the partials from the
+// spins, their totals straight into the caller's pinned block.
+int launch_components(rfim *h, const rfim_dev::Readout &out) {
     Lattice lat = h->lattice();
     lat.nblk = rfim_dev::energy_blocks(lat);
     HIPCHK(rfim_dev::launch_energy(lat, h->stream));
-    HIPCHK(rfim_dev::launch_reduce(lat, h->d_B, h->d_F, h->d_M, h->stream));
+    HIPCHK(rfim_dev::launch_reduce(lat, out, h->stream));
     return RFIM_OK;
 }
+
+// By temperature slot: energies and magnetisations, each if asked for.
+int read_slots(rfim *h, double *E, int64_t *M) {
+    const size_t bytes = (size_t)h->R * 8;
+    Pinned buf;
+    int rc;
+    if ((rc = buf.get(2 * bytes))) return rc;
+    rfim_dev::Readout out;
+    out.E_slot = E ? (double *)buf.at() : nullptr;
+    out.M_slot = M ? (int64_t *)buf.at(bytes) : nullptr;
+    if ((rc = launch_components(h, out))) return rc;
+    HIPCHK(hipStreamSynchronize(h->stream));
+    if (E) std::memcpy(E, buf.at(), bytes);
+    if (M) std::memcpy(M, buf.at(bytes), bytes);
+    return RFIM_OK;
+}
+
+// A configuration goes through pinned memory in pieces of at most a block,
+// two pieces in flight: the device writes (reads) one while the host copies
+// the other.  Pieces are multiples of 64 sites or end with the last replica.
+struct Pieces {
+    size_t total, piece;
+    explicit Pieces(const rfim *h) : total((size_t)h->R * h->N), piece(std::min(total, kPinnedBlock)) {}
+};
 
 // Standalone continuous-field handles at L = 32 with at most this many
 // replicas start on a slab shape (rfim_create_ex).
@@ -996,70 +1112,99 @@ int rfim_temps(const rfim_t *h, double *T) {
 
 int rfim_components(rfim_t *h, int64_t *B, double *F, int64_t *M) {
     if (!h || !B || !F || !M) return fail(RFIM_EINVAL, "NULL argument");
-    int rc = compute_components(h);
-    if (rc) return rc;
-    HIPCHK(hipMemcpyAsync(B, h->d_B, h->R * 8, hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipMemcpyAsync(F, h->d_F, h->R * 8, hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipMemcpyAsync(M, h->d_M, h->R * 8, hipMemcpyDeviceToHost, h->stream));
+    const size_t bytes = (size_t)h->R * 8;
+    Pinned buf;
+    int rc;
+    if ((rc = buf.get(3 * bytes))) return rc;
+    rfim_dev::Readout out;
+    out.B = (int64_t *)buf.at();
+    out.F = (double *)buf.at(bytes);
+    out.M = (int64_t *)buf.at(2 * bytes);
+    if ((rc = launch_components(h, out))) return rc;
     HIPCHK(hipStreamSynchronize(h->stream));
+    std::memcpy(B, out.B, bytes);
+    std::memcpy(F, out.F, bytes);
+    std::memcpy(M, out.M, bytes);
     return RFIM_OK;
 }
 
 int rfim_energies(rfim_t *h, double *E) {
     if (!h || !E) return fail(RFIM_EINVAL, "NULL argument");
-    int rc = compute_components(h);
-    if (rc) return rc;
-    std::vector<double> byrep(h->R);
-    HIPCHK(hipMemcpyAsync(byrep.data(), h->d_E, h->R * 8, hipMemcpyDeviceToHost, h->stream));
-    std::vector<int32_t> t2r;
-    if ((rc = download_perm(h, t2r))) return rc;
-    for (int t = 0; t < h->R; ++t) E[t] = byrep[t2r[t]];
-    return RFIM_OK;
+    return read_slots(h, E, nullptr);
 }
 
 int rfim_magnetizations(rfim_t *h, int64_t *M) {
     if (!h || !M) return fail(RFIM_EINVAL, "NULL argument");
-    int rc = compute_components(h);
-    if (rc) return rc;
-    std::vector<int64_t> byrep(h->R);
-    HIPCHK(hipMemcpyAsync(byrep.data(), h->d_M, h->R * 8, hipMemcpyDeviceToHost, h->stream));
-    std::vector<int32_t> t2r;
-    if ((rc = download_perm(h, t2r))) return rc;
-    for (int t = 0; t < h->R; ++t) M[t] = byrep[t2r[t]];
-    return RFIM_OK;
+    return read_slots(h, nullptr, M);
 }
 
 int rfim_get_spins(rfim_t *h, int8_t *s) {
     if (!h || !s) return fail(RFIM_EINVAL, "NULL argument");
-    const size_t N = (size_t)h->N, half = N / 2;
-    std::vector<uint8_t> dev((size_t)h->R * N);
+    const Pieces p(h);
+    const Lattice lat = h->lattice();
+    const bool two = p.piece < p.total;
+    Pinned buf[2];
     int rc;
-    if ((rc = bytes_from_bits(h))) return rc;
-    HIPCHK(hipMemcpyAsync(dev.data(), h->d_spins, dev.size(), hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
-    for (int r = 0; r < h->R; ++r) {
-        const uint8_t *src = dev.data() + (size_t)r * N;
-        int8_t *dst = s + (size_t)r * N;
-        for_each_site(h->L, [&](size_t i, int c, size_t j) { dst[i] = src[c * half + j] ? 1 : -1; });
+    for (int q = 0; q < (two ? 2 : 1); ++q)
+        if ((rc = buf[q].get(p.piece))) return rc;
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    auto leave = [&](int code) {
+        (void)hipStreamSynchronize(h->stream);      // the blocks go back: nothing may still write them
+        for (hipEvent_t e : ev)
+            if (e) (void)hipEventDestroy(e);
+        return code;
+    };
+    auto start = [&](size_t k) {
+        const size_t at = k * p.piece, n = std::min(p.piece, p.total - at);
+        hipError_t e = rfim_dev::launch_spins_out(lat, at, n, (int8_t *)buf[k & 1].at(), h->stream);
+        if (e == hipSuccess && two) {
+            if (!ev[k & 1]) e = hipEventCreateWithFlags(&ev[k & 1], hipEventDisableTiming);
+            if (e == hipSuccess) e = hipEventRecord(ev[k & 1], h->stream);
+        }
+        return e;
+    };
+    const size_t pieces = (p.total + p.piece - 1) / p.piece;
+    hipError_t e = hipSuccess;
+    for (size_t k = 0; k < std::min<size_t>(pieces, 2) && e == hipSuccess; ++k) e = start(k);
+    for (size_t k = 0; k < pieces && e == hipSuccess; ++k) {
+        e = two ? hipEventSynchronize(ev[k & 1]) : hipStreamSynchronize(h->stream);
+        if (e != hipSuccess) break;
+        std::memcpy(s + k * p.piece, buf[k & 1].at(), std::min(p.piece, p.total - k * p.piece));
+        if (k + 2 < pieces) e = start(k + 2);
     }
-    return RFIM_OK;
+    if (e != hipSuccess) return leave(fail(RFIM_EDEVICE, "reading spins: %s", hipGetErrorString(e)));
+    return leave(RFIM_OK);
 }
 
 int rfim_set_spins(rfim_t *h, const int8_t *s) {
     if (!h || !s) return fail(RFIM_EINVAL, "NULL argument");
-    const size_t N = (size_t)h->N, half = N / 2;
-    for (size_t q = 0; q < (size_t)h->R * N; ++q)
-        if (s[q] != 1 && s[q] != -1) return fail(RFIM_EINVAL, "spins must be +-1 (index %zu)", q);
-    std::vector<uint8_t> dev((size_t)h->R * N);
-    for (int r = 0; r < h->R; ++r) {
-        uint8_t *dst = dev.data() + (size_t)r * N;
-        const int8_t *src = s + (size_t)r * N;
-        for_each_site(h->L, [&](size_t i, int c, size_t j) { dst[c * half + j] = src[i] > 0 ? 1 : 0; });
+    const Pieces p(h);
+    for (size_t at = 0; at < p.total; at += 4096) {         // +-1 and nothing else: s + 1 is 0 or 2
+        const size_t n = std::min<size_t>(4096, p.total - at);
+        uint8_t bad = 0;
+        for (size_t q = 0; q < n; ++q) bad |= (uint8_t)(s[at + q] + 1) & (uint8_t)~2;
+        if (!bad) continue;
+        for (size_t q = at; q < at + n; ++q)
+            if (s[q] != 1 && s[q] != -1) return fail(RFIM_EINVAL, "spins must be +-1 (index %zu)", q);
     }
-    HIPCHK(hipMemcpyAsync(h->d_spins, dev.data(), dev.size(), hipMemcpyHostToDevice, h->stream));
+    const Lattice lat = h->lattice();
+    const bool two = p.piece < p.total;
+    Pinned buf[2];
     int rc;
-    if ((rc = bits_from_bytes(h))) return rc;
-    HIPCHK(hipStreamSynchronize(h->stream));
+    for (int q = 0; q < (two ? 2 : 1); ++q)
+        if ((rc = buf[q].get(p.piece))) return rc;
+    const size_t pieces = (p.total + p.piece - 1) / p.piece;
+    hipError_t e = hipSuccess;
+    for (size_t k = 0; k < pieces && e == hipSuccess; ++k) {
+        const size_t at = k * p.piece, n = std::min(p.piece, p.total - at);
+        if (k >= 2 && (k & 1) == 0) e = hipStreamSynchronize(h->stream);    // both blocks are free again
+        if (e != hipSuccess) break;
+        std::memcpy(buf[k & 1].at(), s + at, n);
+        e = rfim_dev::launch_spins_in(lat, at, n, (const int8_t *)buf[k & 1].at(), h->stream);
+    }
+    const hipError_t e2 = hipStreamSynchronize(h->stream);
+    if (e == hipSuccess) e = e2;
+    if (e != hipSuccess) return fail(RFIM_EDEVICE, "writing spins: %s", hipGetErrorString(e));
     return RFIM_OK;
 }
 
@@ -1086,8 +1231,8 @@ int rfim_set_perm(rfim_t *h, const int32_t *t2r) {
 int rfim_get_counters(rfim_t *h, uint64_t *t, uint64_t *k) {
     if (!h || !t || !k) return fail(RFIM_EINVAL, "NULL argument");
     uint64_t c[2];
-    HIPCHK(hipMemcpyAsync(c, h->d_ctrs, sizeof c, hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
+    const int rc = fetch(h, {{c, h->d_ctrs, sizeof c}});
+    if (rc) return rc;
     if (c[0] != h->t || c[1] != h->k) return fail(RFIM_EDEVICE, "device counters out of step");
     *t = c[0];
     *k = c[1];
@@ -1107,10 +1252,8 @@ int rfim_set_counters(rfim_t *h, uint64_t t, uint64_t k) {
 int rfim_exchange_stats(rfim_t *h, uint64_t *att, uint64_t *acc) {
     if (!h || (h->R > 1 && (!att || !acc))) return fail(RFIM_EINVAL, "NULL argument");
     if (h->R < 2) return RFIM_OK;
-    HIPCHK(hipMemcpyAsync(att, h->d_att, (h->R - 1) * 8, hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipMemcpyAsync(acc, h->d_acc, (h->R - 1) * 8, hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
-    return RFIM_OK;
+    const size_t bytes = (size_t)(h->R - 1) * 8;
+    return fetch(h, {{att, h->d_att, bytes}, {acc, h->d_acc, bytes}});
 }
 
 int rfim_reset_exchange_stats(rfim_t *h) {
@@ -1128,10 +1271,11 @@ static int insert_step(rfim *h, double rate_threshold, int max_insert, int R_cap
     int rc;
     const int R0 = h->R;
     std::vector<uint64_t> att(R0), acc(R0);
-    HIPCHK(hipMemcpyAsync(att.data(), h->d_att, R0 * 8, hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipMemcpyAsync(acc.data(), h->d_acc, R0 * 8, hipMemcpyDeviceToHost, h->stream));
-    std::vector<int32_t> t2r;
-    if ((rc = download_perm(h, t2r))) return rc;
+    std::vector<int32_t> t2r(R0);
+    if ((rc = fetch(h, {{att.data(), h->d_att, (size_t)R0 * 8},
+                        {acc.data(), h->d_acc, (size_t)R0 * 8},
+                        {t2r.data(), h->d_t2r, (size_t)R0 * 4}})))
+        return rc;
     using Item = std::pair<double, int>;
     std::priority_queue<Item, std::vector<Item>, std::greater<Item>> heap;
     for (int p = 0; p + 1 < R0; ++p)
@@ -1206,9 +1350,7 @@ int rfim_adapt_temps(rfim_t *h, int trials, int64_t sweeps_per_trial, int exchan
 
 int rfim_observables(rfim_t *h, double *obs) {
     if (!h || !obs) return fail(RFIM_EINVAL, "NULL argument");
-    HIPCHK(hipMemcpyAsync(obs, h->d_obs, (size_t)h->R * 6 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
-    return RFIM_OK;
+    return fetch(h, {{obs, h->d_obs, (size_t)h->R * 6 * sizeof(double)}});
 }
 
 int rfim_reset_observables(rfim_t *h) {
@@ -1284,10 +1426,7 @@ int rfim_fourier(rfim_t *h, double *fourier) {
         std::memset(fourier, 0, (size_t)h->R * 2 * sizeof(double));
         return RFIM_OK;
     }
-    HIPCHK(hipMemcpyAsync(fourier, h->d_fobs, (size_t)h->R * 2 * sizeof(double), hipMemcpyDeviceToHost,
-                          h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
-    return RFIM_OK;
+    return fetch(h, {{fourier, h->d_fobs, (size_t)h->R * 2 * sizeof(double)}});
 }
 
 int rfim_set_concurrency(rfim_t *h, int streams) {
@@ -1443,10 +1582,8 @@ int rfim_save(rfim_t *h, void *buf, size_t *len) {
     p += (size_t)h->R * h->N;
     if ((rc = rfim_get_perm(h, (int32_t *)p))) return rc;
     p += h->R * 4;
-    HIPCHK(hipMemcpyAsync(p, h->d_att, h->R * 8, hipMemcpyDeviceToHost, h->stream));
-    p += h->R * 8;
-    HIPCHK(hipMemcpyAsync(p, h->d_acc, h->R * 8, hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
+    const size_t stats = (size_t)h->R * 8;
+    if ((rc = fetch(h, {{p, h->d_att, stats}, {p + stats, h->d_acc, stats}}))) return rc;
     *len = need;
     return RFIM_OK;
 }
@@ -2542,8 +2679,7 @@ int rfim_pool_result(rfim_pool_t *p, int slot, rfim_result_t *res) {
     res->exchanges = h->k;
     int rc;
     if (res->temps) std::copy(h->T.begin(), h->T.end(), res->temps);
-    if (res->energies && (rc = rfim_energies(h, res->energies))) return rc;
-    if (res->magnetizations && (rc = rfim_magnetizations(h, res->magnetizations))) return rc;
+    if ((res->energies || res->magnetizations) && (rc = read_slots(h, res->energies, res->magnetizations))) return rc;
     if (res->perm && (rc = rfim_get_perm(h, res->perm))) return rc;
     return RFIM_OK;
 }

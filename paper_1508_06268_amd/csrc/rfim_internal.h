@@ -193,7 +193,31 @@ hipError_t launch_generic_sweep(const Lattice &lat, int colour, int toff, hipStr
 // does not have to match the sweep's.
 int energy_blocks(const Lattice &lat);
 hipError_t launch_energy(const Lattice &lat, hipStream_t s);
-hipError_t launch_reduce(const Lattice &lat, int64_t *B, double *F, int64_t *M, hipStream_t s);
+// Totals of the partials, to the arrays that are not null (device memory or
+// pinned host memory): by replica id, E_slot and M_slot by temperature slot.
+struct Readout {
+    int64_t *B = nullptr;
+    double *F = nullptr;
+    int64_t *M = nullptr;
+    double *E_slot = nullptr;
+    int64_t *M_slot = nullptr;
+};
+hipError_t launch_reduce(const Lattice &lat, const Readout &out, hipStream_t s);
+// Up to kMax device arrays of whole dwords to pinned host memory.
+struct CopyOut {
+    static constexpr int kMax = 3;
+    const void *src[kMax] = {};
+    void *dst[kMax] = {};
+    uint32_t words[kMax] = {};
+};
+hipError_t launch_copy_out(const CopyOut &c, hipStream_t s);
+// Configurations (+-1, natural site order; sites first .. first + count - 1 of
+// the replicas' [R][N], both multiples of 64 or of a replica) to and from
+// pinned host memory, in either storage, and the fields of a realization from
+// it (first and count multiples of 4).
+hipError_t launch_spins_out(const Lattice &lat, size_t first, size_t count, int8_t *dst, hipStream_t s);
+hipError_t launch_spins_in(const Lattice &lat, size_t first, size_t count, const int8_t *src, hipStream_t s);
+hipError_t launch_fields_in(const Lattice &lat, size_t first, size_t count, const float *src, hipStream_t s);
 // One exchange step for each of the n realizations in lats (device array).
 hipError_t launch_exchange(const Lattice *lats, int n, int tadv, hipStream_t s);
 hipError_t launch_advance(const Lattice &lat, int tadv, hipStream_t s);

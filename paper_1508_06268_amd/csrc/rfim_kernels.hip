@@ -1693,6 +1693,170 @@ __global__ __launch_bounds__(256) void unpack_bits_kernel(Lattice lat) {
 }
 
 // ---------------------------------------------------------------------
+// Natural site order <-> the device layout (index only), for the calls that
+// read or write configurations and fields: `dst` / `src` are pinned host
+// memory, sites first .. first + count - 1 of the replicas' [R][N] (a
+// multiple of the unit a thread takes).  Bound by the host link: the kernels
+// read and write it in whole 16-byte (or 4-byte) pieces, in order.  The host
+// did this site by site, with three divisions each, on a copy of the byte
+// array: 3.4 ns a site and pass.
+// ---------------------------------------------------------------------
+
+// Bytes 1 / 0 to +1 / -1 (0x01 / 0xFF), four at a time.
+__device__ __forceinline__ uint32_t signs_of(uint32_t b) { return 0xFFFFFFFFu ^ (b * 0xFEu); }
+
+// Bytes a0 b0 a1 b1 and a2 b2 a3 b3.
+__device__ __forceinline__ void interleave(uint32_t a, uint32_t b, uint32_t &lo, uint32_t &hi) {
+    lo = __builtin_amdgcn_perm(b, a, 0x05010400u);
+    hi = __builtin_amdgcn_perm(b, a, 0x07030602u);
+}
+
+// The replica and the site of natural index e, and whether the even x of its
+// row belong to colour 1.
+struct NaturalPlace {
+    uint32_t r, i, odd_row;
+};
+
+__device__ __forceinline__ NaturalPlace natural_place(const Lattice &lat, const FastDiv &by_l, size_t e) {
+    NaturalPlace p;
+    p.r = (uint32_t)(e / (size_t)(uint32_t)lat.N);
+    p.i = (uint32_t)(e - (size_t)p.r * (size_t)(uint32_t)lat.N);
+    const uint32_t row = div_by(p.i, by_l), z = div_by(row, by_l);
+    p.odd_row = (row - z * (uint32_t)lat.L + z) & 1u;
+    return p;
+}
+
+template <int V, bool BITS>
+__global__ __launch_bounds__(256) void spins_out_kernel(Lattice lat, FastDiv by_l, size_t first, size_t count,
+                                                         int8_t *__restrict__ dst) {
+    const size_t u = (size_t)V * (blockIdx.x * 256u + threadIdx.x);
+    if (u >= count) return;
+    const NaturalPlace p = natural_place(lat, by_l, first + u);
+    const uint32_t j = p.i >> 1;
+    if constexpr (V == 16) {
+        // eight pairs: eight bytes (two Philox blocks' bits) of each colour
+        uint32_t c[2][2];
+#pragma unroll
+        for (int col = 0; col < 2; ++col) {
+            if (BITS) {
+                const uint32_t w = gptr((const uint32_t *)lat.bits)[((size_t)p.r * 2u + col) * ((uint32_t)lat.N >> 6) + (j >> 5)];
+                const uint32_t b = (j & 31u) >> 2;
+                c[col][0] = (w >> b) & 0x01010101u;
+                c[col][1] = (w >> (b + 1u)) & 0x01010101u;
+            } else {
+                load_words<2>(gptr((const uint8_t *)lat.spins) + (size_t)p.r * lat.N + (size_t)col * lat.half, j, c[col]);
+            }
+        }
+        u32x4 v;
+        uint32_t o[4];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            interleave(p.odd_row ? c[1][q] : c[0][q], p.odd_row ? c[0][q] : c[1][q], o[2 * q], o[2 * q + 1]);
+        v.x = signs_of(o[0]);
+        v.y = signs_of(o[1]);
+        v.z = signs_of(o[2]);
+        v.w = signs_of(o[3]);
+        *(u32x4 *)(dst + u) = v;
+    } else {
+        // four sites, which may lie in two rows
+        uint32_t v = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+            const NaturalPlace s = natural_place(lat, by_l, first + u + q);
+            const uint32_t col = s.odd_row ^ (s.i & 1u);
+            v |= (uint32_t)gptr((const uint8_t *)lat.spins)[(size_t)s.r * lat.N + (size_t)col * lat.half + (s.i >> 1)] << (8u * q);
+        }
+        *(uint32_t *)(dst + u) = signs_of(v);
+    }
+}
+
+// +1 / -1 bytes to 1 / 0.
+__device__ __forceinline__ uint32_t ups_of(uint32_t v) { return ~(v >> 7) & 0x01010101u; }
+
+// The bytes of even and of odd x among eight sites (lo: the first four).
+__device__ __forceinline__ void deinterleave(uint32_t lo, uint32_t hi, uint32_t &even, uint32_t &odd) {
+    even = __builtin_amdgcn_perm(hi, lo, 0x06040200u);
+    odd = __builtin_amdgcn_perm(hi, lo, 0x07050301u);
+}
+
+template <int V>
+__global__ __launch_bounds__(256) void spins_in_kernel(Lattice lat, FastDiv by_l, size_t first, size_t count,
+                                                        const int8_t *__restrict__ src) {
+    const size_t u = (size_t)V * (blockIdx.x * 256u + threadIdx.x);
+    if (u >= count) return;
+    if constexpr (V == 16) {
+        const NaturalPlace p = natural_place(lat, by_l, first + u);
+        const u32x4 v = *(const u32x4 *)(src + u);
+        uint32_t even[2], odd[2];
+        deinterleave(ups_of(v.x), ups_of(v.y), even[0], odd[0]);
+        deinterleave(ups_of(v.z), ups_of(v.w), even[1], odd[1]);
+        GAS uint8_t *base = gptr(lat.spins) + (size_t)p.r * lat.N;
+        store_words<2>(base + (p.odd_row ? (size_t)lat.half : 0u), p.i >> 1, even);
+        store_words<2>(base + (p.odd_row ? 0u : (size_t)lat.half), p.i >> 1, odd);
+    } else {
+        const uint32_t v = ups_of(*(const uint32_t *)(src + u));
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+            const NaturalPlace s = natural_place(lat, by_l, first + u + q);
+            const uint32_t col = s.odd_row ^ (s.i & 1u);
+            gptr(lat.spins)[(size_t)s.r * lat.N + (size_t)col * lat.half + (s.i >> 1)] = (uint8_t)(v >> (8u * q));
+        }
+    }
+}
+
+// Bit storage: 64 sites of a row are one word of each colour.
+__global__ __launch_bounds__(256) void bits_in_kernel(Lattice lat, FastDiv by_l, size_t first, size_t count,
+                                                       const int8_t *__restrict__ src) {
+    const size_t u = 64u * (size_t)(blockIdx.x * 256u + threadIdx.x);
+    if (u >= count) return;
+    const NaturalPlace p = natural_place(lat, by_l, first + u);
+    uint32_t even = 0, odd = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+        const u32x4 v = *(const u32x4 *)(src + u + 16u * q);
+        uint32_t e, o;
+        deinterleave(ups_of(v.x), ups_of(v.y), e, o);       // pairs 8q .. 8q + 3: block 2q of the word
+        even |= e << (2u * q);
+        odd |= o << (2u * q);
+        deinterleave(ups_of(v.z), ups_of(v.w), e, o);
+        even |= e << (2u * q + 1u);
+        odd |= o << (2u * q + 1u);
+    }
+    const uint32_t W1 = (uint32_t)lat.N >> 6;
+    GAS uint32_t *base = gptr(lat.bits) + (size_t)p.r * 2u * W1 + (p.i >> 6);
+    base[p.odd_row ? W1 : 0u] = even;
+    base[p.odd_row ? 0u : W1] = odd;
+}
+
+// Fields h_i in natural order to the sweeps' arrays, four sites a thread.
+__global__ __launch_bounds__(256) void fields_in_kernel(Lattice lat, FastDiv by_l, size_t first, size_t count,
+                                                         const float *__restrict__ src) {
+    const size_t u = 4u * (size_t)(blockIdx.x * 256u + threadIdx.x);
+    if (u >= count) return;
+    const f32x4 v = *(const f32x4 *)(src + u);
+    const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+        const NaturalPlace s = natural_place(lat, by_l, first + u + q);
+        const size_t at = (size_t)(s.odd_row ^ (s.i & 1u)) * lat.half + (s.i >> 1);
+        if (lat.kind == 0) {
+            ((GAS uint8_t *)lat.fbits)[at] = f[q] > 0.0f ? 4 : 0;
+        } else {
+            ((GAS float *)lat.fraw)[at] = f[q];
+            ((GAS float *)lat.fhf)[at] = (float)(lat.h * (double)f[q] - 6.0 * lat.J);
+        }
+    }
+}
+
+// Device arrays to pinned host memory, in one launch.
+__global__ __launch_bounds__(256) void copy_out_kernel(CopyOut c) {
+    const uint32_t q = blockIdx.y, n = c.words[q];
+    GAS const uint32_t *src = (GAS const uint32_t *)c.src[q];
+    uint32_t *dst = (uint32_t *)c.dst[q];
+    for (uint32_t w = blockIdx.x * 256u + threadIdx.x; w < n; w += 256u * gridDim.x) dst[w] = src[w];
+}
+
+// ---------------------------------------------------------------------
 // Energy partials (Eq. 1) of a state at rest, for the calls that read
 // energies and for the sweeps that do not write partials themselves.  Every
 // bond joins a colour-0 and a colour-1 site, so B = sum over colour-1 sites
@@ -1814,8 +1978,7 @@ __device__ __forceinline__ void sum_range(GAS const double *pp, size_t qstride, 
     }
 }
 
-__device__ __forceinline__ void replica_totals(const Lattice &lat, int64_t *Bout = nullptr,
-                                               double *Fout = nullptr, int64_t *Mout = nullptr,
+__device__ __forceinline__ void replica_totals(const Lattice &lat, const Readout &out = Readout{},
                                                double *sE = nullptr, double *sM = nullptr) {
     __shared__ double red[kExchangeThreads * 3];
     const int R = lat.R, nblk = lat.nblk;
@@ -1859,9 +2022,14 @@ __device__ __forceinline__ void replica_totals(const Lattice &lat, int64_t *Bout
                 sE[rt] = E;
                 sM[rt] = M;
             }
-            if (Bout) Bout[rt] = (int64_t)B;
-            if (Fout) Fout[rt] = F;
-            if (Mout) Mout[rt] = (int64_t)M;
+            if (out.B) out.B[rt] = (int64_t)B;
+            if (out.F) out.F[rt] = F;
+            if (out.M) out.M[rt] = (int64_t)M;
+            if (out.E_slot || out.M_slot) {
+                const int slot = gptr(lat.r2t)[rt];
+                if (out.E_slot) out.E_slot[slot] = E;
+                if (out.M_slot) out.M_slot[slot] = (int64_t)M;
+            }
         }
         __syncthreads();
     }
@@ -1869,9 +2037,8 @@ __device__ __forceinline__ void replica_totals(const Lattice &lat, int64_t *Bout
 
 // Totals per replica id for the observables calls (same reduction as the
 // exchange step, so both give the same bits).
-__global__ __launch_bounds__(kExchangeThreads) void reduce_kernel(Lattice lat, int64_t *Bout, double *Fout,
-                                                                  int64_t *Mout) {
-    replica_totals(lat, Bout, Fout, Mout);
+__global__ __launch_bounds__(kExchangeThreads) void reduce_kernel(Lattice lat, Readout out) {
+    replica_totals(lat, out);
 }
 
 // The decision for pair (p, p+1) of exchange step k: Philox word pair ->
@@ -1910,7 +2077,7 @@ __global__ __launch_bounds__(kExchangeThreads) void exchange_kernel(const Lattic
         GAS const double *orow = gptr(lat.obs) + 6 * (size_t)tc;
 #pragma unroll
         for (int q = 0; q < 6; ++q) o[q] = orow[q];
-        replica_totals(lat, nullptr, nullptr, nullptr, sE, sM);
+        replica_totals(lat, Readout{}, sE, sM);
         if (mine) st2r[t] = my_t2r;
         __syncthreads();
         // pairs (p, p+1) with p = k mod 2: thread p decides its pair; the
@@ -2421,8 +2588,54 @@ hipError_t launch_energy(const Lattice &lat, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(const Lattice &lat, int64_t *B, double *F, int64_t *M, hipStream_t s) {
-    hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kExchangeThreads), 0, s, lat, B, F, M);
+hipError_t launch_reduce(const Lattice &lat, const Readout &out, hipStream_t s) {
+    hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kExchangeThreads), 0, s, lat, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_out(const CopyOut &c, hipStream_t s) {
+    uint32_t most = 0;
+    for (int q = 0; q < CopyOut::kMax; ++q) most = std::max(most, c.words[q]);
+    if (most == 0) return hipSuccess;
+    hipLaunchKernelGGL(copy_out_kernel, dim3(std::min((most + 255u) / 256u, 256u), (unsigned)CopyOut::kMax), dim3(256), 0, s, c);
+    return hipGetLastError();
+}
+
+// Units of 16 sites where a row holds whole units, else of 4 (a whole number
+// of them in every replica).
+static int natural_unit(const Lattice &lat) { return lat.L % 16 == 0 ? 16 : 4; }
+
+hipError_t launch_spins_out(const Lattice &lat, size_t first, size_t count, int8_t *dst, hipStream_t s) {
+    if (count == 0) return hipSuccess;
+    const FastDiv by_l = fast_div((uint32_t)lat.L);
+    const unsigned nb = (unsigned)((count / (size_t)natural_unit(lat) + 255) / 256);
+    if (lat.bits)
+        hipLaunchKernelGGL((spins_out_kernel<16, true>), dim3(nb), dim3(256), 0, s, lat, by_l, first, count, dst);
+    else if (natural_unit(lat) == 16)
+        hipLaunchKernelGGL((spins_out_kernel<16, false>), dim3(nb), dim3(256), 0, s, lat, by_l, first, count, dst);
+    else
+        hipLaunchKernelGGL((spins_out_kernel<4, false>), dim3(nb), dim3(256), 0, s, lat, by_l, first, count, dst);
+    return hipGetLastError();
+}
+
+hipError_t launch_spins_in(const Lattice &lat, size_t first, size_t count, const int8_t *src, hipStream_t s) {
+    if (count == 0) return hipSuccess;
+    const FastDiv by_l = fast_div((uint32_t)lat.L);
+    const size_t unit = lat.bits ? 64 : (size_t)natural_unit(lat);
+    const unsigned nb = (unsigned)((count / unit + 255) / 256);
+    if (lat.bits)
+        hipLaunchKernelGGL(bits_in_kernel, dim3(nb), dim3(256), 0, s, lat, by_l, first, count, src);
+    else if (unit == 16)
+        hipLaunchKernelGGL(spins_in_kernel<16>, dim3(nb), dim3(256), 0, s, lat, by_l, first, count, src);
+    else
+        hipLaunchKernelGGL(spins_in_kernel<4>, dim3(nb), dim3(256), 0, s, lat, by_l, first, count, src);
+    return hipGetLastError();
+}
+
+hipError_t launch_fields_in(const Lattice &lat, size_t first, size_t count, const float *src, hipStream_t s) {
+    if (count == 0) return hipSuccess;
+    hipLaunchKernelGGL(fields_in_kernel, dim3((unsigned)((count / 4 + 255) / 256)), dim3(256), 0, s, lat,
+                       fast_div((uint32_t)lat.L), first, count, src);
     return hipGetLastError();
 }
 
