@@ -873,6 +873,60 @@ int ensure_aux(rfim *h) {
     return RFIM_OK;
 }
 
+// The two copies of the permutation and of the partials that the pending
+// exchange steps of one call go between (rfim_dev::StepIn).  The second copies
+// lie in rows of the partial array that shapes of so few partials per replica
+// do not use (it has at least 64 rows of R_cap (B, F, M) entries).  Between
+// calls the handle's own arrays hold the permutation.
+struct StepBuffers {
+    rfim_dev::StepIn in;
+    explicit StepBuffers(rfim *h) {
+        const size_t row = (size_t)h->R_cap * 3;
+        part_[0] = h->d_part;
+        part_[1] = h->d_part + rfim_dev::kMaxStepPartials * row;
+        r2t_[0] = h->d_r2t;
+        t2r_[0] = h->d_t2r;
+        r2t_[1] = (int32_t *)(h->d_part + 2 * rfim_dev::kMaxStepPartials * row);
+        t2r_[1] = (int32_t *)(h->d_part + (2 * rfim_dev::kMaxStepPartials + 1) * row);
+        in.nblk = h->nblk;
+        rfim_dev::partial_groups(h->R, h->nblk, &in.groups, &in.per);
+    }
+    bool pending() const { return in.part != nullptr; }
+    // An interval that ends in a step starts at sweep t.
+    void start(uint64_t t) {
+        in.r2t = r2t_[perm_];
+        in.t2r = t2r_[perm_];
+        in.r2t_out = r2t_[perm_ ^ 1];
+        in.t2r_out = t2r_[perm_ ^ 1];
+        in.part_out = part_[next_];
+        in.t0 = (uint32_t)t;
+    }
+    // A sweep launch was issued: it took the pending step, if there was one.
+    void taken() {
+        if (!in.part) return;
+        in.part = nullptr;
+        perm_ ^= 1;
+        in.r2t = r2t_[perm_];
+        in.t2r = t2r_[perm_];
+    }
+    // The interval's last launch was issued: its step k is pending.
+    void end(uint64_t k) {
+        in.part = part_[next_];
+        in.k = (uint32_t)k;
+        next_ ^= 1;
+    }
+    // An exchange launch took the step and wrote the handle's own arrays.
+    void settled() {
+        in.part = nullptr;
+        perm_ = 0;
+    }
+
+  private:
+    double *part_[2];
+    int32_t *r2t_[2], *t2r_[2];
+    int perm_ = 0, next_ = 0;
+};
+
 int sweep_impl(rfim *h, int64_t n, int every) {
     h->lat_host = h->lattice();
     const Lattice &lat = h->lat_host;
@@ -910,12 +964,37 @@ int sweep_impl(rfim *h, int64_t n, int every) {
         HIPCHK(hipEventRecord(h->ev_fork, h->stream));
         HIPCHK(hipStreamWaitEvent(h->aux, h->ev_fork, 0));
     }
+    // Shapes whose kernels run whole intervals of a replica take the exchange
+    // step before their first sweep (StepIn): the steps of a call after its
+    // first interval then need no launch of their own, and the last one, or
+    // one before an interval without a step, is an exchange launch (settle).
+    // Only where the launch is small enough for the device to hold it at once
+    // (256 CUs, one workgroup each at least): a longer one gains little from
+    // the launch saved and runs better with the registers the step takes.
+    const bool lazy = !tiled && !bitsm && !h->measure && h->nblk <= rfim_dev::kMaxStepPartials &&
+                      (long long)h->R * h->nblk <= 256 &&
+                      (pow2 ? h->mode >= 1 : h->box.planes > 0 || rfim_dev::generic_resident(h->L));
+    StepBuffers sb(h);
+    int unsettled = 0;                  // sweeps since the device counters were last right
+    auto settle = [&]() -> int {
+        HIPCHK(rfim_dev::launch_exchange(h->d_lat, 1, unsettled, sb.in, h->stream));
+        sb.settled();
+        unsettled = 0;
+        return RFIM_OK;
+    };
     int64_t remaining = n;
     while (remaining > 0) {
         int64_t to_next = every > 0 ? (int64_t)(every - (int64_t)(h->t % (uint64_t)every)) : remaining;
         const int m = (int)std::min<int64_t>(remaining, to_next);
         const bool exch = every > 0 && m == to_next;
         const bool fused = exch && !tiled && (bitsm || h->box.planes || rfim_dev::fused_energy(lat));
+        if (!exch && sb.pending()) {
+            const int rc = settle();
+            if (rc) return rc;
+        }
+        if (lazy && exch) sb.start(h->t);
+        const rfim_dev::StepIn none;
+        const rfim_dev::StepIn &in = lazy && exch ? sb.in : none;
         if (bitsm) {
             for (int q = 0; q < m; ++q) {
                 const int e = fused && q == m - 1;
@@ -935,14 +1014,16 @@ int sweep_impl(rfim *h, int64_t n, int every) {
             for (int q = 0; q < m;) {
                 const int ns = std::min(K, m - q);
                 const int e = fused && q + ns == m;
-                HIPCHK(rfim_dev::launch_slab_sweep(lat, h->d_spins, h->d_spins_alt, h->mode, h->nw, h->wg, ns, q, e,
+                HIPCHK(rfim_dev::launch_slab_sweep(lat, in, h->d_spins, h->d_spins_alt, h->mode, h->nw, h->wg, ns, q, e,
                                                    h->stream));
                 std::swap(h->d_spins, h->d_spins_alt);
+                sb.taken();
                 q += ns;
             }
             h->lat_host = h->lattice();
         } else if (pow2 && h->mode == 1) {
-            HIPCHK(rfim_dev::launch_resident(ln, m, fused ? 1 : 0, h->stream));
+            HIPCHK(rfim_dev::launch_resident(ln, in, m, fused ? 1 : 0, h->stream));
+            sb.taken();
         } else if (pow2 && split) {
             for (int q = 0; q < m; ++q) {
                 const int e = fused && q == m - 1;
@@ -962,21 +1043,31 @@ int sweep_impl(rfim *h, int64_t n, int every) {
             for (int q = 0; q < m;) {
                 const int left = whole ? 1 : (m - q + h->box.sweeps - 1) / h->box.sweeps, ns = (m - q + left - 1) / left;
                 const int e = fused && q + ns == m;
-                HIPCHK(rfim_dev::launch_box(lat, h->d_spins, whole ? h->d_spins : h->d_spins_alt, h->box, ns, q, e,
+                HIPCHK(rfim_dev::launch_box(lat, in, h->d_spins, whole ? h->d_spins : h->d_spins_alt, h->box, ns, q, e,
                                             h->stream));
                 if (!whole) std::swap(h->d_spins, h->d_spins_alt);
+                sb.taken();
                 q += ns;
             }
             h->lat_host = h->lattice();
         } else if (rfim_dev::generic_resident(h->L)) {
-            HIPCHK(rfim_dev::launch_generic_resident(lat, m, fused ? 1 : 0, h->stream));
+            HIPCHK(rfim_dev::launch_generic_resident(lat, in, m, fused ? 1 : 0, h->stream));
+            sb.taken();
         } else {
             for (int q = 0; q < m; ++q) {
                 HIPCHK(rfim_dev::launch_generic_sweep(lat, 0, q, h->stream));
                 HIPCHK(rfim_dev::launch_generic_sweep(lat, 1, q, h->stream));
             }
         }
-        if (exch) {
+        if (exch && lazy) {
+            unsettled += m;
+            sb.end(h->k);
+            if (remaining == m) {       // the call ends here
+                const int rc = settle();
+                if (rc) return rc;
+            }
+            h->k += 1;
+        } else if (exch) {
             hipStream_t xs = h->stream;
             if (split) {
                 xs = step_on_aux ? h->aux : h->stream;
@@ -985,7 +1076,7 @@ int sweep_impl(rfim *h, int64_t n, int every) {
                 HIPCHK(hipStreamWaitEvent(xs, h->ev_join, 0));
             }
             if (!fused) HIPCHK(rfim_dev::launch_energy(lat, xs));
-            HIPCHK(rfim_dev::launch_exchange(h->d_lat, 1, m, xs));
+            HIPCHK(rfim_dev::launch_exchange(h->d_lat, 1, m, rfim_dev::StepIn{}, xs));
             int rc;
             if ((rc = measure_after_exchange(h, xs))) return rc;
             if (split) {
@@ -2053,7 +2144,7 @@ int batch_segment(rfim_batch *b, int m, bool exch) {
     const int nq = (int)qs.size();
     for (size_t i = 0; i < lanes.size(); ++i)
         if (lanes[i].mode == 1)
-            HIPCHK(rfim_dev::launch_resident(lanes[i].ln[0], m, exch ? 1 : 0, qs[i % nq]));
+            HIPCHK(rfim_dev::launch_resident(lanes[i].ln[0], rfim_dev::StepIn{}, m, exch ? 1 : 0, qs[i % nq]));
     // lane by lane, and in a lane group by group: a group's half-sweeps
     // follow one another on its stream
     for (size_t i = 0; i < lanes.size(); ++i)
@@ -2079,7 +2170,7 @@ int batch_segment(rfim_batch *b, int m, bool exch) {
         for (const auto &c : b->classes)
             if (!class_fused(b, c))
                 for (int i : c.members) HIPCHK(rfim_dev::launch_energy(b->items[i]->lattice(), b->stream));
-        HIPCHK(rfim_dev::launch_exchange(b->d_lats, (int)b->items.size(), m, b->stream));
+        HIPCHK(rfim_dev::launch_exchange(b->d_lats, (int)b->items.size(), m, rfim_dev::StepIn{}, b->stream));
         HIPCHK(rfim_dev::launch_fourier_batch(b->d_lats, b->d_fmap, b->fchunks, b->d_fmap + b->fchunks, b->freplicas,
                                               b->fmax_l, b->stream));
     } else {

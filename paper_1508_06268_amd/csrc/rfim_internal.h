@@ -105,6 +105,28 @@ int stream_blocks_per_replica(int L, int nw, int wg);
 // True when the sweep kernels themselves write the energy partials.
 bool fused_energy(const Lattice &lat);
 
+// One realization's interval kernels (resident, slab, box) can take the
+// exchange step before their first sweep: every workgroup decides the pair of
+// its own replica from the partials of the previous interval, so that an
+// interval is its sweep launches alone.  The step reads one copy of the
+// permutation and of the partials and writes the other (a workgroup that ends
+// early must not change what one that starts late still reads); the counters
+// come from the host.  r2t null: no such step, everything from the descriptor.
+struct StepIn {
+    const int32_t *r2t = nullptr, *t2r = nullptr;   // the permutation to sweep by, or before the step
+    const double *part = nullptr;                   // null: no step is pending
+    int32_t *r2t_out = nullptr, *t2r_out = nullptr; // the permutation after it
+    double *part_out = nullptr;                     // where this interval's partials go
+    uint32_t k = 0, t0 = 0;                         // the step's exchange counter; the sweep counter
+    int nblk = 1, groups = 1, per = 1;              // the order the partials are added in (partial_groups)
+};
+// Workgroups' ranges the totals of nblk partials of R replicas are added in:
+// `groups` ranges of `per`, each in order, then the ranges in order.
+void partial_groups(int R, int nblk, int *groups, int *per);
+// Most replicas whose exchange step runs in one pass of a workgroup, and most
+// partials per replica a step before the sweeps adds.
+constexpr int kExchangeThreads = 1024, kMaxStepPartials = 8;
+
 // One launch over a set of realizations that share L, field kind and shape:
 // lats = device array of descriptors; map = one entry per workgroup:
 // x = (realization << 16) | replica, y = block within the replica
@@ -127,8 +149,8 @@ struct Launch {
 int slab_sweeps_per_launch(int mode);
 size_t slab_lds_bytes(int L, int mode, int nslab);
 int slab_positions_per_thread(int L, int mode, int nslab, int wg);
-hipError_t launch_slab_sweep(const Lattice &lat, const uint8_t *src, uint8_t *dst, int mode, int nslab, int wg,
-                             int nsweep, int toff, int energy, hipStream_t s);
+hipError_t launch_slab_sweep(const Lattice &lat, const StepIn &in, const uint8_t *src, uint8_t *dst, int mode, int nslab,
+                             int wg, int nsweep, int toff, int energy, hipStream_t s);
 
 // Double-checkerboard order with multi-hit updates (Sec. 3.2, Sec. 5.2):
 // tiles of tx * ty * tz sites, `hits` local sweeps per tile visit.  Valid
@@ -165,7 +187,7 @@ hipError_t launch_init(const Lattice &lat, int r0, int r1, hipStream_t s);
 hipError_t launch_stream_sweep(const Launch &ln, int colour, int toff, int energy, hipStream_t s);
 // Resident: nsweep whole sweeps in one launch (energy != 0: also the
 // energy partials of the final state).
-hipError_t launch_resident(const Launch &ln, int nsweep, int energy, hipStream_t s);
+hipError_t launch_resident(const Launch &ln, const StepIn &in, int nsweep, int energy, hipStream_t s);
 // Other even L, one realization: half-sweeps (any L), or whole sweeps of
 // LDS-resident replicas with the energy partials of the final state: for L = 4
 // and the small L whose planes do not split into whole Philox blocks (L % 4 ==
@@ -174,7 +196,7 @@ hipError_t launch_resident(const Launch &ln, int nsweep, int energy, hipStream_t
 // half-sweeps: 2.8 and 7.8 at L = 10; about even at L = 26).
 constexpr int kGenericResidentMaxL = 22;
 bool generic_resident(int L);
-hipError_t launch_generic_resident(const Lattice &lat, int nsweep, int energy, hipStream_t s);
+hipError_t launch_generic_resident(const Lattice &lat, const StepIn &in, int nsweep, int energy, hipStream_t s);
 // Boxes (L a multiple of 4, not a power of two): slabs of `planes` planes, up
 // to `sweeps` whole sweeps a launch, from src to dst (a second spin buffer).
 // box_plan: the split for R replicas, planes = 0 where half-sweeps or the
@@ -185,8 +207,8 @@ struct BoxPlan {
     int planes, sweeps;
 };
 BoxPlan box_plan(int L, int R);
-hipError_t launch_box(const Lattice &lat, const uint8_t *src, uint8_t *dst, const BoxPlan &plan, int nsweep, int toff,
-                      int energy, hipStream_t s);
+hipError_t launch_box(const Lattice &lat, const StepIn &in, const uint8_t *src, uint8_t *dst, const BoxPlan &plan,
+                      int nsweep, int toff, int energy, hipStream_t s);
 hipError_t launch_generic_sweep(const Lattice &lat, int colour, int toff, hipStream_t s);
 // Energy partials of the state at rest, lat.nblk per replica, from the bytes
 // or, in bit storage, the bits; energy_blocks: the count for a reduction that
@@ -218,8 +240,10 @@ hipError_t launch_copy_out(const CopyOut &c, hipStream_t s);
 hipError_t launch_spins_out(const Lattice &lat, size_t first, size_t count, int8_t *dst, hipStream_t s);
 hipError_t launch_spins_in(const Lattice &lat, size_t first, size_t count, const int8_t *src, hipStream_t s);
 hipError_t launch_fields_in(const Lattice &lat, size_t first, size_t count, const float *src, hipStream_t s);
-// One exchange step for each of the n realizations in lats (device array).
-hipError_t launch_exchange(const Lattice *lats, int n, int tadv, hipStream_t s);
+// One exchange step for each of the n realizations in lats (device array);
+// with `in` (n = 1) the step pending there, which brings the permutation, the
+// counters (tadv sweeps, step in.k) and the rest back to the descriptor.
+hipError_t launch_exchange(const Lattice *lats, int n, int tadv, const StepIn &in, hipStream_t s);
 hipError_t launch_advance(const Lattice &lat, int tadv, hipStream_t s);
 // Fourier observable of every replica, accumulated by slot (rfim_measure.hip),
 // through the descriptor's fpart, trig and fobs.

@@ -625,6 +625,123 @@ __device__ __forceinline__ void block_partial(PD dst, int nsite, int ksum, int u
     }
 }
 
+__device__ __forceinline__ double energy_of(const Lattice &lat, double B, double F) {
+    return -(lat.J * B) - (lat.h * F);
+}
+
+// The decision for pair (p, p+1) of exchange step k: Philox word pair ->
+// a uniform double in [0, 1) with 53 random bits, accepted if Delta >= 0 or
+// u < e^Delta.
+__device__ __forceinline__ bool exchange_accept(const Lattice &lat, int p, uint64_t k, double delta) {
+    const Words w = philox10((uint32_t)p, (uint32_t)k, 0u, (kTagExch << 28) | lat.rho, lat.key0, lat.key1);
+    const double u53 = ((double)(w.w0 >> 11) * 4294967296.0 + (double)w.w1) * 0x1p-53;
+    return delta >= 0.0 || u53 < exp(delta);
+}
+
+// Energy and magnetisation of replica r from its partials, added in the order
+// of replica_totals.
+__device__ __forceinline__ void partial_totals(const Lattice &lat, const StepIn &in, uint32_t r, double &E, double &M) {
+    GAS const double *pp = (GAS const double *)in.part + 3 * (size_t)r;
+    const size_t stride = 3 * (size_t)lat.pstride;
+    double v[kMaxStepPartials][3];
+#pragma unroll
+    for (int q = 0; q < kMaxStepPartials; ++q)
+        if (q < in.nblk)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) v[q][i] = pp[(size_t)q * stride + i];
+    double T[3] = {0.0, 0.0, 0.0}, g[3] = {0.0, 0.0, 0.0};
+    int left = in.per;
+#pragma unroll
+    for (int q = 0; q < kMaxStepPartials; ++q) {
+        if (q >= in.nblk) break;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) g[i] += v[q][i];
+        if (--left > 0 && q + 1 < in.nblk) continue;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            T[i] = q < in.per ? g[i] : T[i] + g[i];
+            g[i] = 0.0;
+        }
+        left = in.per;
+    }
+    E = energy_of(lat, T[0], T[1]);
+    M = T[2];
+}
+
+// The slot replica r sweeps at (first wave of a workgroup).  With a pending
+// step, its pair's exchange first; `lead` (one workgroup per replica) records
+// it: the permutation, the pair's counters if the replica was the colder one,
+// and the sample of the slot the replica ends at.
+// STEP is a template parameter of the kernels: the step's FP64 code costs
+// scalar registers, and with them a wave per SIMD, that launches without one
+// should not pay.
+template <bool STEP>
+__device__ __forceinline__ int take_slot(const Lattice &lat, const StepIn &in, uint32_t r, bool lead) {
+    const int p = ((GAS const int32_t *)(in.r2t ? in.r2t : lat.r2t))[r];
+    if (!STEP) return p;
+    // the pairs of step k are (q, q + 1) with q = k mod 2
+    const int lo = ((p ^ (int)in.k) & 1) == 0 ? p : p - 1;
+    const bool pair = lo >= 0 && lo + 1 < lat.R;
+    double E, M;
+    partial_totals(lat, in, r, E, M);
+    int slot = p;
+    bool yes = false;
+    if (pair) {
+        const int other = p == lo ? lo + 1 : lo;
+        const int b = ((GAS const int32_t *)in.t2r)[other];
+        const double db = gptr(lat.beta)[lo + 1] - gptr(lat.beta)[lo];
+        double Eb, Mb;
+        partial_totals(lat, in, (uint32_t)b, Eb, Mb);
+        const double delta = p == lo ? db * (Eb - E) : db * (E - Eb);
+        yes = exchange_accept(lat, lo, in.k, delta);
+        if (yes) slot = other;
+    }
+    if (lead) {
+        if (threadIdx.x == 0) {
+            in.r2t_out[r] = slot;
+            in.t2r_out[slot] = (int32_t)r;
+            if (pair && p == lo) {
+                gptr(lat.att)[p] += 1;
+                if (yes) gptr(lat.acc)[p] += 1;
+            }
+        }
+        if (threadIdx.x < 6u) {
+            const double m2 = M * M;
+            const double add[6] = {1.0, E, E * E, fabs(M), m2, m2 * m2};
+            double a = add[0];
+#pragma unroll
+            for (int q = 1; q < 6; ++q) a = threadIdx.x == (uint32_t)q ? add[q] : a;
+            gptr(lat.obs)[6 * (size_t)slot + threadIdx.x] += a;
+        }
+    }
+    return slot;
+}
+
+// The slot's table into LDS: thresholds (+-1 fields) or the continuous
+// factors; by the first wave.
+template <int KIND, bool STEP>
+__device__ __forceinline__ void stage_table(const Lattice &lat, const StepIn &in, uint32_t r, bool lead, uint32_t *sthr) {
+    if (threadIdx.x >= 64u) return;
+    const int slot = take_slot<STEP>(lat, in, r, lead);
+    if (KIND == 0) {
+        if (threadIdx.x < 32u) sthr[threadIdx.x] = gptr(lat.thr)[slot * 32 + threadIdx.x];
+    } else {
+        cont_table_fill(sthr, gptr(lat.betaf)[slot], lat.Jf);
+    }
+}
+
+// The same for the sizes whose decisions take the exponent's factor a.
+template <int KIND, bool STEP>
+__device__ __forceinline__ void stage_factor(const Lattice &lat, const StepIn &in, uint32_t r, bool lead, uint32_t *sthr) {
+    if (threadIdx.x >= 64u) return;
+    const int slot = take_slot<STEP>(lat, in, r, lead);
+    if (KIND == 0) {
+        if (threadIdx.x < 32u) sthr[threadIdx.x] = gptr(lat.thr)[slot * 32 + threadIdx.x];
+    } else if (threadIdx.x == 0) {
+        sthr[0] = __float_as_uint(-2.0f * 1.44269504088896341f * gptr(lat.betaf)[slot]);
+    }
+}
+
 // Streaming half-sweep: one chunk per thread; one launch covers every
 // replica of every realization listed in the block map (entry: realization,
 // (replica << 16) | block within the replica), or, for one realization,
@@ -802,24 +919,23 @@ __global__ __launch_bounds__(256) void sweep_generic(Lattice lat, FastDiv by_row
 // workgroup holds one replica's spins in LDS for `nsweep` whole sweeps and
 // writes the energy partial of the final state, as sweep_resident does for
 // powers of two.
-template <int KIND>
-__global__ __launch_bounds__(1024) void sweep_generic_resident(Lattice lat, FastDiv by_row, FastDiv by_l, int nsweep,
+template <int KIND, bool STEP>
+__global__ __launch_bounds__(1024) void sweep_generic_resident(Lattice lat, StepIn in, FastDiv by_row, FastDiv by_l, int nsweep,
                                                                 int energy) {
     extern __shared__ uint4 lds_raw[];
     __shared__ __align__(16) uint32_t sthr[32];
     uint8_t *sp = (uint8_t *)lds_raw;                  // [2][half]
     uint32_t *lds1 = (uint32_t *)lds_raw;
     const uint32_t r = blockIdx.x, half = (uint32_t)lat.half, words = (uint32_t)lat.N >> 2;
-    const int slot = gptr(lat.r2t)[r];
     // N is a multiple of 8: whole dwords
     GAS uint32_t *home = (GAS uint32_t *)(gptr(lat.spins) + (size_t)r * lat.N);
     for (uint32_t q = threadIdx.x; q < words; q += blockDim.x) lds1[q] = home[q];
-    if (KIND == 0 && threadIdx.x < 32u) sthr[threadIdx.x] = gptr(lat.thr)[slot * 32 + threadIdx.x];
-    const float a = KIND == 1 ? -2.0f * 1.44269504088896341f * gptr(lat.betaf)[slot] : 0.0f;
-    const uint32_t t0 = (uint32_t)gptr(lat.ctrs)[0];
+    stage_factor<KIND, STEP>(lat, in, r, true, sthr);
+    const uint32_t t0 = in.r2t ? in.t0 : (uint32_t)gptr(lat.ctrs)[0];
     GAS const uint8_t *fbits = gptr(lat.fbits);
     GAS const float *fhf = gptr(lat.fhf), *fraw = gptr(lat.fraw);
     __syncthreads();
+    const float a = KIND == 1 ? __uint_as_float(sthr[0]) : 0.0f;
     const uint32_t never = KIND == 0 ? __builtin_amdgcn_readfirstlane(sthr[31]) : 0u;
     for (int sw = 0; sw < nsweep; ++sw) {
         for (uint32_t col = 0; col < 2; ++col) {
@@ -849,7 +965,7 @@ __global__ __launch_bounds__(1024) void sweep_generic_resident(Lattice lat, Fast
             U[0] = site_counts(s0, j0, W[0], 1u, (uint32_t)lat.L, by_row, by_l);
             chunk_energy<KIND, 1>(lat, S1, W, U, F1, fbits, fraw + half, fraw, j0, ksum, upsum, eqsum, fsum);
         }
-        block_partial<KIND>(gptr(lat.part) + (size_t)r * 3, 4 * n, ksum, upsum, eqsum, fsum);
+        block_partial<KIND>(gptr(in.r2t ? in.part_out : lat.part) + (size_t)r * 3, 4 * n, ksum, upsum, eqsum, fsum);
     }
     for (uint32_t q = threadIdx.x; q < words; q += blockDim.x) home[q] = lds1[q];
 }
@@ -924,8 +1040,8 @@ __device__ __forceinline__ uint32_t plane_counts(const uint8_t *oth, const uint8
 // half-sweep launches (resident form at L = 24): L = 24, R = 32 3.3 and 3.9;
 // L = 40, R = 32 6.0 and 8.4, R = 256 13.2 and 23.8; L = 48, R = 32 8.6 and
 // 9.2; L = 52, R = 64 15.6 and 35.
-template <int KIND, bool ROWS, bool WHOLE>
-__global__ __launch_bounds__(1024) void sweep_box(Lattice lat, FastDiv by_row, FastDiv by_plane, FastDiv by_slab,
+template <int KIND, bool ROWS, bool WHOLE, bool STEP>
+__global__ __launch_bounds__(1024) void sweep_box(Lattice lat, StepIn in, FastDiv by_row, FastDiv by_plane, FastDiv by_slab,
                                                    const uint8_t *__restrict__ src, uint8_t *__restrict__ dst, int np_,
                                                    int nsweep, int toff, int energy) {
     extern __shared__ uint4 lds_raw[];
@@ -938,8 +1054,7 @@ __global__ __launch_bounds__(1024) void sweep_box(Lattice lat, FastDiv by_row, F
     const uint32_t np = min((uint32_t)np_, L - z0);
     const uint32_t H = WHOLE ? 0u : 2u * (uint32_t)nsweep, P = np + 2u * H;
     GAS const uint8_t *rsrc = gptr(src) + (size_t)r * lat.N;
-    const int slot = gptr(lat.r2t)[r];
-    const uint32_t t0 = (uint32_t)(gptr(lat.ctrs)[0] + (uint64_t)toff);
+    const uint32_t t0 = (in.r2t ? in.t0 : (uint32_t)gptr(lat.ctrs)[0]) + (uint32_t)toff;
     GAS const uint8_t *fbits = gptr(lat.fbits);
     GAS const float *fhf = gptr(lat.fhf), *fraw = gptr(lat.fraw);
     // plane b of the box is plane z0 - H + b of the lattice (H <= L)
@@ -958,9 +1073,9 @@ __global__ __launch_bounds__(1024) void sweep_box(Lattice lat, FastDiv by_row, F
         for (uint32_t c = 0; c < 2; ++c)
             *(uint32_t *)(box + (2u * b + c) * plane + place.d) = *(GAS const uint32_t *)(rsrc + c * half + at);
     }
-    if (KIND == 0 && threadIdx.x < 32u) sthr[threadIdx.x] = gptr(lat.thr)[slot * 32 + threadIdx.x];
-    const float a = KIND == 1 ? -2.0f * 1.44269504088896341f * gptr(lat.betaf)[slot] : 0.0f;
+    stage_factor<KIND, STEP>(lat, in, r, sl == 0u, sthr);
     __syncthreads();
+    const float a = KIND == 1 ? __uint_as_float(sthr[0]) : 0.0f;
     const uint32_t never = KIND == 0 ? __builtin_amdgcn_readfirstlane(sthr[31]) : 0u;
     for (uint32_t st = 0; st < 2u * (uint32_t)nsweep; ++st) {
         const uint32_t c = st & 1u, c1 = 2u * (t0 + (st >> 1)) + c;
@@ -997,7 +1112,8 @@ __global__ __launch_bounds__(1024) void sweep_box(Lattice lat, FastDiv by_row, F
             if (KIND == 0) load_words<1>(fbits + half, j0, F1);
             chunk_energy<KIND, 1>(lat, S1, W, U, F1, fbits, fraw + half, fraw, j0, ksum, upsum, eqsum, fsum);
         }
-        block_partial<KIND>(gptr(lat.part) + ((size_t)sl * lat.pstride + r) * 3, 4 * cnt, ksum, upsum, eqsum, fsum);
+        block_partial<KIND>(gptr(in.r2t ? in.part_out : lat.part) + ((size_t)sl * lat.pstride + r) * 3, 4 * cnt, ksum, upsum,
+                            eqsum, fsum);
     }
     GAS uint8_t *rdst = gptr(dst) + (size_t)r * lat.N;
     for (uint32_t k = pg; k < np; k += G) {
@@ -1013,9 +1129,9 @@ __global__ __launch_bounds__(1024) void sweep_box(Lattice lat, FastDiv by_row, F
 // between half-sweeps), then, if asked, the energy partial of the final
 // state, and writes the spins back.  Fields stay in global memory (shared
 // by every replica, so they live in L2).
-template <int KIND, int NW, bool BATCH, bool ONE>
+template <int KIND, int NW, bool BATCH, bool ONE, bool STEP>
 __global__ __launch_bounds__(1024) void sweep_resident(Lattice lat0, const Lattice *__restrict__ lats,
-                                                        const uint2 *__restrict__ map, int nsweep,
+                                                        const uint2 *__restrict__ map, StepIn in, int nsweep,
                                                         int energy) {
     extern __shared__ uint4 lds_raw[];
     __shared__ __align__(16) uint32_t sthr[32];   // +-1 thresholds or the continuous-field table
@@ -1024,14 +1140,12 @@ __global__ __launch_bounds__(1024) void sweep_resident(Lattice lat0, const Latti
     const Lattice &lat = BATCH ? lats[map[blockIdx.x].x >> 16] : lat0;
     const uint32_t r = BATCH ? (map[blockIdx.x].x & 0xFFFFu) : blockIdx.x;
     const uint32_t N = (uint32_t)lat.N, half = (uint32_t)lat.half;
-    const int slot = gptr(lat.r2t)[r];
     GAS const u32x4 *src = (GAS const u32x4 *)(gptr(lat.spins) + (size_t)r * N);
     u32x4 *lds4 = (u32x4 *)lds_raw;
     for (uint32_t q = threadIdx.x; q < N / 16u; q += blockDim.x) lds4[q] = src[q];
-    if (KIND == 0 && threadIdx.x < 32) sthr[threadIdx.x] = gptr(lat.thr)[slot * 32 + threadIdx.x];
-    const float beta = KIND == 1 ? gptr(lat.betaf)[slot] : 0.0f;
-    if (KIND == 1) cont_table_fill(sthr, beta, lat.Jf);
-    const uint32_t t0 = (uint32_t)gptr(lat.ctrs)[0];
+    stage_table<KIND, STEP>(lat, in, r, true, sthr);
+    const float beta = 0.0f;                           // the table holds what depends on it
+    const uint32_t t0 = in.r2t ? in.t0 : (uint32_t)gptr(lat.ctrs)[0];
     GAS const uint8_t *fbits = gptr(lat.fbits);
     GAS const float *fhf = gptr(lat.fhf), *fraw = gptr(lat.fraw);
     const uint32_t nchunk = half / (4u * NW);
@@ -1108,7 +1222,7 @@ __global__ __launch_bounds__(1024) void sweep_resident(Lattice lat0, const Latti
         // every thread covered 4*NW sites per chunk it took; nsite per thread
         // differs, so fold the affine offsets into the total instead
         const int nch = (int)((nchunk > threadIdx.x) ? (nchunk - 1 - threadIdx.x) / blockDim.x + 1 : 0);
-        block_partial<KIND>(gptr(lat.part) + (size_t)r * 3, 4 * NW * nch, ksum, upsum, eqsum, fsum);
+        block_partial<KIND>(gptr(in.r2t ? in.part_out : lat.part) + (size_t)r * 3, 4 * NW * nch, ksum, upsum, eqsum, fsum);
     }
     GAS u32x4 *dst = (GAS u32x4 *)(gptr(lat.spins) + (size_t)r * N);
     for (uint32_t q = threadIdx.x; q < N / 16u; q += blockDim.x) dst[q] = lds4[q];
@@ -1135,8 +1249,8 @@ __global__ __launch_bounds__(1024) void sweep_resident(Lattice lat0, const Latti
 // L * L / (8 SW) items: at L = 32 a wave's positions share one plane, so
 // the test is uniform per wave.
 // ---------------------------------------------------------------------
-template <int KIND, int NP>
-__global__ __launch_bounds__(1024) void sweep_slabs(Lattice lat, const uint8_t *__restrict__ src,
+template <int KIND, int NP, bool STEP>
+__global__ __launch_bounds__(1024) void sweep_slabs(Lattice lat, StepIn in, const uint8_t *__restrict__ src,
                                                      uint8_t *__restrict__ dst, int S, int nsweep, int toff,
                                                      int energy) {
     constexpr int SW = 2;
@@ -1156,9 +1270,8 @@ __global__ __launch_bounds__(1024) void sweep_slabs(Lattice lat, const uint8_t *
     const uint32_t r = blockIdx.x / (uint32_t)S, sl = blockIdx.x % (uint32_t)S;
     const uint32_t z0 = sl * slab;
     GAS const uint8_t *rsrc = gptr(src) + (size_t)r * lat.N;
-    const int slot = gptr(lat.r2t)[r];
-    const float beta = KIND == 1 ? gptr(lat.betaf)[slot] : 0.0f;
-    const uint32_t t0 = (uint32_t)(gptr(lat.ctrs)[0] + (uint64_t)toff);
+    const float beta = 0.0f;                               // the table holds what depends on it
+    const uint32_t t0 = (in.r2t ? in.t0 : (uint32_t)gptr(lat.ctrs)[0]) + (uint32_t)toff;
     GAS const uint8_t *fbits = gptr(lat.fbits);
     GAS const float *fhf = gptr(lat.fhf), *fraw = gptr(lat.fraw);
     // the positions of this thread and their fields (issued first, so the
@@ -1197,8 +1310,7 @@ __global__ __launch_bounds__(1024) void sweep_slabs(Lattice lat, const uint8_t *
         const uint32_t zg = (z0 + L - H + b) & (L - 1u);
         ((u32x4 *)box)[e] = *(GAS const u32x4 *)(rsrc + (size_t)c * half + (size_t)zg * plane + 16u * q);
     }
-    if (KIND == 0 && threadIdx.x < 32u) sthr[threadIdx.x] = gptr(lat.thr)[slot * 32 + threadIdx.x];
-    if (KIND == 1) cont_table_fill(sthr, beta, lat.Jf);
+    stage_table<KIND, STEP>(lat, in, r, sl == 0u, sthr);
     const uint32_t *bw = (const uint32_t *)box;
     const uint32_t ppw = plane >> 2;                       // dwords per colour-plane
     __syncthreads();
@@ -1270,8 +1382,8 @@ __global__ __launch_bounds__(1024) void sweep_slabs(Lattice lat, const uint8_t *
             if (KIND == 0) load_words<SW>(fbits + half, j0, F1);
             chunk_energy<KIND, SW>(lat, S1, a.W, U, F1, fbits, fraw + half, fraw, j0, ksum, upsum, eqsum, fsum);
         }
-        block_partial<KIND>(gptr(lat.part) + ((size_t)sl * lat.pstride + r) * 3, 4 * SW * nch, ksum, upsum, eqsum,
-                            fsum);
+        block_partial<KIND>(gptr(in.r2t ? in.part_out : lat.part) + ((size_t)sl * lat.pstride + r) * 3, 4 * SW * nch, ksum,
+                            upsum, eqsum, fsum);
     }
     // the slab's planes, both colours
     GAS uint8_t *rdst = gptr(dst) + (size_t)r * lat.N;
@@ -1935,15 +2047,17 @@ __global__ __launch_bounds__(256) void energy_bits(Lattice lat) {
     block_partial<KIND>(gptr(lat.part) + ((size_t)blockIdx.x * lat.pstride + r) * 3, 32 * n, ksum, upsum, eqsum, fsum);
 }
 
-__device__ __forceinline__ double energy_of(const Lattice &lat, double B, double F) {
-    return -(lat.J * B) - (lat.h * F);
-}
-
 // ---------------------------------------------------------------------
 // Exchange step k (Eq. 2): pairs (p, p+1) with p = k mod 2; temperatures
 // move through t2r / r2t (Sec. 3.3).  One workgroup of kExchangeThreads.
 // ---------------------------------------------------------------------
-constexpr int kExchangeThreads = 1024;
+// The ranges of block partials replica_totals adds: G ranges of `per` blocks.
+__host__ __device__ inline void partial_ranges(int R, int nblk, int *groups, int *per) {
+    int G = 1;
+    while (2 * G <= nblk && 2 * G <= 64 && (long long)R * 2 * G <= kExchangeThreads) G *= 2;
+    *groups = G;
+    *per = (nblk + G - 1) / G;
+}
 
 // Energy and magnetisation of every replica from its partials (B, F, M per
 // block, block-major).  Thread (g, r) sums blocks [g per, min((g+1) per,
@@ -1978,13 +2092,13 @@ __device__ __forceinline__ void sum_range(GAS const double *pp, size_t qstride, 
     }
 }
 
-__device__ __forceinline__ void replica_totals(const Lattice &lat, const Readout &out = Readout{},
+__device__ __forceinline__ void replica_totals(const Lattice &lat, const double *part, const Readout &out = Readout{},
                                                double *sE = nullptr, double *sM = nullptr) {
     __shared__ double red[kExchangeThreads * 3];
     const int R = lat.R, nblk = lat.nblk;
-    int G = 1;
-    while (2 * G <= nblk && 2 * G <= 64 && (long long)R * 2 * G <= kExchangeThreads) G *= 2;
-    const int tile = kExchangeThreads / G, per = (nblk + G - 1) / G;
+    int G, per;
+    partial_ranges(R, nblk, &G, &per);
+    const int tile = kExchangeThreads / G;
     const int g = (int)threadIdx.x / tile, rl = (int)threadIdx.x % tile;
     const int q_end = min(per, nblk - g * per);   // blocks in this thread's range (may be <= 0)
     const size_t qstride = (size_t)lat.pstride * 3;
@@ -1992,7 +2106,7 @@ __device__ __forceinline__ void replica_totals(const Lattice &lat, const Readout
         const int r = r0 + rl;
         double b = 0.0, f = 0.0, m = 0.0;
         if (r < R) {
-            GAS const double *pp = gptr(lat.part) + ((size_t)g * per * lat.pstride + r) * 3;
+            GAS const double *pp = gptr(part) + ((size_t)g * per * lat.pstride + r) * 3;
             if (per == 1)       // the batch width follows the range (uniform per block)
                 sum_range<1>(pp, qstride, q_end, b, f, m);
             else if (per == 2)
@@ -2038,16 +2152,7 @@ __device__ __forceinline__ void replica_totals(const Lattice &lat, const Readout
 // Totals per replica id for the observables calls (same reduction as the
 // exchange step, so both give the same bits).
 __global__ __launch_bounds__(kExchangeThreads) void reduce_kernel(Lattice lat, Readout out) {
-    replica_totals(lat, out);
-}
-
-// The decision for pair (p, p+1) of exchange step k: Philox word pair ->
-// a uniform double in [0, 1) with 53 random bits, accepted if Delta >= 0 or
-// u < e^Delta.
-__device__ __forceinline__ bool exchange_accept(const Lattice &lat, int p, uint64_t k, double delta) {
-    const Words w = philox10((uint32_t)p, (uint32_t)k, 0u, (kTagExch << 28) | lat.rho, lat.key0, lat.key1);
-    const double u53 = ((double)(w.w0 >> 11) * 4294967296.0 + (double)w.w1) * 0x1p-53;
-    return delta >= 0.0 || u53 < exp(delta);
+    replica_totals(lat, lat.part, out);
 }
 
 // One exchange step per workgroup (one realization each).  Up to
@@ -2056,18 +2161,19 @@ __device__ __forceinline__ bool exchange_accept(const Lattice &lat, int p, uint6
 // loaded together with the energy partials, so the whole step costs about
 // two memory round trips; more replicas take the same steps through global
 // memory.
-__global__ __launch_bounds__(kExchangeThreads) void exchange_kernel(const Lattice *__restrict__ lats, int tadv) {
+__global__ __launch_bounds__(kExchangeThreads) void exchange_kernel(const Lattice *__restrict__ lats, int tadv, StepIn in) {
     __shared__ double sE[kExchangeThreads], sM[kExchangeThreads];
     __shared__ int32_t st2r[kExchangeThreads];
     const Lattice &lat = lats[blockIdx.x];
-    const uint64_t k = lat.ctrs[1];
+    const bool pending = in.part != nullptr;      // then R <= kExchangeThreads
+    const uint64_t k = pending ? (uint64_t)in.k : lat.ctrs[1];
     const int R = lat.R, t = (int)threadIdx.x;
     if (R <= kExchangeThreads) {
         // inputs that do not depend on the energies, fetched first
         const bool mine = t < R;
         const int tc = mine ? t : 0;
         // (global-typed loads: flat ones would also hold up the scalar waits)
-        const int32_t my_t2r = gptr(lat.t2r)[tc];
+        const int32_t my_t2r = gptr(pending ? in.t2r : (const int32_t *)lat.t2r)[tc];
         GAS const double *beta = gptr(lat.beta);
         const double my_beta = beta[tc], my_beta1 = beta[min(tc + 1, R - 1)];
         const bool pair = t + 1 < R && (t & 1) == (int)(k & 1);
@@ -2077,7 +2183,7 @@ __global__ __launch_bounds__(kExchangeThreads) void exchange_kernel(const Lattic
         GAS const double *orow = gptr(lat.obs) + 6 * (size_t)tc;
 #pragma unroll
         for (int q = 0; q < 6; ++q) o[q] = orow[q];
-        replica_totals(lat, Readout{}, sE, sM);
+        replica_totals(lat, pending ? in.part : lat.part, Readout{}, sE, sM);
         if (mine) st2r[t] = my_t2r;
         __syncthreads();
         // pairs (p, p+1) with p = k mod 2: thread p decides its pair; the
@@ -2100,6 +2206,10 @@ __global__ __launch_bounds__(kExchangeThreads) void exchange_kernel(const Lattic
         // one measurement per exchange step (Sec. 7), by temperature slot
         if (mine) {
             const int a = st2r[t];
+            if (pending) {                        // the permutation may come from its other copy
+                lat.t2r[t] = a;
+                lat.r2t[a] = t;
+            }
             const double e = sE[a], m = sM[a], m2 = m * m;
             double *op = lat.obs + 6 * (size_t)t;
             op[0] = o[0] + 1.0;
@@ -2110,7 +2220,7 @@ __global__ __launch_bounds__(kExchangeThreads) void exchange_kernel(const Lattic
             op[5] = o[5] + m2 * m2;
         }
     } else {
-        replica_totals(lat);
+        replica_totals(lat, lat.part);
         __syncthreads();
         for (int p = (int)(k & 1) + 2 * t; p + 1 < R; p += 2 * kExchangeThreads) {
             const int a = lat.t2r[p], b = lat.t2r[p + 1];
@@ -2269,7 +2379,7 @@ static int device_cus() {
 }
 
 template <int KIND, int NW, bool BATCH>
-static void launch_res_nw(const Launch &ln, const Lattice &lat0, int nsweep, int energy, hipStream_t s) {
+static void launch_res_nw(const Launch &ln, const Lattice &lat0, const StepIn &in, int nsweep, int energy, hipStream_t s) {
     const size_t lds = (size_t)ln.L * ln.L * ln.L;
     const dim3 grid(ln.nblocks), block(ln.wg);
     // one chunk per thread and colour: the register-field form, unless its
@@ -2281,29 +2391,31 @@ static void launch_res_nw(const Launch &ln, const Lattice &lat0, int nsweep, int
         // L of NW = 1; index the cache by L
         static std::atomic<int> occ[2][6] = {{-1, -1, -1, -1, -1, -1}, {-1, -1, -1, -1, -1, -1}};
         const int li = ln.L == 8 ? 0 : (ln.L == 16 ? 1 : (ln.L == 32 ? 2 : 3));
-        const int b1 = resident_blocks_per_cu(occ[1][li], (const void *)sweep_resident<KIND, NW, BATCH, true>,
+        const int b1 = resident_blocks_per_cu(occ[1][li], (const void *)sweep_resident<KIND, NW, BATCH, true, false>,
                                               ln.wg, lds);
-        const int b0 = resident_blocks_per_cu(occ[0][li], (const void *)sweep_resident<KIND, NW, BATCH, false>,
+        const int b0 = resident_blocks_per_cu(occ[0][li], (const void *)sweep_resident<KIND, NW, BATCH, false, false>,
                                               ln.wg, lds);
         const long long cus = device_cus();
         if (b1 < b0 && (long long)ln.nblocks > cus * b1) one = false;
     }
+    const bool step = !BATCH && in.part != nullptr;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, lds, s, lat0, ln.lats, ln.map, in, nsweep, energy);
+    };
     if (one)
-        hipLaunchKernelGGL((sweep_resident<KIND, NW, BATCH, true>), grid, block, lds, s, lat0, ln.lats, ln.map,
-                           nsweep, energy);
+        step ? go(sweep_resident<KIND, NW, BATCH, true, !BATCH>) : go(sweep_resident<KIND, NW, BATCH, true, false>);
     else
-        hipLaunchKernelGGL((sweep_resident<KIND, NW, BATCH, false>), grid, block, lds, s, lat0, ln.lats, ln.map,
-                           nsweep, energy);
+        step ? go(sweep_resident<KIND, NW, BATCH, false, !BATCH>) : go(sweep_resident<KIND, NW, BATCH, false, false>);
 }
 
 template <int KIND, bool BATCH>
-static void launch_res(const Launch &ln, const Lattice &lat0, int nsweep, int energy, hipStream_t s) {
+static void launch_res(const Launch &ln, const Lattice &lat0, const StepIn &in, int nsweep, int energy, hipStream_t s) {
     if (ln.nw == 4)
-        launch_res_nw<KIND, 4, BATCH>(ln, lat0, nsweep, energy, s);
+        launch_res_nw<KIND, 4, BATCH>(ln, lat0, in, nsweep, energy, s);
     else if (ln.nw == 2)
-        launch_res_nw<KIND, 2, BATCH>(ln, lat0, nsweep, energy, s);
+        launch_res_nw<KIND, 2, BATCH>(ln, lat0, in, nsweep, energy, s);
     else
-        launch_res_nw<KIND, 1, BATCH>(ln, lat0, nsweep, energy, s);
+        launch_res_nw<KIND, 1, BATCH>(ln, lat0, in, nsweep, energy, s);
 }
 
 hipError_t launch_stream_sweep(const Launch &ln, int colour, int toff, int energy, hipStream_t s) {
@@ -2321,27 +2433,30 @@ hipError_t launch_stream_sweep(const Launch &ln, int colour, int toff, int energ
     return hipGetLastError();
 }
 
-hipError_t launch_resident(const Launch &ln, int nsweep, int energy, hipStream_t s) {
+hipError_t launch_resident(const Launch &ln, const StepIn &in, int nsweep, int energy, hipStream_t s) {
     if (ln.nblocks == 0) return hipSuccess;
     const bool b = ln.single == nullptr;
     const Lattice lat0 = b ? Lattice{} : *ln.single;
-    if (ln.kind == 0) b ? launch_res<0, true>(ln, lat0, nsweep, energy, s) : launch_res<0, false>(ln, lat0, nsweep, energy, s);
-    else b ? launch_res<1, true>(ln, lat0, nsweep, energy, s) : launch_res<1, false>(ln, lat0, nsweep, energy, s);
+    if (ln.kind == 0) b ? launch_res<0, true>(ln, lat0, in, nsweep, energy, s) : launch_res<0, false>(ln, lat0, in, nsweep, energy, s);
+    else b ? launch_res<1, true>(ln, lat0, in, nsweep, energy, s) : launch_res<1, false>(ln, lat0, in, nsweep, energy, s);
     return hipGetLastError();
 }
 
 bool generic_resident(int L) { return L <= kGenericResidentMaxL && (L % 4 == 2 || L == 4); }
 
 template <int KIND>
-static void launch_generic_kind(const Lattice &lat, int colour, int toff, int nsweep, int energy, hipStream_t s) {
+static void launch_generic_kind(const Lattice &lat, const StepIn &in, int colour, int toff, int nsweep, int energy,
+                                hipStream_t s) {
     const FastDiv by_row = fast_div((uint32_t)lat.L / 2u), by_l = fast_div((uint32_t)lat.L);
     const int G = lat.half >> 2;
     const unsigned nb = (unsigned)((G + 255) / 256);
-    if (nsweep > 0)
-        hipLaunchKernelGGL((sweep_generic_resident<KIND>), dim3((unsigned)lat.R),
-                           dim3((unsigned)std::min(1024, (G + 63) / 64 * 64)), (size_t)lat.N, s, lat, by_row, by_l, nsweep,
-                           energy);
-    else if (lat.L % 8 == 0)
+    if (nsweep > 0) {
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)lat.R), dim3((unsigned)std::min(1024, (G + 63) / 64 * 64)), (size_t)lat.N,
+                               s, lat, in, by_row, by_l, nsweep, energy);
+        };
+        in.part ? go(sweep_generic_resident<KIND, true>) : go(sweep_generic_resident<KIND, false>);
+    } else if (lat.L % 8 == 0)
         hipLaunchKernelGGL((sweep_generic<KIND, true>), dim3(nb * (unsigned)lat.R), dim3(256), 0, s, lat, by_row, by_l,
                            fast_div(nb), colour, toff);
     else
@@ -2349,21 +2464,22 @@ static void launch_generic_kind(const Lattice &lat, int colour, int toff, int ns
                            fast_div(nb), colour, toff);
 }
 
-static hipError_t launch_generic(const Lattice &lat, int colour, int toff, int nsweep, int energy, hipStream_t s) {
+static hipError_t launch_generic(const Lattice &lat, const StepIn &in, int colour, int toff, int nsweep, int energy,
+                                 hipStream_t s) {
     if (lat.kind == 0)
-        launch_generic_kind<0>(lat, colour, toff, nsweep, energy, s);
+        launch_generic_kind<0>(lat, in, colour, toff, nsweep, energy, s);
     else
-        launch_generic_kind<1>(lat, colour, toff, nsweep, energy, s);
+        launch_generic_kind<1>(lat, in, colour, toff, nsweep, energy, s);
     return hipGetLastError();
 }
 
 hipError_t launch_generic_sweep(const Lattice &lat, int colour, int toff, hipStream_t s) {
-    return launch_generic(lat, colour, toff, 0, 0, s);
+    return launch_generic(lat, StepIn{}, colour, toff, 0, 0, s);
 }
 
-hipError_t launch_generic_resident(const Lattice &lat, int nsweep, int energy, hipStream_t s) {
+hipError_t launch_generic_resident(const Lattice &lat, const StepIn &in, int nsweep, int energy, hipStream_t s) {
     if (nsweep < 1) return hipSuccess;
-    return launch_generic(lat, 0, 0, nsweep, energy, s);
+    return launch_generic(lat, in, 0, 0, nsweep, energy, s);
 }
 
 size_t box_lds_bytes(int L, int planes) { return (size_t)planes * (size_t)L * (size_t)L; }   // both colours
@@ -2414,23 +2530,25 @@ BoxPlan box_plan(int L, int R) {
 }
 
 template <int KIND, bool ROWS>
-static void launch_box_form(const Lattice &lat, const uint8_t *src, uint8_t *dst, int np, int nsweep, int toff, int energy,
-                            hipStream_t s) {
+static void launch_box_form(const Lattice &lat, const StepIn &in, const uint8_t *src, uint8_t *dst, int np, int nsweep,
+                            int toff, int energy, hipStream_t s) {
     const uint32_t L = (uint32_t)lat.L, slabs = (L + (uint32_t)np - 1u) / (uint32_t)np, bpp = L * L / 8u;
     const bool whole = slabs == 1u;
     const uint32_t active = whole ? L : (uint32_t)(np + 4 * nsweep - 2);     // planes of the largest half-sweep
     const dim3 grid((unsigned)lat.R * slabs), block(bpp * std::min(1024u / bpp, active));
     const FastDiv by_row = fast_div(L / 2u), by_plane = fast_div(bpp), by_slab = fast_div(slabs);
+    const size_t lds = box_lds_bytes(lat.L, whole ? lat.L : np + 4 * nsweep);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, lds, s, lat, in, by_row, by_plane, by_slab, src, dst, np, nsweep, toff, energy);
+    };
     if (whole)
-        hipLaunchKernelGGL((sweep_box<KIND, ROWS, true>), grid, block, box_lds_bytes(lat.L, lat.L), s, lat, by_row, by_plane,
-                           by_slab, src, dst, np, nsweep, toff, energy);
+        in.part ? go(sweep_box<KIND, ROWS, true, true>) : go(sweep_box<KIND, ROWS, true, false>);
     else
-        hipLaunchKernelGGL((sweep_box<KIND, ROWS, false>), grid, block, box_lds_bytes(lat.L, np + 4 * nsweep), s, lat,
-                           by_row, by_plane, by_slab, src, dst, np, nsweep, toff, energy);
+        in.part ? go(sweep_box<KIND, ROWS, false, true>) : go(sweep_box<KIND, ROWS, false, false>);
 }
 
-hipError_t launch_box(const Lattice &lat, const uint8_t *src, uint8_t *dst, const BoxPlan &plan, int nsweep, int toff,
-                      int energy, hipStream_t s) {
+hipError_t launch_box(const Lattice &lat, const StepIn &in, const uint8_t *src, uint8_t *dst, const BoxPlan &plan,
+                      int nsweep, int toff, int energy, hipStream_t s) {
     const int np = plan.planes;
     const bool whole = np >= lat.L;
     if (np < 1 || nsweep < 1 || lat.L % 4 != 0 || lat.L > kBoxMaxL) return hipErrorInvalidValue;
@@ -2438,11 +2556,11 @@ hipError_t launch_box(const Lattice &lat, const uint8_t *src, uint8_t *dst, cons
     if (box_lds_bytes(lat.L, whole ? lat.L : np + 4 * nsweep) > 65536) return hipErrorInvalidValue;
     const bool rows = lat.L % 8 == 0;
     if (lat.kind == 0)
-        rows ? launch_box_form<0, true>(lat, src, dst, np, nsweep, toff, energy, s)
-             : launch_box_form<0, false>(lat, src, dst, np, nsweep, toff, energy, s);
+        rows ? launch_box_form<0, true>(lat, in, src, dst, np, nsweep, toff, energy, s)
+             : launch_box_form<0, false>(lat, in, src, dst, np, nsweep, toff, energy, s);
     else
-        rows ? launch_box_form<1, true>(lat, src, dst, np, nsweep, toff, energy, s)
-             : launch_box_form<1, false>(lat, src, dst, np, nsweep, toff, energy, s);
+        rows ? launch_box_form<1, true>(lat, in, src, dst, np, nsweep, toff, energy, s)
+             : launch_box_form<1, false>(lat, in, src, dst, np, nsweep, toff, energy, s);
     return hipGetLastError();
 }
 
@@ -2459,24 +2577,27 @@ int slab_positions_per_thread(int L, int mode, int nslab, int wg) {
 }
 
 template <int KIND>
-static void launch_slab_kind(const Lattice &lat, const uint8_t *src, uint8_t *dst, int np, int nslab, int wg,
+static void launch_slab_kind(const Lattice &lat, const StepIn &in, const uint8_t *src, uint8_t *dst, int np, int nslab, int wg,
                              size_t lds, int nsweep, int toff, int energy, hipStream_t s) {
     const dim3 grid((unsigned)(lat.R * nslab)), block((unsigned)wg);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, lds, s, lat, in, src, dst, nslab, nsweep, toff, energy);
+    };
     if (np == 1)
-        hipLaunchKernelGGL((sweep_slabs<KIND, 1>), grid, block, lds, s, lat, src, dst, nslab, nsweep, toff, energy);
+        in.part ? go(sweep_slabs<KIND, 1, true>) : go(sweep_slabs<KIND, 1, false>);
     else
-        hipLaunchKernelGGL((sweep_slabs<KIND, 2>), grid, block, lds, s, lat, src, dst, nslab, nsweep, toff, energy);
+        in.part ? go(sweep_slabs<KIND, 2, true>) : go(sweep_slabs<KIND, 2, false>);
 }
 
-hipError_t launch_slab_sweep(const Lattice &lat, const uint8_t *src, uint8_t *dst, int mode, int nslab, int wg,
-                             int nsweep, int toff, int energy, hipStream_t s) {
+hipError_t launch_slab_sweep(const Lattice &lat, const StepIn &in, const uint8_t *src, uint8_t *dst, int mode, int nslab,
+                             int wg, int nsweep, int toff, int energy, hipStream_t s) {
     const size_t lds = slab_lds_bytes(lat.L, mode, nslab);
     const int np = slab_positions_per_thread(lat.L, mode, nslab, wg);
     if (np < 1 || np > 2 || nsweep < 1 || nsweep > slab_sweeps_per_launch(mode)) return hipErrorInvalidValue;
     if (lat.kind == 0)
-        launch_slab_kind<0>(lat, src, dst, np, nslab, wg, lds, nsweep, toff, energy, s);
+        launch_slab_kind<0>(lat, in, src, dst, np, nslab, wg, lds, nsweep, toff, energy, s);
     else
-        launch_slab_kind<1>(lat, src, dst, np, nslab, wg, lds, nsweep, toff, energy, s);
+        launch_slab_kind<1>(lat, in, src, dst, np, nslab, wg, lds, nsweep, toff, energy, s);
     return hipGetLastError();
 }
 
@@ -2639,9 +2760,11 @@ hipError_t launch_fields_in(const Lattice &lat, size_t first, size_t count, cons
     return hipGetLastError();
 }
 
-hipError_t launch_exchange(const Lattice *lats, int n, int tadv, hipStream_t s) {
+void partial_groups(int R, int nblk, int *groups, int *per) { partial_ranges(R, nblk, groups, per); }
+
+hipError_t launch_exchange(const Lattice *lats, int n, int tadv, const StepIn &in, hipStream_t s) {
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(exchange_kernel, dim3(n), dim3(kExchangeThreads), 0, s, lats, tadv);
+    hipLaunchKernelGGL(exchange_kernel, dim3(n), dim3(kExchangeThreads), 0, s, lats, tadv, in);
     return hipGetLastError();
 }
 
