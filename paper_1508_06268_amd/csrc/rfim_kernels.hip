@@ -1521,11 +1521,13 @@ __device__ __forceinline__ uint32_t maj3(uint32_t a, uint32_t b, uint32_t c) {
 __host__ __device__ constexpr uint32_t bit_of_index(uint32_t i) { return 8u * (i & 3u) + (i >> 2); }
 
 // Exchange the bits of a at positions i + sh with the bits of b at
-// positions i, for the positions i that mask m selects.
+// positions i, for the positions i that mask m selects: two shifts and two
+// bit selects (table 0xD8: the third operand chooses the second over the
+// first); the three-XOR swap takes one more.
 __device__ __forceinline__ void swap_bit_groups(uint32_t &a, uint32_t &b, uint32_t sh, uint32_t m) {
-    const uint32_t t = ((a >> sh) ^ b) & m;
-    b ^= t;
-    a ^= t << sh;
+    const uint32_t x = a >> sh, y = b << sh;
+    a = __builtin_amdgcn_bitop3_b32(a, y, m << sh, 0xD8);
+    b = __builtin_amdgcn_bitop3_b32(b, x, m, 0xD8);
 }
 
 // Table offsets of all eight Philox blocks of a word at once.  Byte q of
@@ -1585,27 +1587,43 @@ __device__ __forceinline__ int bits_aligned(uint32_t U0, uint32_t U1, uint32_t U
 
 constexpr int kBitsThreads = 256;
 
-// Word i of a colour's bit array, addressed as a wave-uniform base plus a
+// A word of a colour's bit array, addressed as a wave-uniform base plus a
 // 32-bit byte offset (one vector register per load instead of a 64-bit
-// address; i < 2^30 at every L that bit storage takes).
-__device__ __forceinline__ uint32_t bits_word(GAS const uint32_t *base, uint32_t i) {
-    return *(GAS const uint32_t *)((GAS const char *)base + (i << 2));
+// address).
+__device__ __forceinline__ uint32_t bits_word(GAS const uint32_t *base, uint32_t byte) {
+    return *(GAS const uint32_t *)((GAS const char *)base + byte);
 }
 
-// The other colour's word W at word w of colour c's index space and the up
-// count of the six neighbours of w's 32 sites in three bit planes.
-__device__ __forceinline__ void bits_up_counts(const Lattice &lat, GAS const uint32_t *oth, uint32_t w, uint32_t c,
-                                               uint32_t &W, uint32_t &U0, uint32_t &U1, uint32_t &U2) {
-    const uint32_t L = (uint32_t)lat.L, l = (uint32_t)lat.log2L;
-    const uint32_t lrw = l - 6u, rw_ = 1u << lrw;
-    const uint32_t p = (c + (w >> lrw) + (w >> (lrw + l))) & 1u;
-    const uint32_t xm = rw_ - 1u, ym = (L - 1u) << lrw, zm = ym << l;
-    W = bits_word(oth, w);
-    const uint32_t Wn = bits_word(oth, ((w + 2u * p - 1u) & xm) | (w & ~xm));
-    const uint32_t Wyp = bits_word(oth, ((w + rw_) & ym) | (w & ~ym));
-    const uint32_t Wym = bits_word(oth, ((w - rw_) & ym) | (w & ~ym));
-    const uint32_t Wzp = bits_word(oth, ((w + (rw_ << l)) & zm) | (w & ~zm));
-    const uint32_t Wzm = bits_word(oth, ((w - (rw_ << l)) & zm) | (w & ~zm));
+// The words around word w of colour c's index space, as byte offsets.  The
+// offset 4 w = 4 ((z L + y) words-per-row + wr) has the bit fields of wr, y and
+// z side by side, so a neighbour's is a step inside one field, put back (the
+// step's carry or borrow out of the field masked off: periodic wrap).  x: the
+// word that holds index m - 1 (p = 0) or m + 1 (p = 1).
+struct BitsAround {
+    uint32_t own, x, yp, ym, zp, zm, p;
+};
+
+__device__ __forceinline__ BitsAround bits_around(const Lattice &lat, uint32_t w, uint32_t c) {
+    const uint32_t L = (uint32_t)lat.L, l = (uint32_t)lat.log2L, lrw = l - 6u;
+    const uint32_t y1 = 4u << lrw, z1 = y1 << l;
+    const uint32_t xf = y1 - 4u, yf = (L - 1u) << (lrw + 2u), zf = yf << l;
+    BitsAround a;
+    a.own = 4u * w;
+    a.p = (c + (w >> lrw) + (w >> (lrw + l))) & 1u;                   // (c + y + z) mod 2
+    a.x = ((a.own + 8u * a.p - 4u) & xf) | (a.own & ~xf);
+    a.yp = ((a.own + y1) & yf) | (a.own & ~yf);
+    a.ym = ((a.own - y1) & yf) | (a.own & ~yf);
+    a.zp = ((a.own + z1) & zf) | (a.own & ~zf);
+    a.zm = ((a.own - z1) & zf) | (a.own & ~zf);
+    return a;
+}
+
+// Up counts of a word's 32 sites in three bit planes.  The x neighbour, index
+// m - 1 or m + 1, in the interleaved order: a step of one index is a step of
+// one byte, with the carry between byte 3 and byte 0 one bit along, and the
+// end bit from the neighbouring word of the row (around the row).
+__device__ __forceinline__ void bits_planes(uint32_t p, uint32_t W, uint32_t Wn, uint32_t Wyp, uint32_t Wym, uint32_t Wzp,
+                                            uint32_t Wzm, uint32_t &U0, uint32_t &U1, uint32_t &U2) {
     const uint32_t Wx = p ? ((W >> 8) | ((W << 23) & 0x7F000000u) | (Wn << 31))
                           : ((W << 8) | ((W >> 23) & 0x000000FEu) | (Wn >> 31));
     const uint32_t s1 = xor3(W, Wx, Wyp), c1 = maj3(W, Wx, Wyp);
@@ -1666,6 +1684,14 @@ __host__ __device__ constexpr int bits_wg(int L) { return L == 64 ? 128 : 256; }
 // BATCH: the replicas of several realizations that share L and the field
 // kind, one map entry per replica (x = (realization << 16) | replica) and
 // 2^lbpr workgroups each; else replicas r0.. of lat0.
+// Bound by instruction issue: 496 VALU instructions per wavefront of 2048
+// +-1 attempts, of them 144 64-bit products (Gaussian 630), 514 (650) with
+// the neighbour words indexed by words and a three-XOR swap in the transpose.
+// A sweep then and now, production path: L = 64, R = 192, +-1 23.1 -> 22.4 us,
+// Gaussian 27.7 -> 25.7; L = 128, R = 64, +-1 54.0 -> 50.9.  Thresholds from
+// lane registers (ds_bpermute) instead of the LDS table save another 8 per
+// wavefront and were no faster, slower for few replicas (L = 64, R = 32: 10.9
+// against 9.2).
 template <int KIND, int ENERGY, bool BATCH>
 __global__ __launch_bounds__(kBitsThreads) void sweep_bits(Lattice lat0, const Lattice *__restrict__ lats,
                                                           const uint2 *__restrict__ map, int colour, int toff,
@@ -1680,26 +1706,16 @@ __global__ __launch_bounds__(kBitsThreads) void sweep_bits(Lattice lat0, const L
     const Lattice &lat = BATCH ? lats[e >> 16] : lat0;
     const uint32_t r = BATCH ? (e & 0xFFFFu) : (uint32_t)r0 + (blk >> lbpr);
     const uint32_t gb = blk & ((1u << lbpr) - 1u);
-    const uint32_t L = (uint32_t)lat.L, l = (uint32_t)lat.log2L;
     const uint32_t W1 = (uint32_t)lat.N >> 6;            // words per colour
-    const uint32_t lrw = l - 6u, rw_ = 1u << lrw;        // words per row
-    // w = (z L + y) rw_ + wr: the bit fields of wr, y and z side by side, so
-    // a neighbour's word is w stepped inside one field and put back (the
-    // step's carry or borrow out of the field masked off: periodic wrap)
     const uint32_t w = gb * blockDim.x + threadIdx.x;
     const uint32_t c = (uint32_t)colour;
-    const uint32_t p = (c + (w >> lrw) + (w >> (lrw + l))) & 1u;      // (c + y + z) mod 2
-    const uint32_t xm = rw_ - 1u, ym = (L - 1u) << lrw, zm = ym << l;
-    const uint32_t wx = ((w + 2u * p - 1u) & xm) | (w & ~xm);          // the word holding index m -+ 1
-    const uint32_t wyp = ((w + rw_) & ym) | (w & ~ym), wym = ((w - rw_) & ym) | (w & ~ym);
-    const uint32_t wzp = ((w + (rw_ << l)) & zm) | (w & ~zm), wzm = ((w - (rw_ << l)) & zm) | (w & ~zm);
+    const BitsAround at = bits_around(lat, w, c);
     GAS uint32_t *own = gptr(lat.bits) + ((size_t)r * 2u + c) * W1;
     GAS const uint32_t *oth = gptr(lat.bits) + ((size_t)r * 2u + (1u - c)) * W1;
-    const uint32_t S = bits_word(own, w);
-    const uint32_t W = bits_word(oth, w);
-    const uint32_t Wn = bits_word(oth, wx);
-    const uint32_t Wyp = bits_word(oth, wyp), Wym = bits_word(oth, wym);
-    const uint32_t Wzp = bits_word(oth, wzp), Wzm = bits_word(oth, wzm);
+    const uint32_t S = bits_word(own, at.own);
+    const uint32_t W = bits_word(oth, at.own), Wn = bits_word(oth, at.x);
+    const uint32_t Wyp = bits_word(oth, at.yp), Wym = bits_word(oth, at.ym);
+    const uint32_t Wzp = bits_word(oth, at.zp), Wzm = bits_word(oth, at.zm);
     uint32_t F = 0;
     f32x4 HF[8];
     if (KIND == 0) {
@@ -1723,17 +1739,8 @@ __global__ __launch_bounds__(kBitsThreads) void sweep_bits(Lattice lat0, const L
         cont_table_fill(sthr, beta, lat.Jf);
         __syncthreads();
     }
-    // the x neighbour, index m-1 (p = 0) or m+1 (p = 1), in the interleaved
-    // order: a step of one index is a step of one byte, with the carry
-    // between byte 3 and byte 0 one bit along, and the end bit from the
-    // neighbouring word of the row (around the row)
-    const uint32_t Wx = p ? ((W >> 8) | ((W << 23) & 0x7F000000u) | (Wn << 31))
-                          : ((W << 8) | ((W >> 23) & 0x000000FEu) | (Wn >> 31));
-    // up count of the six neighbours in three bit planes
-    const uint32_t s1 = xor3(W, Wx, Wyp), c1 = maj3(W, Wx, Wyp);
-    const uint32_t s2 = xor3(Wym, Wzp, Wzm), c2 = maj3(Wym, Wzp, Wzm);
-    const uint32_t U0 = s1 ^ s2, c3 = s1 & s2;
-    const uint32_t U1 = xor3(c1, c2, c3), U2 = maj3(c1, c2, c3);
+    uint32_t U0, U1, U2;
+    bits_planes(at.p, W, Wn, Wyp, Wym, Wzp, Wzm, U0, U1, U2);
     const uint32_t c1w = 2u * t + c, c3w = (kTagSweep << 28) | lat.rho;
     uint32_t Acls[8];
     class_offsets(U0, U1, U2, S, KIND == 0 ? F : 0u, Acls);
@@ -1745,7 +1752,7 @@ __global__ __launch_bounds__(kBitsThreads) void sweep_bits(Lattice lat0, const L
             ? word_flips<KIND, true>(sthr, never, Acls, HF, w, m0v, c1w, r, c3w, lat.key0, lat.key1)
             : word_flips<KIND, false>(sthr, never, Acls, HF, w, m0v, c1w, r, c3w, lat.key0, lat.key1);
     const uint32_t Snew = S ^ flips;
-    if (flips) *(GAS uint32_t *)((GAS char *)own + (w << 2)) = Snew;
+    if (flips) *(GAS uint32_t *)((GAS char *)own + at.own) = Snew;
     if (ENERGY) {
         // colour 1 of the last sweep before an exchange: the final state.
         // B counts each bond once through the colour-1 sites: sum of
@@ -2032,13 +2039,15 @@ __global__ __launch_bounds__(256) void energy_bits(Lattice lat) {
     int ksum = 0, upsum = 0, eqsum = 0, n = 0;
     double fsum = 0.0;
     for (uint32_t w = blockIdx.x * 256u + threadIdx.x; w < W1; w += 256u * gridDim.x, ++n) {
-        const uint32_t S = bits_word(b1, w);
-        uint32_t W, U0, U1, U2;
-        bits_up_counts(lat, b0, w, 1u, W, U0, U1, U2);
+        const BitsAround at = bits_around(lat, w, 1u);
+        const uint32_t S = bits_word(b1, at.own), W = bits_word(b0, at.own);
+        uint32_t U0, U1, U2;
+        bits_planes(at.p, W, bits_word(b0, at.x), bits_word(b0, at.yp), bits_word(b0, at.ym), bits_word(b0, at.zp),
+                    bits_word(b0, at.zm), U0, U1, U2);
         ksum += bits_aligned(U0, U1, U2, S);
         upsum += __popc(S) + __popc(W);
         if (KIND == 0) {
-            eqsum += __popc(~(S ^ bits_word(gptr(lat.fbw) + W1, w))) + __popc(~(W ^ bits_word(gptr(lat.fbw), w)));
+            eqsum += __popc(~(S ^ bits_word(gptr(lat.fbw) + W1, at.own))) + __popc(~(W ^ bits_word(gptr(lat.fbw), at.own)));
         } else {
             const uint32_t w0 = w & ~63u;
             fsum += bits_field_sum(gptr(lat.fraw) + lat.half, w0, S) + bits_field_sum(gptr(lat.fraw), w0, W);
