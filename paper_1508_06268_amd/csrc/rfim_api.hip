@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -660,26 +661,45 @@ struct Fetch {
     size_t bytes;
 };
 
+// Waits until the last launch on s has set its n words of `done`, which also
+// ends the wait when the stream does (a failed launch is reported there).
+// The words are polled for as long as a small readout takes; a longer wait is
+// for work before it, and left to the stream.
+int wait_done(hipStream_t s, const uint32_t *done, unsigned n) {
+    const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(50);
+    unsigned q = 0;
+    do {
+        for (int i = 0; i < 64 && q < n; ++i)
+            if (__atomic_load_n(done + q, __ATOMIC_ACQUIRE)) ++q;
+        if (q == n) return RFIM_OK;
+    } while (std::chrono::steady_clock::now() < until);
+    HIPCHK(hipStreamSynchronize(s));
+    return RFIM_OK;
+}
+
 int fetch(rfim *h, std::initializer_list<Fetch> parts) {
+    rfim_dev::CopyOut c;
     size_t off[rfim_dev::CopyOut::kMax] = {}, total = 0;
     int q = 0;
     for (const Fetch &f : parts) {
-        off[q++] = total;
+        off[q] = total;
+        c.words[q++] = (uint32_t)(f.bytes / 4);
         total += (f.bytes + 63) & ~(size_t)63;
     }
+    const unsigned nflags = rfim_dev::copy_out_flags(c);
     Pinned buf;
     int rc;
-    if ((rc = buf.get(total))) return rc;
-    rfim_dev::CopyOut c;
+    if ((rc = buf.get(total + nflags * sizeof(uint32_t)))) return rc;
+    c.done = (uint32_t *)buf.at(total);
+    std::memset(c.done, 0, nflags * sizeof(uint32_t));
     q = 0;
     for (const Fetch &f : parts) {
         c.src[q] = f.src;
         c.dst[q] = buf.at(off[q]);
-        c.words[q] = (uint32_t)(f.bytes / 4);
         ++q;
     }
     HIPCHK(rfim_dev::launch_copy_out(c, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
+    if ((rc = wait_done(h->stream, c.done, nflags))) return rc;
     q = 0;
     for (const Fetch &f : parts) std::memcpy(f.dst, buf.at(off[q++]), f.bytes);
     return RFIM_OK;
@@ -690,14 +710,15 @@ int download_perm(rfim *h, std::vector<int32_t> &t2r) {
     return fetch(h, {{t2r.data(), h->d_t2r, (size_t)h->R * 4}});
 }
 
-// Energies and magnetisations of the current state: the partials from the
-// spins, their totals straight into the caller's pinned block.
-int launch_components(rfim *h, const rfim_dev::Readout &out) {
-    Lattice lat = h->lattice();
-    lat.nblk = rfim_dev::energy_blocks(lat);
-    HIPCHK(rfim_dev::launch_energy(lat, h->stream));
-    HIPCHK(rfim_dev::launch_reduce(lat, out, h->stream));
-    return RFIM_OK;
+// Energies and magnetisations of the current state, straight into the
+// caller's pinned block, which has the flags at flags_at.
+int read_state(rfim *h, rfim_dev::Readout &out, const Pinned &buf, size_t flags_at) {
+    const Lattice lat = h->lattice();
+    const unsigned n = rfim_dev::readout_flags(lat);
+    out.done = (uint32_t *)buf.at(flags_at);
+    std::memset(out.done, 0, n * sizeof(uint32_t));
+    HIPCHK(rfim_dev::launch_readout(lat, out, h->stream));
+    return wait_done(h->stream, out.done, n);
 }
 
 // By temperature slot: energies and magnetisations, each if asked for.
@@ -705,12 +726,11 @@ int read_slots(rfim *h, double *E, int64_t *M) {
     const size_t bytes = (size_t)h->R * 8;
     Pinned buf;
     int rc;
-    if ((rc = buf.get(2 * bytes))) return rc;
+    if ((rc = buf.get(3 * bytes))) return rc;
     rfim_dev::Readout out;
     out.E_slot = E ? (double *)buf.at() : nullptr;
     out.M_slot = M ? (int64_t *)buf.at(bytes) : nullptr;
-    if ((rc = launch_components(h, out))) return rc;
-    HIPCHK(hipStreamSynchronize(h->stream));
+    if ((rc = read_state(h, out, buf, 2 * bytes))) return rc;
     if (E) std::memcpy(E, buf.at(), bytes);
     if (M) std::memcpy(M, buf.at(bytes), bytes);
     return RFIM_OK;
@@ -1223,13 +1243,12 @@ int rfim_components(rfim_t *h, int64_t *B, double *F, int64_t *M) {
     const size_t bytes = (size_t)h->R * 8;
     Pinned buf;
     int rc;
-    if ((rc = buf.get(3 * bytes))) return rc;
+    if ((rc = buf.get(4 * bytes))) return rc;
     rfim_dev::Readout out;
     out.B = (int64_t *)buf.at();
     out.F = (double *)buf.at(bytes);
     out.M = (int64_t *)buf.at(2 * bytes);
-    if ((rc = launch_components(h, out))) return rc;
-    HIPCHK(hipStreamSynchronize(h->stream));
+    if ((rc = read_state(h, out, buf, 3 * bytes))) return rc;
     std::memcpy(B, out.B, bytes);
     std::memcpy(F, out.F, bytes);
     std::memcpy(M, out.M, bytes);

@@ -211,27 +211,32 @@ hipError_t launch_box(const Lattice &lat, const StepIn &in, const uint8_t *src, 
                       int nsweep, int toff, int energy, hipStream_t s);
 hipError_t launch_generic_sweep(const Lattice &lat, int colour, int toff, hipStream_t s);
 // Energy partials of the state at rest, lat.nblk per replica, from the bytes
-// or, in bit storage, the bits; energy_blocks: the count for a reduction that
-// does not have to match the sweep's.
-int energy_blocks(const Lattice &lat);
+// or, in bit storage, the bits.
 hipError_t launch_energy(const Lattice &lat, hipStream_t s);
-// Totals of the partials, to the arrays that are not null (device memory or
-// pinned host memory): by replica id, E_slot and M_slot by temperature slot.
+// Energies and magnetisations to the arrays that are not null (pinned host
+// memory): by replica id, E_slot and M_slot by temperature slot.  Each
+// workgroup that writes any sets its word of `done` (pinned, cleared by the
+// caller) to 1 after its writes: readout_flags words, copy_out_flags for
+// CopyOut.
 struct Readout {
     int64_t *B = nullptr;
     double *F = nullptr;
     int64_t *M = nullptr;
     double *E_slot = nullptr;
     int64_t *M_slot = nullptr;
+    uint32_t *done = nullptr;
 };
-hipError_t launch_reduce(const Lattice &lat, const Readout &out, hipStream_t s);
+unsigned readout_flags(const Lattice &lat);
+hipError_t launch_readout(const Lattice &lat, const Readout &out, hipStream_t s);
 // Up to kMax device arrays of whole dwords to pinned host memory.
 struct CopyOut {
     static constexpr int kMax = 3;
     const void *src[kMax] = {};
     void *dst[kMax] = {};
     uint32_t words[kMax] = {};
+    uint32_t *done = nullptr;
 };
+unsigned copy_out_flags(const CopyOut &c);
 hipError_t launch_copy_out(const CopyOut &c, hipStream_t s);
 // Configurations (+-1, natural site order; sites first .. first + count - 1 of
 // the replicas' [R][N], both multiples of 64 or of a replica) to and from

@@ -1967,12 +1967,24 @@ __global__ __launch_bounds__(256) void fields_in_kernel(Lattice lat, FastDiv by_
     }
 }
 
+// The workgroup's writes to pinned host memory are done: the host, which polls
+// the word, sees them all once it sees the 1.  A readout of a small lattice
+// waits for little else than this; with a stream synchronisation instead
+// (which has the device run a barrier packet and signal its end) such a call
+// took 14 us, not 9.5.
+__device__ __forceinline__ void signal_done(uint32_t *done) {
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Device arrays to pinned host memory, in one launch.
 __global__ __launch_bounds__(256) void copy_out_kernel(CopyOut c) {
     const uint32_t q = blockIdx.y, n = c.words[q];
     GAS const uint32_t *src = (GAS const uint32_t *)c.src[q];
     uint32_t *dst = (uint32_t *)c.dst[q];
     for (uint32_t w = blockIdx.x * 256u + threadIdx.x; w < n; w += 256u * gridDim.x) dst[w] = src[w];
+    signal_done(c.done + blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 // ---------------------------------------------------------------------
@@ -1987,9 +1999,38 @@ __global__ __launch_bounds__(256) void copy_out_kernel(CopyOut c) {
 // and then read one site per step with divisions by L (126 and 336 us).
 // ---------------------------------------------------------------------
 
+// What an energy kernel does with a workgroup's sums: the partial of block
+// blockIdx.x of replica r or, where the workgroup took the whole replica
+// (WHOLE), its energy and magnetisation for the reader: one launch less (a
+// call at L = 16, R = 32 that took 18 us takes 11.5 with it and the polled end;
+// L = 32, R = 64 the same).
+constexpr int kWholeEnergyThreads = 1024;
+
+template <int KIND, bool WHOLE>
+__device__ __forceinline__ void energy_sums(const Lattice &lat, const Readout &out, uint32_t r, int nsite, int ksum, int upsum,
+                                            int eqsum, double fsum) {
+    if constexpr (!WHOLE) {
+        block_partial<KIND>(gptr(lat.part) + ((size_t)blockIdx.x * lat.pstride + r) * 3, nsite, ksum, upsum, eqsum, fsum);
+    } else {
+        __shared__ double tot[3];
+        const int slot = gptr(lat.r2t)[r];
+        block_partial<KIND>(tot, nsite, ksum, upsum, eqsum, fsum);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            if (out.B) out.B[r] = (int64_t)tot[0];
+            if (out.F) out.F[r] = tot[1];
+            if (out.M) out.M[r] = (int64_t)tot[2];
+            if (out.E_slot) out.E_slot[slot] = energy_of(lat, tot[0], tot[1]);
+            if (out.M_slot) out.M_slot[slot] = (int64_t)tot[2];
+            __hip_atomic_store(out.done + r, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+}
+
 // Rows of whole dwords (L a multiple of 8 NW): chunks as in the sweeps.
-template <int KIND, int NW>
-__global__ __launch_bounds__(256) void energy_rows(Lattice lat, FastDiv by_row, FastDiv by_l) {
+template <int KIND, int NW, bool WHOLE>
+__global__ __launch_bounds__(WHOLE ? kWholeEnergyThreads : 256) void energy_rows(Lattice lat, FastDiv by_row, FastDiv by_l,
+                                                                                 Readout out) {
     const uint32_t r = blockIdx.y, L = (uint32_t)lat.L, half = (uint32_t)lat.half;
     GAS const uint8_t *s0 = gptr((const uint8_t *)lat.spins) + (size_t)r * lat.N;
     GAS const uint8_t *s1 = s0 + half;
@@ -1997,7 +2038,8 @@ __global__ __launch_bounds__(256) void energy_rows(Lattice lat, FastDiv by_row, 
     GAS const float *fraw = gptr(lat.fraw);
     int ksum = 0, upsum = 0, eqsum = 0, n = 0;
     double fsum = 0.0;
-    for (uint32_t j0 = 4u * NW * (blockIdx.x * 256u + threadIdx.x); j0 < half; j0 += 4u * NW * 256u * gridDim.x, ++n) {
+    for (uint32_t j0 = 4u * NW * (blockIdx.x * blockDim.x + threadIdx.x); j0 < half;
+         j0 += 4u * NW * blockDim.x * gridDim.x, ++n) {
         const Chunk c = row_chunk<NW>(j0, 1u, L, by_row, by_l);
         uint32_t S1[NW], W[NW], U[NW], F1[NW];
         load_words<NW>(s1, j0, S1);
@@ -2005,13 +2047,13 @@ __global__ __launch_bounds__(256) void energy_rows(Lattice lat, FastDiv by_row, 
         neighbour_counts<NW>(s0, j0, c, W, U);
         chunk_energy<KIND, NW>(lat, S1, W, U, F1, fbits, fraw + half, fraw, j0, ksum, upsum, eqsum, fsum);
     }
-    block_partial<KIND>(gptr(lat.part) + ((size_t)blockIdx.x * lat.pstride + r) * 3, 4 * NW * n, ksum, upsum, eqsum,
-                        fsum);
+    energy_sums<KIND, WHOLE>(lat, out, r, 4 * NW * n, ksum, upsum, eqsum, fsum);
 }
 
 // Any even L: four consecutive pairs per step, which may lie in two rows.
-template <int KIND>
-__global__ __launch_bounds__(256) void energy_sites(Lattice lat, FastDiv by_row, FastDiv by_l) {
+template <int KIND, bool WHOLE>
+__global__ __launch_bounds__(WHOLE ? kWholeEnergyThreads : 256) void energy_sites(Lattice lat, FastDiv by_row, FastDiv by_l,
+                                                                                  Readout out) {
     const uint32_t r = blockIdx.y, half = (uint32_t)lat.half;
     GAS const uint8_t *s0 = gptr((const uint8_t *)lat.spins) + (size_t)r * lat.N;
     GAS const uint8_t *s1 = s0 + half;
@@ -2019,7 +2061,7 @@ __global__ __launch_bounds__(256) void energy_sites(Lattice lat, FastDiv by_row,
     GAS const float *fraw = gptr(lat.fraw);
     int ksum = 0, upsum = 0, eqsum = 0, n = 0;
     double fsum = 0.0;
-    for (uint32_t j0 = 4u * (blockIdx.x * 256u + threadIdx.x); j0 < half; j0 += 4u * 256u * gridDim.x, ++n) {
+    for (uint32_t j0 = 4u * (blockIdx.x * blockDim.x + threadIdx.x); j0 < half; j0 += 4u * blockDim.x * gridDim.x, ++n) {
         uint32_t S1[1], W[1], U[1], F1[1];
         load_words<1>(s1, j0, S1);
         load_words<1>(s0, j0, W);
@@ -2027,7 +2069,7 @@ __global__ __launch_bounds__(256) void energy_sites(Lattice lat, FastDiv by_row,
         U[0] = site_counts(s0, j0, W[0], 1u, (uint32_t)lat.L, by_row, by_l);
         chunk_energy<KIND, 1>(lat, S1, W, U, F1, fbits, fraw + half, fraw, j0, ksum, upsum, eqsum, fsum);
     }
-    block_partial<KIND>(gptr(lat.part) + ((size_t)blockIdx.x * lat.pstride + r) * 3, 4 * n, ksum, upsum, eqsum, fsum);
+    energy_sums<KIND, WHOLE>(lat, out, r, 4 * n, ksum, upsum, eqsum, fsum);
 }
 
 // Bit storage: a thread takes whole words of colour 1, as the bit sweep's
@@ -2162,6 +2204,7 @@ __device__ __forceinline__ void replica_totals(const Lattice &lat, const double 
 // exchange step, so both give the same bits).
 __global__ __launch_bounds__(kExchangeThreads) void reduce_kernel(Lattice lat, Readout out) {
     replica_totals(lat, lat.part, out);
+    signal_done(out.done);
 }
 
 // One exchange step per workgroup (one realization each).  Up to
@@ -2684,50 +2727,72 @@ hipError_t launch_unpack_bits(const Lattice &lat, hipStream_t s) {
     return hipGetLastError();
 }
 
-int energy_blocks(const Lattice &lat) {
-    // a step of every thread in each block, 64 blocks at most (the arena
-    // holds at least 64 partials per replica)
+// Workgroups per replica of the energy kernels in a readout, whose reduction
+// does not have to match the sweep's: a step of every thread in each, 64 at
+// most (the arena holds at least 64 partials per replica).
+static int energy_blocks(const Lattice &lat) {
     const int unit = lat.bits ? 256 * 32 : 256 * 4 * (lat.L % 32 == 0 ? 4 : 1);
     return std::min(64, (lat.half + unit - 1) / unit);
 }
 
+template <int KIND, bool WHOLE>
+static void launch_energy_kind(const Lattice &lat, dim3 grid, dim3 block, const Readout &out, hipStream_t s) {
+    const FastDiv by_row = fast_div((uint32_t)lat.L / 2u), by_l = fast_div((uint32_t)lat.L);
+    if (lat.bits)
+        hipLaunchKernelGGL(energy_bits<KIND>, grid, block, 0, s, lat);
+    else if (lat.L % 32 == 0)
+        hipLaunchKernelGGL((energy_rows<KIND, 4, WHOLE>), grid, block, 0, s, lat, by_row, by_l, out);
+    else if (lat.L % 8 == 0)
+        hipLaunchKernelGGL((energy_rows<KIND, 1, WHOLE>), grid, block, 0, s, lat, by_row, by_l, out);
+    else
+        hipLaunchKernelGGL((energy_sites<KIND, WHOLE>), grid, block, 0, s, lat, by_row, by_l, out);
+}
+
 hipError_t launch_energy(const Lattice &lat, hipStream_t s) {
     const dim3 grid((unsigned)lat.nblk, (unsigned)lat.R), block(256);
-    const FastDiv by_row = fast_div((uint32_t)lat.L / 2u), by_l = fast_div((uint32_t)lat.L);
-    if (lat.bits) {
-        if (lat.kind == 0)
-            hipLaunchKernelGGL(energy_bits<0>, grid, block, 0, s, lat);
-        else
-            hipLaunchKernelGGL(energy_bits<1>, grid, block, 0, s, lat);
-    } else if (lat.L % 32 == 0) {
-        if (lat.kind == 0)
-            hipLaunchKernelGGL((energy_rows<0, 4>), grid, block, 0, s, lat, by_row, by_l);
-        else
-            hipLaunchKernelGGL((energy_rows<1, 4>), grid, block, 0, s, lat, by_row, by_l);
-    } else if (lat.L % 8 == 0) {
-        if (lat.kind == 0)
-            hipLaunchKernelGGL((energy_rows<0, 1>), grid, block, 0, s, lat, by_row, by_l);
-        else
-            hipLaunchKernelGGL((energy_rows<1, 1>), grid, block, 0, s, lat, by_row, by_l);
-    } else {
-        if (lat.kind == 0)
-            hipLaunchKernelGGL(energy_sites<0>, grid, block, 0, s, lat, by_row, by_l);
-        else
-            hipLaunchKernelGGL(energy_sites<1>, grid, block, 0, s, lat, by_row, by_l);
-    }
+    if (lat.kind == 0)
+        launch_energy_kind<0, false>(lat, grid, block, Readout{}, s);
+    else
+        launch_energy_kind<1, false>(lat, grid, block, Readout{}, s);
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(const Lattice &lat, const Readout &out, hipStream_t s) {
+// One workgroup takes a whole replica up to L = 32 (at most 16 sites of each
+// colour per thread): beyond, too few workgroups would read too much each.
+static bool whole_energy(const Lattice &lat) { return !lat.bits && lat.half <= 16 * kWholeEnergyThreads; }
+
+unsigned readout_flags(const Lattice &lat) { return whole_energy(lat) ? (unsigned)lat.R : 1u; }
+
+hipError_t launch_readout(const Lattice &lat0, const Readout &out, hipStream_t s) {
+    Lattice lat = lat0;
+    if (whole_energy(lat)) {
+        const unsigned chunks = (unsigned)(lat.half / 4 + 3) / (lat.L % 32 == 0 ? 4u : 1u);
+        const dim3 grid(1, (unsigned)lat.R), block(std::min<unsigned>(kWholeEnergyThreads, (chunks + 63u) & ~63u));
+        if (lat.kind == 0)
+            launch_energy_kind<0, true>(lat, grid, block, out, s);
+        else
+            launch_energy_kind<1, true>(lat, grid, block, out, s);
+        return hipGetLastError();
+    }
+    lat.nblk = energy_blocks(lat);
+    const hipError_t e = launch_energy(lat, s);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kExchangeThreads), 0, s, lat, out);
     return hipGetLastError();
 }
 
-hipError_t launch_copy_out(const CopyOut &c, hipStream_t s) {
+static unsigned copy_out_blocks(const CopyOut &c) {
     uint32_t most = 0;
     for (int q = 0; q < CopyOut::kMax; ++q) most = std::max(most, c.words[q]);
-    if (most == 0) return hipSuccess;
-    hipLaunchKernelGGL(copy_out_kernel, dim3(std::min((most + 255u) / 256u, 256u), (unsigned)CopyOut::kMax), dim3(256), 0, s, c);
+    return std::min((most + 255u) / 256u, 256u);
+}
+
+unsigned copy_out_flags(const CopyOut &c) { return copy_out_blocks(c) * (unsigned)CopyOut::kMax; }
+
+hipError_t launch_copy_out(const CopyOut &c, hipStream_t s) {
+    const unsigned nb = copy_out_blocks(c);
+    if (nb == 0) return hipSuccess;
+    hipLaunchKernelGGL(copy_out_kernel, dim3(nb, (unsigned)CopyOut::kMax), dim3(256), 0, s, c);
     return hipGetLastError();
 }
 
