@@ -81,6 +81,35 @@ __device__ __forceinline__ int dot_spins(const Spins<V> &s, const Spins<V> &t, i
     }
 }
 
+// The workgroup's sums of RB replicas: the partials of block b or, if it is
+// the only one, the energies.
+template <int RB>
+__device__ __forceinline__ void write_sums(const int (&bsum)[RB], const double (&fsum)[RB], int R, int nb, int b, int r0,
+                                           double J, double h, double *part, double *E) {
+    __shared__ double red[2 * RB][4];
+    const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+        const double wb = (double)__ockl_wfred_add_i32(bsum[q]), wf = wave_total(fsum[q]);
+        if (lane == 63) {
+            red[2 * q][wave] = wb;
+            red[2 * q + 1][wave] = wf;
+        }
+    }
+    __syncthreads();
+    const int q = (int)threadIdx.x;
+    if (q >= RB || r0 + q >= R) return;
+    const double B = ((red[2 * q][0] + red[2 * q][1]) + red[2 * q][2]) + red[2 * q][3];
+    const double F = ((red[2 * q + 1][0] + red[2 * q + 1][1]) + red[2 * q + 1][2]) + red[2 * q + 1][3];
+    if (nb == 1) {
+        E[r0 + q] = -(J * B) - (h * F);
+    } else {
+        double *o = part + 2 * ((size_t)(r0 + q) * nb + b);
+        o[0] = B;
+        o[1] = F;
+    }
+}
+
 // Block (b, group g): sites [b * chunk, min(N, (b + 1) * chunk)) of replicas
 // g * RB .. g * RB + RB - 1 (chunk a multiple of V).  B counts each bond once
 // through its forward partner along x, y and z (periodic); F = sum f_i s_i in
@@ -93,8 +122,9 @@ __device__ __forceinline__ int dot_spins(const Spins<V> &s, const Spins<V> &t, i
 //
 // Bound: load latency and the L1 (each spin row is read for its own sites and
 // as the forward row of two others); the spins are read from memory about
-// once.  L = 64, R = 192 (50 MB of spins): 19.6 us a call with the totals,
-// against 136 with one site per thread step and 64-bit divisions.
+// once.  For the rows that are not whole 16-site units, and arrays without
+// their alignment: L = 100, R = 50
+// (also 50 MB) 32 us.
 template <int V, int RB>
 __global__ __launch_bounds__(kThreads) void site_energy_partials(int L, int R, int nb, int N, int chunk, double J,
                                                                  double h, const int8_t *__restrict__ spins,
@@ -173,28 +203,87 @@ __global__ __launch_bounds__(kThreads) void site_energy_partials(int L, int R, i
             ++z;
         }
     }
-    __shared__ double red[2 * RB][4];
-    const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+    write_sums<RB>(bsum, fsum, R, nb, b, r0, J, h, part, E);
+}
+
+// Rows of whole 16-site units (L a multiple of 16): a thread keeps one unit of
+// the plane and walks `cz` planes up, so that the unit above is the next
+// step's own; the sums as in site_energy_partials.  Block b of a group takes
+// threads [256 b, 256 b + 256) of the (L / cz rounded up) * L * L / 16 columns.
+// SHUF (L a power of two): a wave holds whole rows and the spin past a unit's
+// end comes from the lane that has it; else it is a load of one byte.
+//
+// Bound: the FP64 field sum (three instructions per site) and the loads, by
+// turns; the spins are read from memory once, their row ahead in y a second
+// time from the L1.  L = 64, R = 192 (50 MB of spins): 16.5 us a call with the
+// totals, 20.8 with each unit's three rows loaded for itself (136 with one site
+// per thread step and 64-bit divisions); L = 128, R = 64 36 against 62.  The
+// next plane's loads ahead of this one's sums: 18.6 and 38 (registers).
+template <int RB, bool SHUF>
+__global__ __launch_bounds__(kThreads) void site_energy_columns(int L, int R, int nb, int N, int cz, double J, double h,
+                                                                const int8_t *__restrict__ spins,
+                                                                const float *__restrict__ fields,
+                                                                double *__restrict__ part, double *__restrict__ E,
+                                                                int remap) {
+    uint32_t blk = blockIdx.x;
+    if (remap) blk = (blk & 7u) * (gridDim.x >> 3) + (blk >> 3);
+    const int b = (int)(blk % (uint32_t)nb), r0 = (int)(blk / (uint32_t)nb) * RB;
+    const int LL = L * L, rowu = L >> 4, upp = rowu * L;
+    const int g = b * kThreads + (int)threadIdx.x, zc = g / upp, p = g - zc * upp;
+    const int y = p / rowu, x = p - y * rowu;
+    int z = zc * cz;
+    const int z1 = min(z + cz, L);
+    int i = z * LL + 16 * p;
+    const int dx = x + 1 == rowu ? 16 - L : 16, dy = y + 1 == L ? -(L - 1) * L : L;
+    const int next_lane = 4 * (int)(((threadIdx.x & 63u) - (uint32_t)x) + (x + 1 == rowu ? 0u : (uint32_t)x + 1u));
+    int bsum[RB];
+    double fsum[RB];
+    const int8_t *sp[RB];
+    Spins<16> s[RB];
 #pragma unroll
     for (int q = 0; q < RB; ++q) {
-        const double wb = (double)__ockl_wfred_add_i32(bsum[q]), wf = wave_total(fsum[q]);
-        if (lane == 63) {
-            red[2 * q][wave] = wb;
-            red[2 * q + 1][wave] = wf;
+        bsum[q] = 0;
+        fsum[q] = 0.0;
+        sp[q] = spins + (size_t)min(r0 + q, R - 1) * (size_t)N;   // past the last: read again, not written
+        if (z < L) s[q] = load_spins<16>(sp[q] + i);
+    }
+    for (; z < z1; ++z) {
+        const int iz = z + 1 == L ? i - (L - 1) * LL : i + LL;
+        Spins<16> up[RB], sy[RB];
+        int32_t next[RB];
+#pragma unroll
+        for (int q = 0; q < RB; ++q) {
+            up[q] = load_spins<16>(sp[q] + iz);
+            sy[q] = load_spins<16>(sp[q] + i + dy);
+            if (!SHUF) next[q] = *(const uint8_t *)(sp[q] + i + dx);
         }
+        float4 f[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k] = *(const float4 *)(fields + i + 4 * k);
+#pragma unroll
+        for (int q = 0; q < RB; ++q) {
+            if (SHUF) next[q] = __builtin_amdgcn_ds_bpermute(next_lane, s[q].w[0]);
+            Spins<16> sx;
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                sx.w[w] = (int32_t)__builtin_amdgcn_alignbyte((uint32_t)(w < 3 ? s[q].w[w < 3 ? w + 1 : 0] : next[q]),
+                                                              (uint32_t)s[q].w[w], 1u);
+            bsum[q] = dot_spins<16>(s[q], sx, dot_spins<16>(s[q], sy[q], dot_spins<16>(s[q], up[q], bsum[q])));
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double fk[4] = {f[k].x, f[k].y, f[k].z, f[k].w};
+#pragma unroll
+            for (int q = 0; q < RB; ++q)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    fsum[q] = fma(fk[j], (double)(int)(int8_t)(s[q].w[k] >> (8 * j)), fsum[q]);   // the product is exact
+        }
+#pragma unroll
+        for (int q = 0; q < RB; ++q) s[q] = up[q];
+        i += LL;
     }
-    __syncthreads();
-    const int q = (int)threadIdx.x;
-    if (q >= RB || r0 + q >= R) return;
-    const double B = ((red[2 * q][0] + red[2 * q][1]) + red[2 * q][2]) + red[2 * q][3];
-    const double F = ((red[2 * q + 1][0] + red[2 * q + 1][1]) + red[2 * q + 1][2]) + red[2 * q + 1][3];
-    if (nb == 1) {
-        E[r0 + q] = -(J * B) - (h * F);
-    } else {
-        double *o = part + 2 * ((size_t)(r0 + q) * nb + b);
-        o[0] = B;
-        o[1] = F;
-    }
+    write_sums<RB>(bsum, fsum, R, nb, b, r0, J, h, part, E);
 }
 
 // E_r = -(J B_r) - (h F_r): one wave per replica, lane l adds blocks l,
@@ -232,6 +321,15 @@ Split split_sites(int N, int V, int groups, int R) {
     return {(units + per - 1) / per, per * unit};
 }
 
+hipError_t launch_totals(int R, int nb, double J, double h, const double *part, double *E, hipStream_t s) {
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess && nb > 1) {
+        hipLaunchKernelGGL(site_energy_totals, dim3((unsigned)((R + 3) / 4)), dim3(kThreads), 0, s, R, nb, J, h, part, E);
+        e = hipGetLastError();
+    }
+    return e;
+}
+
 template <int V, int RB>
 hipError_t launch_energies(int L, int R, double J, double h, const int8_t *spins, const float *fields, double *part,
                            double *E, hipStream_t s) {
@@ -240,13 +338,36 @@ hipError_t launch_energies(int L, int R, double J, double h, const int8_t *spins
     const unsigned blocks = (unsigned)sp.nb * (unsigned)groups;
     hipLaunchKernelGGL((site_energy_partials<V, RB>), dim3(blocks), dim3(kThreads), 0, s, L, R, sp.nb, N, sp.chunk, J,
                        h, spins, fields, part, E, blocks % 8u == 0 ? 1 : 0);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess && sp.nb > 1) {
-        hipLaunchKernelGGL(site_energy_totals, dim3((unsigned)((R + 3) / 4)), dim3(kThreads), 0, s, R, sp.nb, J, h,
-                           (const double *)part, E);
-        e = hipGetLastError();
-    }
-    return e;
+    return launch_totals(R, sp.nb, J, h, part, E, s);
+}
+
+// Planes a thread walks: as many as leave kMinColumnBlocks workgroups, each of
+// them full, and no more partials than the scratch array and the totals take.
+// Two to four workgroups per CU are best: L = 64, R = 192 16.5 us with 768,
+// 19.5 with 384 or 1536; L = 128, R = 40 27.6 us with 640, 42 with 1280, 33
+// with 320; R = 64 36 with 512, 45 with 1024.
+constexpr int kMinColumnBlocks = 512;
+
+template <int RB>
+hipError_t launch_columns(int L, int R, double J, double h, const int8_t *spins, const float *fields, double *part, double *E,
+                          hipStream_t s) {
+    const int N = L * L * L, groups = (R + RB - 1) / RB, upp = L * L / 16;
+    auto blocks_of = [&](int cz) { return (int)(((long long)((L + cz - 1) / cz) * upp + kThreads - 1) / kThreads); };
+    const int most = std::min(kMaxBlocks, kScratchPairs / R);
+    int cz = 1;
+    while (cz < L && (blocks_of(cz) > most || ((long long)L * upp >= 2ll * cz * kThreads &&
+                                               (long long)blocks_of(2 * cz) * groups >= kMinColumnBlocks)))
+        cz *= 2;
+    const int nb = blocks_of(cz);
+    if (nb > most) return launch_energies<4, RB>(L, R, J, h, spins, fields, part, E, s);   // R beyond 10^5
+    const unsigned blocks = (unsigned)nb * (unsigned)groups;
+    if ((L & (L - 1)) == 0)
+        hipLaunchKernelGGL((site_energy_columns<RB, true>), dim3(blocks), dim3(kThreads), 0, s, L, R, nb, N, cz, J, h, spins,
+                           fields, part, E, blocks % 8u == 0 ? 1 : 0);
+    else
+        hipLaunchKernelGGL((site_energy_columns<RB, false>), dim3(blocks), dim3(kThreads), 0, s, L, R, nb, N, cz, J, h, spins,
+                           fields, part, E, blocks % 8u == 0 ? 1 : 0);
+    return launch_totals(R, nb, J, h, part, E, s);
 }
 
 std::mutex g_mu;
@@ -289,14 +410,13 @@ extern "C" int rfim_energies_noalloc(int L, int R, double J, double h, const int
     if (rc) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
     // Widest step that divides a row, where both arrays allow its loads.  Two
-    // replicas share a pass over the field (L = 64, R = 192: 19.6 us with two,
-    // 23 with one, 21-25 with four, 38 with eight, whose loads the registers
-    // no longer keep in flight).
+    // replicas share a pass over the field (L = 64, R = 192: 16.5 us with two,
+    // 21 with one, 18 with four).
     const bool a16 = ((uintptr_t)d_fields & 15u) == 0;
     hipError_t e;
     if (L % 16 == 0 && a16 && ((uintptr_t)d_spins & 15u) == 0)
-        e = R >= 2 ? launch_energies<16, 2>(L, R, J, h, d_spins, d_fields, part, d_E, s)
-                   : launch_energies<16, 1>(L, R, J, h, d_spins, d_fields, part, d_E, s);
+        e = R >= 2 ? launch_columns<2>(L, R, J, h, d_spins, d_fields, part, d_E, s)
+                   : launch_columns<1>(L, R, J, h, d_spins, d_fields, part, d_E, s);
     else if (L % 4 == 0 && a16 && ((uintptr_t)d_spins & 3u) == 0)
         e = R >= 2 ? launch_energies<4, 2>(L, R, J, h, d_spins, d_fields, part, d_E, s)
                    : launch_energies<4, 1>(L, R, J, h, d_spins, d_fields, part, d_E, s);

@@ -87,3 +87,33 @@ def test_noalloc_energies_every_width(rfim_mod, L, R, kind, offset):
         assert np.array_equal(E.cpu().numpy(), want)
     else:
         assert np.allclose(E.cpu().numpy(), want, rtol=1e-12, atol=1e-9)
+
+
+@pytest.mark.parametrize("L,R", [(16, 3), (16, 1100), (32, 521), (48, 520), (80, 110), (128, 9)])
+@pytest.mark.parametrize("kind", ["b", "g"])
+def test_noalloc_energies_columns(rfim_mod, L, R, kind):
+    """Columns of whole 16-site units at one plane and several planes per
+    thread (L = 48: 32 and then 16; L = 80: rows that no wave holds whole),
+    odd replica counts; equal configurations have equal energies wherever
+    they lie."""
+    import torch
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(45 + L)
+    s = 2 * torch.randint(0, 2, (R, L, L, L), device="cuda", dtype=torch.int8, generator=g) - 1
+    s[R - 1] = s[0]
+    f = W.bimodal_fields(L, [45, L]) if kind == "b" else W.gaussian_fields(L, [45, L])
+    f = torch.from_numpy(f).cuda().reshape(L, L, L)
+    E = torch.full((R,), np.nan, dtype=torch.float64, device="cuda")
+    rfim_mod.rfim.rfim_energies_noalloc(L, R, J, H, s, f, E)
+    torch.cuda.synchronize()
+    for r in (0, 1, R // 2, R - 1):
+        a = s[r].to(torch.int32)
+        bonds = sum(int((a * torch.roll(a, -1, k)).sum()) for k in range(3))
+        want = -J * bonds - H * float((f.double() * a).sum())
+        if kind == "b":
+            assert float(E[r]) == want
+        else:       # FP64 sums of N terms in another order
+            assert np.isclose(float(E[r]), want, rtol=1e-12, atol=1e-9)
+    assert float(E[0]) == float(E[R - 1])
+    assert not torch.isnan(E).any()
