@@ -1,0 +1,103 @@
+"""Calls of several exchange intervals on shapes whose launches run whole
+intervals: the step between two intervals runs inside the first launch of the
+next one, the last one by itself.  +-1 fields follow the oracle bit for bit;
+with continuous fields one call ends in the state of single intervals, whose
+steps are all of the second kind."""
+import numpy as np
+import pytest
+
+from paper_1508_06268_amd import workloads as W
+from parity_util import assert_same_state, make_pair
+
+pytestmark = pytest.mark.gpu
+
+# (L, R, launch shape or None for the default): resident; slabs of one, two and
+# three sweeps a launch; boxes and residents of other sizes; around the largest
+# ladder (R times the partials per replica up to 256) that takes the step so
+SHAPES = [(8, 1, None), (8, 2, None), (8, 5, None), (8, 256, None), (8, 257, None), (16, 7, None), (16, 6, (2, 4, 256)),
+          (32, 3, (1, 4, 1024)), (32, 5, (2, 8, 512)), (32, 64, (3, 4, 1024)), (32, 3, (4, 2, 1024)), (22, 3, None),
+          (24, 9, None), (24, 60, None), (40, 3, None), (48, 5, None), (6, 300, None)]
+
+
+def ladder(R, L):
+    return W.linear_temps(R, 2.0, 2.0 + 0.002 * (R - 1) * (64 / L) ** 1.5) if R > 1 else np.array([2.0])
+
+
+@pytest.mark.parametrize("L,R,shape", SHAPES)
+def test_intervals_match_oracle(rfim_mod, oracle_mod, L, R, shape):
+    f = W.bimodal_fields(L, [101, L])
+    g, o = make_pair(rfim_mod, oracle_mod, L, R, 1.0, 1.5, f, ladder(R, L), seed=L, realization=R)
+    if shape:
+        g.set_launch_shape(*shape)
+    for n, every in ((9, 3), (4, 4), (7, 2), (5, 0), (3, 1)):     # ends on a step, one step, ends off one, none, each sweep
+        g.sweep(n, every)
+        o.sweep(n, every)
+        assert_same_state(g, o, "L=%d R=%d (%d, %d)" % (L, R, n, every))
+    g.close()
+    o.close()
+
+
+@pytest.mark.parametrize("L,R,shape", SHAPES)
+def test_one_call_equals_single_intervals(rfim_mod, L, R, shape):
+    f = W.gaussian_fields(L, [102, L])
+    out = []
+    for calls in ([(15, 3), (4, 3)], [(3, 3)] * 5 + [(4, 3)]):
+        g = rfim_mod.Rfim(L, R, 1.0, 1.5, f, ladder(R, L), seed=L, realization=R)
+        if shape:
+            g.set_launch_shape(*shape)
+        for n, every in calls:
+            g.sweep(n, every)
+        att, acc = g.exchange_stats()
+        out.append((g.spins(), g.perm(), g.observables(), att, acc, g.energies()))
+        g.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("L,R", [(8, 16), (32, 6), (24, 5)])
+def test_two_handles_on_one_stream_and_two_threads(rfim_mod, L, R):
+    """The pending steps' state is the call's own: handles that take turns on
+    one stream, and handles of two threads, end as each does alone."""
+    import threading
+
+    import torch
+
+    def make(q, stream=None):
+        f = W.bimodal_fields(L, [103, L, q])
+        return rfim_mod.Rfim(L, R, 1.0, 1.5, f, ladder(R, L), seed=q, stream=stream)
+
+    def state(g):
+        return g.spins(), g.perm(), g.observables(), g.energies()
+
+    alone = []
+    for q in range(2):
+        g = make(q)
+        g.sweep(40, 4)
+        g.sweep(20, 4)
+        alone.append(state(g))
+        g.close()
+    stream = torch.cuda.Stream()
+    pair = [make(q, stream) for q in range(2)]
+    for n in (40, 20):
+        for g in pair:
+            g.sweep(n, 4)
+    got = [state(g) for g in pair]
+    for g in pair:
+        g.close()
+    threaded = [None, None]
+
+    def work(q):
+        g = make(q)
+        g.sweep(40, 4)
+        g.sweep(20, 4)
+        threaded[q] = state(g)
+        g.close()
+
+    ts = [threading.Thread(target=work, args=(q,)) for q in range(2)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for q in range(2):
+        for a, b, c in zip(alone[q], got[q], threaded[q]):
+            assert np.array_equal(a, b) and np.array_equal(a, c)
