@@ -991,9 +991,16 @@ int sweep_impl(rfim *h, int64_t n, int every) {
     // Only where the launch is small enough for the device to hold it at once
     // (256 CUs, one workgroup each at least): a longer one gains little from
     // the launch saved and runs better with the registers the step takes.
-    const bool lazy = !tiled && !bitsm && !h->measure && h->nblk <= rfim_dev::kMaxStepPartials &&
+    // A captured call takes its counters from the device, so that its replays
+    // go on where the last one ended, and sweeps in place where it can.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    HIPCHK(hipStreamIsCapturing(h->stream, &capture));
+    const bool captured = capture != hipStreamCaptureStatusNone;
+    const bool whole = h->box.planes >= h->L;           // boxes of whole replicas: in place, any number of sweeps
+    const bool boxes = h->box.planes > 0 && (whole || !captured);
+    const bool lazy = !captured && !tiled && !bitsm && !h->measure && h->nblk <= rfim_dev::kMaxStepPartials &&
                       (long long)h->R * h->nblk <= 256 &&
-                      (pow2 ? h->mode >= 1 : h->box.planes > 0 || rfim_dev::generic_resident(h->L));
+                      (pow2 ? h->mode >= 1 : boxes || rfim_dev::generic_resident(h->L));
     StepBuffers sb(h);
     int unsettled = 0;                  // sweeps since the device counters were last right
     auto settle = [&]() -> int {
@@ -1007,7 +1014,7 @@ int sweep_impl(rfim *h, int64_t n, int every) {
         int64_t to_next = every > 0 ? (int64_t)(every - (int64_t)(h->t % (uint64_t)every)) : remaining;
         const int m = (int)std::min<int64_t>(remaining, to_next);
         const bool exch = every > 0 && m == to_next;
-        const bool fused = exch && !tiled && (bitsm || h->box.planes || rfim_dev::fused_energy(lat));
+        const bool fused = exch && !tiled && (bitsm || (h->box.planes ? boxes : rfim_dev::fused_energy(lat)));
         if (!exch && sb.pending()) {
             const int rc = settle();
             if (rc) return rc;
@@ -1057,9 +1064,8 @@ int sweep_impl(rfim *h, int64_t n, int every) {
                 HIPCHK(rfim_dev::launch_stream_sweep(ln, 0, q, 0, h->stream));
                 HIPCHK(rfim_dev::launch_stream_sweep(ln, 1, q, fused && q == m - 1, h->stream));
             }
-        } else if (h->box.planes) {
+        } else if (boxes) {
             // as many launches as the plan's sweeps need, of about equal length
-            const bool whole = h->box.planes >= h->L;       // in place, any number of sweeps
             for (int q = 0; q < m;) {
                 const int left = whole ? 1 : (m - q + h->box.sweeps - 1) / h->box.sweeps, ns = (m - q + left - 1) / left;
                 const int e = fused && q + ns == m;

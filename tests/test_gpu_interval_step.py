@@ -101,3 +101,31 @@ def test_two_handles_on_one_stream_and_two_threads(rfim_mod, L, R):
     for q in range(2):
         for a, b, c in zip(alone[q], got[q], threaded[q]):
             assert np.array_equal(a, b) and np.array_equal(a, c)
+
+
+@pytest.mark.parametrize("L,R", [(8, 5), (16, 3), (22, 4), (32, 3), (40, 3), (48, 30), (60, 2)])
+def test_captured_call_goes_on_at_each_replay(rfim_mod, oracle_mod, L, R):
+    """A call captured on the handle's stream: every replay runs the next
+    sweeps and steps, as the next call would."""
+    import torch
+
+    f = W.bimodal_fields(L, [104, L])
+    stream = torch.cuda.Stream()
+    g = rfim_mod.Rfim(L, R, 1.0, 1.5, f, ladder(R, L), seed=L, stream=stream)
+    o = oracle_mod.Oracle(L, R, 1.0, 1.5, f, ladder(R, L), seed=L)
+    g.sweep(4, 2)
+    o.sweep(4, 2)
+    g.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream, capture_error_mode="thread_local"):
+        g.sweep(6, 2)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        o.sweep(6, 2)
+        assert np.array_equal(g.spins(), o.spins()) and np.array_equal(g.perm(), o.perm())
+        assert np.array_equal(g.energies(), o.energies())
+    for a, b in zip(g.exchange_stats(), o.exchange_stats()):
+        assert np.array_equal(a, b)
+    g.close()
+    o.close()
