@@ -105,8 +105,8 @@ typedef struct rfim_params {
  * at create time (all its buffers), at most two more for its default
  * storage and shape (the bit arrays of handles that start in bits, the
  * second spin buffer of a slab shape or, at L not a power of two, of the
- * slabs a handle of few replicas runs on), one when a slab shape is first set, two for
- * bit storage, and three when rfim_set_measure first turns the measurement
+ * slabs a handle of few replicas runs on), one when a slab shape is first
+ * set, two for bit storage, and three when rfim_set_measure first turns the measurement
  * on.  A caching allocator (e.g. PyTorch's) can serve them. */
 typedef struct rfim_alloc {
     void *(*alloc)(size_t bytes, void *ctx);
@@ -228,9 +228,12 @@ int rfim_fourier(rfim_t *h, double *fourier);
  * (RFIM_ENOMEM if that fails).  Other L have the single shape (0, 0, 0).
  * A new handle starts from a shape chosen by L from measurements on gfx950
  * (rfim_get_launch_shape reports it): (1, 1, 64), (1, 2, 256), (1, 4, 1024)
- * at L = 8, 16, 32, (0, 4, 128) above; a standalone handle with continuous
- * fields at L = 32 and R_cap <= 64 starts on the slab shape (3, 4, 1024)
- * when its second spin buffer can be allocated.
+ * at L = 8, 16, 32, (0, 4, 128) above; a standalone handle starts on
+ * (1, 1, 512) at L = 16 and R_cap <= 256 and, when its second spin buffer can
+ * be allocated, on the slab shape (4, 8, 1024) at L = 32 and R_cap <= 32 or
+ * (3, 4, 1024) at L = 32 and R_cap <= 64 with continuous fields.  A call made
+ * while the handle's stream is being captured runs the shape of the class
+ * instead of slabs.
  * RFIM_EINVAL for a shape not valid for the handle's L. */
 int rfim_set_launch_shape(rfim_t *h, int mode, int nw, int wg);
 int rfim_get_launch_shape(const rfim_t *h, int *mode, int *nw, int *wg);

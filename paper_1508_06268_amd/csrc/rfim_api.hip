@@ -744,9 +744,28 @@ struct Pieces {
     explicit Pieces(const rfim *h) : total((size_t)h->R * h->N), piece(std::min(total, kPinnedBlock)) {}
 };
 
-// Standalone continuous-field handles at L = 32 with at most this many
-// replicas start on a slab shape (rfim_create_ex).
-constexpr int kSlabDefaultMaxReplicas = 64;
+// The launch shape a standalone handle starts on, where it is not the one of
+// its class: with few replicas a finer split fills more of the 256 CUs.
+// Microseconds a sweep on gfx950 at a step every 10 sweeps (every sweep, no
+// step), +-1 and continuous fields:
+//   L = 32, R = 32: resident 4.08 and 5.07 (10.0 and 12.4, 3.41 and 4.16);
+//     4 slabs, two sweeps a launch 3.96 and 4.51 (8.94 and 10.2, 3.67 and
+//     4.14); 8 slabs, three sweeps a launch 3.62 and 4.11 (9.84 and 10.7,
+//     2.96 and 3.42); R = 8 3.33 and 3.75 with the last;
+//   L = 32, R = 40: 4.10 and 5.05; 4.00 and 4.55; 5.93 and 6.77 (more than a
+//     workgroup per CU); R = 64: 4.09 and 5.12; 4.17 and 4.72;
+//   L = 16, R = 64: two dwords per thread 1.47 and 1.59, one 1.41 and 1.49;
+//     R = 384 1.97 and 2.16, 1.99 and 2.14; R = 4096 8.7 and 10.3, 9.2 and
+//     10.6.
+struct Shape3 {
+    int mode = 0, nw = 0, wg = 0;
+};
+Shape3 standalone_shape(int L, int R_cap, int kind) {
+    if (L == 16 && R_cap <= 256) return {1, 1, 512};
+    if (L == 32 && R_cap <= 32) return {4, 8, 1024};
+    if (L == 32 && R_cap <= 64 && kind == 1) return {3, 4, 1024};
+    return {};
+}
 
 // Energy partials per replica of a handle in byte storage.
 int byte_partials(const rfim *h) {
@@ -950,8 +969,12 @@ struct StepBuffers {
 int sweep_impl(rfim *h, int64_t n, int every) {
     h->lat_host = h->lattice();
     const Lattice &lat = h->lat_host;
-    const rfim_dev::Launch ln = single_launch(h);
+    rfim_dev::Launch ln = single_launch(h);
     const bool pow2 = h->log2L >= 3;
+    if (pow2 && h->mode >= 2) {     // the resident shape in place of slabs (captured calls)
+        default_shape(h->L, h->R, &ln.mode, &ln.nw, &ln.wg);
+        ln.nblocks = h->R;
+    }
     const bool tiled = h->order == 1;
     const bool bitsm = h->bits_mode;
     const bool big = (long long)(h->R / 2) * h->half >=
@@ -998,6 +1021,7 @@ int sweep_impl(rfim *h, int64_t n, int every) {
     const bool captured = capture != hipStreamCaptureStatusNone;
     const bool whole = h->box.planes >= h->L;           // boxes of whole replicas: in place, any number of sweeps
     const bool boxes = h->box.planes > 0 && (whole || !captured);
+    const bool slabs = pow2 && h->mode >= 2 && !captured;
     const bool lazy = !captured && !tiled && !bitsm && !h->measure && h->nblk <= rfim_dev::kMaxStepPartials &&
                       (long long)h->R * h->nblk <= 256 &&
                       (pow2 ? h->mode >= 1 : boxes || rfim_dev::generic_resident(h->L));
@@ -1014,7 +1038,7 @@ int sweep_impl(rfim *h, int64_t n, int every) {
         int64_t to_next = every > 0 ? (int64_t)(every - (int64_t)(h->t % (uint64_t)every)) : remaining;
         const int m = (int)std::min<int64_t>(remaining, to_next);
         const bool exch = every > 0 && m == to_next;
-        const bool fused = exch && !tiled && (bitsm || (h->box.planes ? boxes : rfim_dev::fused_energy(lat)));
+        const bool fused = exch && !tiled && (bitsm || (h->box.planes ? boxes : h->mode >= 2 ? slabs : rfim_dev::fused_energy(lat)));
         if (!exch && sb.pending()) {
             const int rc = settle();
             if (rc) return rc;
@@ -1035,8 +1059,8 @@ int sweep_impl(rfim *h, int64_t n, int every) {
                 HIPCHK(rfim_dev::launch_tile_sweep(lat, h->tiles, 0, q, h->stream));
                 HIPCHK(rfim_dev::launch_tile_sweep(lat, h->tiles, 1, q, h->stream));
             }
-        } else if (pow2 && h->mode >= 2) {
-            // slabs: up to mode - 1 sweeps per launch, alternating buffers
+        } else if (slabs) {
+            // up to mode - 1 sweeps per launch, alternating buffers
             const int K = rfim_dev::slab_sweeps_per_launch(h->mode);
             for (int q = 0; q < m;) {
                 const int ns = std::min(K, m - q);
@@ -1048,7 +1072,7 @@ int sweep_impl(rfim *h, int64_t n, int every) {
                 q += ns;
             }
             h->lat_host = h->lattice();
-        } else if (pow2 && h->mode == 1) {
+        } else if (pow2 && h->mode >= 1) {
             HIPCHK(rfim_dev::launch_resident(ln, in, m, fused ? 1 : 0, h->stream));
             sb.taken();
         } else if (pow2 && split) {
@@ -1163,13 +1187,10 @@ rfim_t *rfim_create_ex(const rfim_params_t *params, const rfim_alloc_t *alloc, v
         (void)hipGetLastError();
         g_error.clear();
     }
-    // continuous fields at L = 32 with few replicas: slabs of 8 planes, two
-    // sweeps per launch, so that the replicas cover all CUs (measured on
-    // gfx950 at R = 64: +14 % over one workgroup per replica; at R = 128 the
-    // resident shape is faster); without the second spin buffer the handle
-    // keeps the resident shape
-    if (h->kind == 1 && h->L == 32 && h->R_cap <= kSlabDefaultMaxReplicas &&
-        rfim_set_launch_shape(h, 3, 4, 1024) != RFIM_OK) {
+    // (without the second spin buffer of a slab shape the handle keeps the
+    // shape of its class)
+    const Shape3 own = standalone_shape(h->L, h->R_cap, h->kind);
+    if (own.mode && rfim_set_launch_shape(h, own.mode, own.nw, own.wg) != RFIM_OK) {
         (void)hipGetLastError();
         g_error.clear();
     }

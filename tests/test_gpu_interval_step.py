@@ -129,3 +129,27 @@ def test_captured_call_goes_on_at_each_replay(rfim_mod, oracle_mod, L, R):
         assert np.array_equal(a, b)
     g.close()
     o.close()
+
+
+@pytest.mark.parametrize("kind", ["b", "g"])
+@pytest.mark.parametrize("L,R,bimodal,gaussian", [
+    (16, 256, (1, 1, 512), (1, 1, 512)), (16, 257, (1, 2, 256), (1, 2, 256)),
+    (32, 32, (4, 8, 1024), (4, 8, 1024)), (32, 33, (1, 4, 1024), (3, 4, 1024)),
+    (32, 65, (1, 4, 1024), (1, 4, 1024))])
+def test_default_shapes(rfim_mod, L, R, bimodal, gaussian, kind):
+    """The shape a handle starts on follows its capacity; the chain does not."""
+    f = W.bimodal_fields(L, [105, L]) if kind == "b" else W.gaussian_fields(L, [105, L])
+    out = []
+    for cap, shape in ((R, None), (R, (1, 2, 256)), (R + 300, None)):
+        g = rfim_mod.Rfim(L, R, 1.0, 1.5, f, ladder(R, L), seed=L, R_cap=cap)
+        if shape:
+            g.set_launch_shape(*shape)
+        elif cap == R:
+            assert g.launch_shape() == (bimodal if kind == "b" else gaussian)
+        else:
+            assert g.launch_shape() == ((1, 2, 256) if L == 16 else (1, 4, 1024))
+        g.sweep(11, 5)
+        out.append((g.spins(), g.perm()))
+        g.close()
+    for other in out[1:]:
+        assert np.array_equal(out[0][0], other[0]) and np.array_equal(out[0][1], other[1])
