@@ -1124,7 +1124,8 @@ __global__ __launch_bounds__(1024) void sweep_box(Lattice lat, StepIn in, FastDi
     }
 }
 
-// Resident sweeps (L = 2^l <= 32): one workgroup holds one replica's spins
+// Resident sweeps (L = 2^l <= 32; few replicas at L = 8 run
+// sweep_resident_ahead below): one workgroup holds one replica's spins
 // in LDS and runs `nsweep` whole sweeps (colour 0 then colour 1, a barrier
 // between half-sweeps), then, if asked, the energy partial of the final
 // state, and writes the spins back.  Fields stay in global memory (shared
@@ -1226,6 +1227,107 @@ __global__ __launch_bounds__(1024) void sweep_resident(Lattice lat0, const Latti
     }
     GAS u32x4 *dst = (GAS u32x4 *)(gptr(lat.spins) + (size_t)r * N);
     for (uint32_t q = threadIdx.x; q < N / 16u; q += blockDim.x) dst[q] = lds4[q];
+}
+
+// L = 8, few replicas: a replica is one wave's worth of work, and the wave
+// spends more than half of a half-sweep's instructions on the random words.
+// Here its spins stay in the first wave's registers (lane: word of the row (y,
+// z) = lane, both colours; the rows around it come from the other lanes) and
+// three more waves, on the CU's other SIMDs, compute the words kAhead
+// half-sweeps at a time into LDS while the first one uses the batch before
+// them (the first batch while it finds its slot).
+// Bound by the first wave's own chain: an exchange, a table read and about 40
+// instructions per half-sweep, 0.16 us (+-1; 0.25 in sweep_resident, where one
+// wave does everything), and by the launch.  R = 16, ten sweeps and a step:
+// +-1 9.99 -> 8.19 us, continuous 10.7 -> 8.87.
+constexpr int kWordsAhead = 24;                 // half-sweeps per batch (even)
+// While a CU has SIMDs for the extra waves: R = 512 12.8 -> 11.9 us, R = 768
+// (continuous) 14.4 and 14.0, R = 1024 15.1 and 17.5.
+constexpr int kAheadMaxReplicas = 512;
+
+template <int KIND, bool STEP>
+__global__ __launch_bounds__(256) void sweep_resident_ahead(Lattice lat, StepIn in, int nsweep, int energy) {
+    __shared__ u32x4 words[2][kWordsAhead][64];
+    __shared__ __align__(16) uint32_t sthr[32];   // +-1 thresholds or the continuous-field table
+    const uint32_t r = blockIdx.x, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t t0 = in.r2t ? in.t0 : (uint32_t)gptr(lat.ctrs)[0], c3 = (kTagSweep << 28) | lat.rho;
+    const int steps = 2 * nsweep;
+    auto produce = [&](int h0) {
+        const int n = min(kWordsAhead, steps - h0), buf = (h0 / kWordsAhead) & 1;
+        for (int k = (int)wave - 1; k < n; k += 3) {
+            const Words w = philox10(lane, 2u * t0 + (uint32_t)(h0 + k), r, c3, lat.key0, lat.key1);
+            words[buf][k][lane] = u32x4{w.w0, w.w1, w.w2, w.w3};
+        }
+    };
+    GAS uint32_t *home = (GAS uint32_t *)(gptr(lat.spins) + (size_t)r * 512u) + lane;
+    GAS const uint8_t *fbits = gptr(lat.fbits);
+    GAS const float *fraw = gptr(lat.fraw);
+    uint32_t S[2] = {0u, 0u}, F4[2] = {0u, 0u};
+    f32x4 HF[2];
+    if (wave == 0u) {
+#pragma unroll
+        for (uint32_t c = 0; c < 2; ++c) {
+            S[c] = home[64u * c];
+            if (KIND == 0)
+                F4[c] = ((GAS const uint32_t *)fbits)[64u * c + lane];
+            else
+                HF[c] = ((GAS const f32x4 *)gptr(lat.fhf))[64u * c + lane];
+        }
+        stage_table<KIND, STEP>(lat, in, r, true, sthr);
+    } else {
+        produce(0);
+    }
+    __syncthreads();
+    const uint32_t never = KIND == 0 ? __builtin_amdgcn_readfirstlane(sthr[31]) : 0u;
+    // lanes of the rows around (byte addresses), and the byte order that puts
+    // the x neighbours of colour 0 below its sites (colour 1: the other one)
+    const int yp = (int)(4u * ((lane & 56u) | ((lane + 1u) & 7u))), ym = (int)(4u * ((lane & 56u) | ((lane - 1u) & 7u)));
+    const int zp = (int)(4u * ((lane + 8u) & 63u)), zm = (int)(4u * ((lane - 8u) & 63u));
+    const bool odd = ((lane ^ (lane >> 3)) & 1u) != 0u;
+    const uint32_t sel0 = odd ? 0x00030201u : 0x02010003u, sel1 = odd ? 0x02010003u : 0x00030201u;
+    auto counts = [&](uint32_t w, uint32_t sel) {
+        return w + __builtin_amdgcn_perm(w, w, sel) + (uint32_t)__builtin_amdgcn_ds_bpermute(yp, (int)w) +
+               (uint32_t)__builtin_amdgcn_ds_bpermute(ym, (int)w) + (uint32_t)__builtin_amdgcn_ds_bpermute(zp, (int)w) +
+               (uint32_t)__builtin_amdgcn_ds_bpermute(zm, (int)w);
+    };
+    for (int h0 = 0; h0 < steps; h0 += kWordsAhead) {
+        if (wave == 0u) {
+            const u32x4 *wd = &words[(h0 / kWordsAhead) & 1][0][lane];
+            const int n = min(kWordsAhead, steps - h0);
+            u32x4 next = wd[0];
+            for (int k = 0; k < n; k += 2) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const Words rw = {next.x, next.y, next.z, next.w};
+                    next = wd[64 * min(k + c + 1, n - 1)];
+                    const uint32_t U = counts(S[1 - c], c ? sel1 : sel0);
+                    if (KIND == 1)
+                        S[c] ^= continuous_flips(sthr, U, S[c], HF[c], rw);
+                    else if (never != 0u)
+                        S[c] ^= bimodal_flips<true>(sthr, U, S[c], F4[c], rw, never);
+                    else
+                        S[c] ^= bimodal_flips<false>(sthr, U, S[c], F4[c], rw, 0u);
+                }
+            }
+        } else if (h0 + kWordsAhead < steps) {
+            produce(h0 + kWordsAhead);
+        }
+        __syncthreads();
+    }
+    if (energy) {
+        int ksum = 0, upsum = 0, eqsum = 0, n = 0;
+        double fsum = 0.0;
+        if (wave == 0u) {
+            const uint32_t S1[1] = {S[1]}, W[1] = {S[0]}, U[1] = {counts(S[0], sel1)}, F1[1] = {F4[1]};
+            chunk_energy<KIND, 1>(lat, S1, W, U, F1, fbits, fraw + 256, fraw, 4u * lane, ksum, upsum, eqsum, fsum);
+            n = 4;
+        }
+        block_partial<KIND>(gptr(in.r2t ? in.part_out : lat.part) + (size_t)r * 3, n, ksum, upsum, eqsum, fsum);
+    }
+    if (wave == 0u) {
+        home[0] = S[0];
+        home[64] = S[1];
+    }
 }
 
 // ---------------------------------------------------------------------
@@ -2452,6 +2554,13 @@ static void launch_res_nw(const Launch &ln, const Lattice &lat0, const StepIn &i
         if (b1 < b0 && (long long)ln.nblocks > cus * b1) one = false;
     }
     const bool step = !BATCH && in.part != nullptr;
+    if (!BATCH && NW == 1 && ln.L == 8 && ln.wg == 64 && ln.nblocks <= kAheadMaxReplicas) {
+        if (step)
+            hipLaunchKernelGGL((sweep_resident_ahead<KIND, true>), grid, dim3(256), 0, s, lat0, in, nsweep, energy);
+        else
+            hipLaunchKernelGGL((sweep_resident_ahead<KIND, false>), grid, dim3(256), 0, s, lat0, in, nsweep, energy);
+        return;
+    }
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, block, lds, s, lat0, ln.lats, ln.map, in, nsweep, energy);
     };

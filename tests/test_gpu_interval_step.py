@@ -153,3 +153,35 @@ def test_default_shapes(rfim_mod, L, R, bimodal, gaussian, kind):
         g.close()
     for other in out[1:]:
         assert np.array_equal(out[0][0], other[0]) and np.array_equal(out[0][1], other[1])
+
+
+@pytest.mark.parametrize("R", [1, 3, 512, 513])
+@pytest.mark.parametrize("hot", [True, False])
+def test_l8_intervals_of_every_length(rfim_mod, oracle_mod, R, hot):
+    """L = 8 around the batches of random words (12 sweeps) and the largest
+    ladder that uses them; cold: temperatures at which classes never flip."""
+    f = W.bimodal_fields(8, [106, R])
+    T = ladder(R, 8) if hot else np.linspace(0.03, 0.6, R)
+    g, o = make_pair(rfim_mod, oracle_mod, 8, R, 1.0, 1.5, f, T, seed=7)
+    for n, every in ((12, 12), (13, 13), (50, 25), (24, 24), (31, 0), (2, 1)):
+        g.sweep(n, every)
+        o.sweep(n, every)
+        assert_same_state(g, o, "R=%d (%d, %d)" % (R, n, every))
+    g.close()
+    o.close()
+
+
+@pytest.mark.parametrize("R", [2, 512])
+def test_l8_continuous_fields_do_not_depend_on_the_shape(rfim_mod, R):
+    f = W.gaussian_fields(8, [107, R])
+    out = []
+    for shape in (None, (1, 1, 128)):
+        g = rfim_mod.Rfim(8, R, 1.0, 1.5, f, ladder(R, 8), seed=9)
+        if shape:
+            g.set_launch_shape(*shape)
+        for n, every in ((12, 12), (13, 13), (50, 25), (31, 0)):
+            g.sweep(n, every)
+        out.append((g.spins(), g.perm()))
+        g.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
