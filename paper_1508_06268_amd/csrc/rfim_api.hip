@@ -635,14 +635,12 @@ rfim_dev::Launch single_launch(const rfim *h) {
 }
 
 int reset_stats(rfim *h) {
-    HIPCHK(hipMemsetAsync(h->d_att, 0, (size_t)h->R_cap * 8, h->stream));
-    HIPCHK(hipMemsetAsync(h->d_acc, 0, (size_t)h->R_cap * 8, h->stream));
+    HIPCHK(rfim_dev::launch_clear(h->d_att, (size_t)h->R_cap, h->d_acc, (size_t)h->R_cap, h->stream));
     return RFIM_OK;
 }
 
 int reset_obs(rfim *h) {
-    HIPCHK(hipMemsetAsync(h->d_obs, 0, (size_t)h->R_cap * 6 * sizeof(double), h->stream));
-    if (h->d_fobs) HIPCHK(hipMemsetAsync(h->d_fobs, 0, (size_t)h->R_cap * 2 * sizeof(double), h->stream));
+    HIPCHK(rfim_dev::launch_clear(h->d_obs, (size_t)h->R_cap * 6, h->d_fobs, h->d_fobs ? (size_t)h->R_cap * 2 : 0, h->stream));
     return RFIM_OK;
 }
 
@@ -1568,7 +1566,7 @@ int rfim_set_measure(rfim_t *h, int flags) {
         }
         HIPCHK(hipMemcpyAsync(h->d_trig, trig.data(), trig.size() * sizeof(double), hipMemcpyHostToDevice,
                               h->stream));
-        HIPCHK(hipMemsetAsync(h->d_fobs, 0, Rc * 2 * sizeof(double), h->stream));
+        HIPCHK(rfim_dev::launch_clear(h->d_fobs, Rc * 2, nullptr, 0, h->stream));
         HIPCHK(hipStreamSynchronize(h->stream));
     }
     h->measure = flags;

@@ -237,6 +237,8 @@ struct CopyOut {
     uint32_t *done = nullptr;
 };
 unsigned copy_out_flags(const CopyOut &c);
+// Zeros to two arrays of 8-byte words (either may be empty).
+hipError_t launch_clear(void *a, size_t na, void *b, size_t nb, hipStream_t s);
 hipError_t launch_copy_out(const CopyOut &c, hipStream_t s);
 // Configurations (+-1, natural site order; sites first .. first + count - 1 of
 // the replicas' [R][N], both multiples of 64 or of a replica) to and from

@@ -2081,6 +2081,14 @@ __device__ __forceinline__ void signal_done(uint32_t *done, bool wrote) {
     if (threadIdx.x == 0) __hip_atomic_store(done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Two arrays of a handle's counters or sums to zero in one launch (a memset
+// call per array took 2.6 us each to issue, a launch takes 2.7).
+__global__ __launch_bounds__(256) void clear_kernel(uint64_t *a, uint32_t na, uint64_t *b, uint32_t nb) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i < na) a[i] = 0ull;
+    if (i < nb) b[i] = 0ull;
+}
+
 // Device arrays to pinned host memory, in one launch.
 __global__ __launch_bounds__(256) void copy_out_kernel(CopyOut c) {
     const uint32_t q = blockIdx.y, n = c.words[q];
@@ -2893,6 +2901,14 @@ hipError_t launch_readout(const Lattice &lat0, const Readout &out, hipStream_t s
     const hipError_t e = launch_energy(lat, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kExchangeThreads), 0, s, lat, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear(void *a, size_t na, void *b, size_t nb, hipStream_t s) {
+    const size_t most = std::max(na, nb);
+    if (most == 0) return hipSuccess;
+    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)((most + 255) / 256)), dim3(256), 0, s, (uint64_t *)a, (uint32_t)na,
+                       (uint64_t *)b, (uint32_t)nb);
     return hipGetLastError();
 }
 
