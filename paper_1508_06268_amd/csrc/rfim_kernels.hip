@@ -1352,11 +1352,10 @@ __global__ __launch_bounds__(256) void sweep_resident_ahead(Lattice lat, StepIn 
 // the test is uniform per wave.  Every size is a power of two: no divisions.
 //
 // Bound by its fixed part: of 9.2 us a launch (L = 32, R = 64, two sweeps) the
-// four half-sweeps' instructions are about 3 us; the rest is the launch, the
-// instruction fetch, staging and write-back.  An interval of ten sweeps
-// 46.7 -> 45.9 us without the divisions.  The first half-sweep's random words
-// made while the box is being staged: 47.4 (a peeled half-sweep is more code
-// to fetch).
+// four half-sweeps' instructions are about 3 us; the rest is the launch,
+// staging, barriers and write-back.  An interval of ten sweeps 46.7 -> 45.9 us
+// without the divisions.  The first half-sweep peeled, its random words made
+// while the box is being staged: 47.4.
 // ---------------------------------------------------------------------
 template <int KIND, int NP, bool STEP>
 __global__ __launch_bounds__(1024) void sweep_slabs(Lattice lat, StepIn in, const uint8_t *__restrict__ src,
@@ -1749,7 +1748,9 @@ __device__ __forceinline__ void bits_planes(uint32_t p, uint32_t W, uint32_t Wn,
 // never flip (+-1 fields), checked per block; the common case runs
 // without that check.  (Interleaving the blocks' Philox chains by hand,
 // two, four or eight at a time, was no faster: the sweep is bound by
-// instruction issue, not by the chains' latency.)
+// instruction issue, not by the chains' latency.  Nor was a loop of one, two
+// or four blocks a turn, less code to fetch: L = 64, R = 192 21.6 us a sweep
+// unrolled, 22.2 to 22.5 so.)
 template <int KIND, bool NEV>
 __device__ __forceinline__ uint32_t word_flips(const uint32_t *sthr, uint32_t never, const uint32_t (&Acls)[8],
                                                const f32x4 (&HF)[8], uint32_t w, uint32_t m0v, uint32_t c1w,
