@@ -1233,7 +1233,7 @@ __global__ __launch_bounds__(1024) void sweep_resident(Lattice lat0, const Latti
 // spends more than half of a half-sweep's instructions on the random words.
 // Here its spins stay in the first wave's registers (lane: word of the row (y,
 // z) = lane, both colours; the rows around it come from the other lanes) and
-// three more waves, on the CU's other SIMDs, compute the words kAhead
+// three more waves, on the CU's other SIMDs, compute the words kWordsAhead
 // half-sweeps at a time into LDS while the first one uses the batch before
 // them (the first batch while it finds its slot).
 // Bound by the first wave's own chain: an exchange, a table read and about 40
@@ -2090,8 +2090,8 @@ __device__ __forceinline__ void signal_done(uint32_t *done, bool wrote) {
     if (threadIdx.x == 0) __hip_atomic_store(done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Two arrays of a handle's counters or sums to zero in one launch (a memset
-// call per array took 2.6 us each to issue, a launch takes 2.7).
+// Two arrays of a handle's counters or sums to zero in one launch, 2.7 us to
+// issue (a memset call took 2.6 us for each array).
 __global__ __launch_bounds__(256) void clear_kernel(uint64_t *a, uint32_t na, uint64_t *b, uint32_t nb) {
     const uint32_t i = blockIdx.x * 256u + threadIdx.x;
     if (i < na) a[i] = 0ull;
@@ -2122,8 +2122,8 @@ __global__ __launch_bounds__(256) void copy_out_kernel(CopyOut c) {
 // What an energy kernel does with a workgroup's sums: the partial of block
 // blockIdx.x of replica r or, where the workgroup took the whole replica
 // (WHOLE), its energy and magnetisation for the reader: one launch less (a
-// call at L = 16, R = 32 that took 18 us takes 11.5 with it and the polled end;
-// L = 32, R = 64 the same).
+// call at L = 16, R = 32 that took 18 us takes 12 with it and the polled end;
+// L = 32, R = 64 18.9 and 15.5).
 constexpr int kWholeEnergyThreads = 1024;
 
 template <int KIND, bool WHOLE>
