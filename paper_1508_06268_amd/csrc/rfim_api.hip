@@ -71,16 +71,16 @@ hipError_t create_lane_stream(hipStream_t *s) {
 // stream) and shared by every handle issuing on that stream, reference
 // counted.  Each call forks from and joins back into its handle stream, so
 // handles sharing a stream also share its order on the second stream.  A
-// second stream that no handle holds any more stays alive and is bound to
-// the next handle stream on its device that needs one: a loop that creates
-// and destroys handles one at a time then reuses one hardware queue instead
-// of setting up a new one (4 ms) per handle.  Their number is the largest
-// number of handle streams in use at once on a device.  The ones that nobody
-// holds go when a batch or pool is made: beside a stream with a queue of its
-// own, even an idle one, the lanes of batches run worse side by side (with one
-// left over by an L = 64 handle, against without: batch of 64 9.9 and 9.1 ms,
-// served requests 54 and 41 ms, Fourier study 7.1 and 3.8 ms, and afterwards
-// the two streams of another L = 64 handle 7.7 and 4.5 ms).
+// second stream that no handle holds any more stays alive and is bound to the
+// next handle stream on its device that needs one and runs beside it: a loop
+// that creates and destroys handles one at a time then reuses one hardware
+// queue instead of setting up a new one (4 ms) per handle.  Their number is the
+// largest number of handle streams in use at once on a device, and up to
+// kMaxIdleSides more.  The ones that nobody holds go when a batch or pool is
+// made: beside a stream with a queue of its own, even an idle one, the lanes of
+// batches run worse side by side (with one left over by an L = 64 handle,
+// against without: batch of 64 9.9 and 9.1 ms, served requests 54 and 41 ms,
+// Fourier study 7.1 and 3.8 ms).
 struct SideStream {
     hipStream_t main;
     int device;
@@ -90,12 +90,46 @@ struct SideStream {
 std::mutex g_side_mu;
 std::vector<SideStream> g_side;
 
+__global__ void nothing_kernel() {}
+
+// Whether launches on two streams run side by side.  Hardware queues that share
+// a pipe of the command processor take turns instead, and which do depends on
+// every stream the process made before: on such a pair a sweep of L = 64,
+// R = 128 takes 69 us, on others 18 to 22 (of 90 handles made among batches 18
+// had one, of 180 none since pairs are tried).  A few empty launches on both in turn tell: 27 us side by side,
+// 110 to 130 in turns.  Taken for good where it cannot be tried (work is
+// queued on `main`, or it is being captured).
+bool side_by_side(hipStream_t main, hipStream_t side) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(main, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone ||
+        hipStreamQuery(main) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    for (int tries = 0; tries < 3; ++tries) {       // the first may wait for a queue to be set up
+        const auto t0 = std::chrono::steady_clock::now();
+        for (int q = 0; q < 6; ++q) {
+            hipLaunchKernelGGL(nothing_kernel, dim3(1), dim3(64), 0, main);
+            hipLaunchKernelGGL(nothing_kernel, dim3(1), dim3(64), 0, side);
+        }
+        if (hipStreamSynchronize(main) != hipSuccess || hipStreamSynchronize(side) != hipSuccess) {
+            (void)hipGetLastError();
+            return true;
+        }
+        if (std::chrono::steady_clock::now() - t0 < std::chrono::microseconds(60)) return true;
+    }
+    return false;
+}
+
+// No more second streams are made while this many wait for a handle.
+constexpr size_t kMaxIdleSides = 4;
+
 hipError_t acquire_side_stream(hipStream_t main, hipStream_t *side) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     std::lock_guard<std::mutex> lock(g_side_mu);
-    SideStream *idle = nullptr;
+    std::vector<SideStream *> idle;
     for (auto &s : g_side) {
         if (s.device != dev) continue;
         if (s.main == main && s.refs > 0) {
@@ -103,19 +137,28 @@ hipError_t acquire_side_stream(hipStream_t main, hipStream_t *side) {
             *side = s.side;
             return hipSuccess;
         }
-        if (s.refs == 0 && (!idle || s.main == main)) idle = &s;
+        if (s.refs == 0) idle.push_back(&s);
     }
-    if (idle) {
-        idle->main = main;
-        idle->refs = 1;
-        *side = idle->side;
+    std::stable_partition(idle.begin(), idle.end(), [&](const SideStream *s) { return s->main == main; });
+    auto bind = [&](SideStream *s) {
+        s->main = main;
+        s->refs = 1;
+        *side = s->side;
         return hipSuccess;
+    };
+    for (SideStream *s : idle)
+        if (side_by_side(main, s->side)) return bind(s);
+    // New ones until one does; the others stay, idle, since the queues are dealt
+    // out to the pipes again when one goes.
+    for (size_t waiting = idle.size(); waiting < kMaxIdleSides; ++waiting) {
+        hipStream_t q = nullptr;
+        if ((e = create_lane_stream(&q)) != hipSuccess) break;
+        g_side.push_back({main, dev, q, 0});
+        if (side_by_side(main, q)) return bind(&g_side.back());
     }
-    hipStream_t q = nullptr;
-    if ((e = create_lane_stream(&q)) != hipSuccess) return e;
-    g_side.push_back({main, dev, q, 1});
-    *side = q;
-    return hipSuccess;
+    for (auto &s : g_side)
+        if (s.device == dev && s.refs == 0) return bind(&s);
+    return e;
 }
 
 void drop_idle_side_streams() {

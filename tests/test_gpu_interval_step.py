@@ -185,3 +185,38 @@ def test_l8_continuous_fields_do_not_depend_on_the_shape(rfim_mod, R):
         g.close()
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("seed", [1, 2])
+def test_second_streams_among_batches(rfim_mod, seed):
+    """Two-stream handles on their own and on torch's streams, between batches
+    that come and go (whose creation drops the idle second streams): each ends
+    as it does on one stream."""
+    import torch
+
+    rng = np.random.default_rng([108, seed])
+    f = W.bimodal_fields(64, [108, 64])
+    T = W.linear_temps(8, 1.5, 4.0)
+    one = rfim_mod.Rfim(64, 8, 1.0, 1.5, f, T, seed=3)
+    one.set_concurrency(1)
+    one.sweep(12, 4)
+    want = one.spins(), one.perm(), one.energies()
+    kept = []
+    for q in range(8):
+        if rng.random() < 0.5:
+            specs = [W.Realization(L=L, R=4, J=1.0, h=1.0, fields=W.bimodal_fields(L, [109, L]), temps=W.linear_temps(4, 1.5, 4.0),
+                                   seed=1, realization=L, every=2) for L in (8, 16, 32)]
+            b = rfim_mod.Batch(specs)
+            b.sweep(4, 2)
+            b.synchronize()
+            b.close()
+        g = rfim_mod.Rfim(64, 8, 1.0, 1.5, f, T, seed=3, stream=torch.cuda.Stream() if rng.random() < 0.5 else None)
+        g.set_concurrency(2)
+        g.sweep(12, 4)
+        for a, b in zip((g.spins(), g.perm(), g.energies()), want):
+            assert np.array_equal(a, b)
+        kept.append(g)
+        if len(kept) > 3:
+            kept.pop(0).close()
+    for g in kept + [one]:
+        g.close()
