@@ -339,6 +339,7 @@ struct rfim {
     int nblk = 1;
     int mode = 0, nw = 0, wg = 0;   // launch shape (see rfim_set_launch_shape)
     rfim_dev::BoxPlan box = {0, 0}; // boxes (L not a power of two), planes = 0: none
+    bool recorded = false;          // a sweep call has been captured: its replays advance the device's counters alone
     // device copy of lattice() and the workgroup maps of the sweep launches
     Lattice lat_host;
     Lattice *d_lat = nullptr;
@@ -1057,14 +1058,18 @@ int sweep_impl(rfim *h, int64_t n, int every) {
     // (256 CUs, one workgroup each at least): a longer one gains little from
     // the launch saved and runs better with the registers the step takes.
     // A captured call takes its counters from the device, so that its replays
-    // go on where the last one ended, and sweeps in place where it can.
+    // go on where the last one ended, and sweeps in place where it can.  The
+    // replays move the device's counters but not the host's, so from the first
+    // captured call on every call of the handle takes them from the device:
+    // no step inside the next interval's launch, whose counters are the host's.
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     HIPCHK(hipStreamIsCapturing(h->stream, &capture));
     const bool captured = capture != hipStreamCaptureStatusNone;
+    if (captured) h->recorded = true;
     const bool whole = h->box.planes >= h->L;           // boxes of whole replicas: in place, any number of sweeps
     const bool boxes = h->box.planes > 0 && (whole || !captured);
     const bool slabs = pow2 && h->mode >= 2 && !captured;
-    const bool lazy = !captured && !tiled && !bitsm && !h->measure && h->nblk <= rfim_dev::kMaxStepPartials &&
+    const bool lazy = !h->recorded && !tiled && !bitsm && !h->measure && h->nblk <= rfim_dev::kMaxStepPartials &&
                       (long long)h->R * h->nblk <= 256 &&
                       (pow2 ? h->mode >= 1 : boxes || rfim_dev::generic_resident(h->L));
     StepBuffers sb(h);

@@ -220,3 +220,39 @@ def test_second_streams_among_batches(rfim_mod, seed):
             kept.pop(0).close()
     for g in kept + [one]:
         g.close()
+
+
+def captured_between_ordinary_calls(rfim_mod, ref, L, R, f):
+    """A captured call, replayed before, between and after ordinary calls of
+    one launch an interval and of an odd number of them: all of them are one
+    chain, the one that ref runs in ordinary calls alone."""
+    import torch
+
+    stream = torch.cuda.Stream()
+    g = rfim_mod.Rfim(L, R, 1.0, 1.5, f, ladder(R, L), seed=L, stream=stream)
+    g.sweep(4, 2)
+    ref.sweep(4, 2)
+    g.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream, capture_error_mode="thread_local"):
+        g.sweep(6, 2)
+    for what in ("replay", "replay", (6, 2), "replay", (3, 1), (5, 0), "replay", "replay", (4, 4), (2, 1), "replay"):
+        if what == "replay":
+            graph.replay()
+            torch.cuda.synchronize()
+            ref.sweep(6, 2)
+        else:
+            g.sweep(*what)
+            ref.sweep(*what)
+        assert np.array_equal(g.spins(), ref.spins()) and np.array_equal(g.perm(), ref.perm()), what
+        assert np.array_equal(g.energies(), ref.energies()), what
+    for a, b in zip(g.exchange_stats(), ref.exchange_stats()):
+        assert np.array_equal(a, b)
+    g.close()
+    ref.close()
+
+
+@pytest.mark.parametrize("L,R", [(8, 5), (16, 3), (22, 4), (12, 40)])
+def test_ordinary_calls_between_replays_in_place(rfim_mod, oracle_mod, L, R):
+    f = W.bimodal_fields(L, [110, L])
+    captured_between_ordinary_calls(rfim_mod, oracle_mod.Oracle(L, R, 1.0, 1.5, f, ladder(R, L), seed=L), L, R, f)
