@@ -320,6 +320,7 @@ struct rfim {
     // d_spins is always the current one, d_spins_alt the other, and
     // d_spins_own the second buffer as allocated (freed with the handle)
     uint8_t *d_spins_alt = nullptr, *d_spins_own = nullptr;
+    uint8_t *d_spins_recorded = nullptr;    // the buffer that captured sweep calls work in, null before the first
     rfim_alloc_t alloc = {nullptr, nullptr, nullptr};   // device memory provider (rfim_create_ex)
     // optional Fourier measurement (rfim_set_measure)
     int measure = 0;
@@ -339,7 +340,6 @@ struct rfim {
     int nblk = 1;
     int mode = 0, nw = 0, wg = 0;   // launch shape (see rfim_set_launch_shape)
     rfim_dev::BoxPlan box = {0, 0}; // boxes (L not a power of two), planes = 0: none
-    bool recorded = false;          // a sweep call has been captured: its replays advance the device's counters alone
     // device copy of lattice() and the workgroup maps of the sweep launches
     Lattice lat_host;
     Lattice *d_lat = nullptr;
@@ -1061,15 +1061,16 @@ int sweep_impl(rfim *h, int64_t n, int every) {
     // go on where the last one ended, and sweeps in place where it can.  The
     // replays move the device's counters but not the host's, so from the first
     // captured call on every call of the handle takes them from the device:
-    // no step inside the next interval's launch, whose counters are the host's.
+    // no step inside the next interval's launch, whose counters are the host's;
+    // and every call ends in the spin buffer that the replays work in.
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     HIPCHK(hipStreamIsCapturing(h->stream, &capture));
     const bool captured = capture != hipStreamCaptureStatusNone;
-    if (captured) h->recorded = true;
+    if (captured && !h->d_spins_recorded) h->d_spins_recorded = h->d_spins;
     const bool whole = h->box.planes >= h->L;           // boxes of whole replicas: in place, any number of sweeps
     const bool boxes = h->box.planes > 0 && (whole || !captured);
     const bool slabs = pow2 && h->mode >= 2 && !captured;
-    const bool lazy = !h->recorded && !tiled && !bitsm && !h->measure && h->nblk <= rfim_dev::kMaxStepPartials &&
+    const bool lazy = !h->d_spins_recorded && !tiled && !bitsm && !h->measure && h->nblk <= rfim_dev::kMaxStepPartials &&
                       (long long)h->R * h->nblk <= 256 &&
                       (pow2 ? h->mode >= 1 : boxes || rfim_dev::generic_resident(h->L));
     StepBuffers sb(h);
@@ -1198,6 +1199,12 @@ int sweep_impl(rfim *h, int64_t n, int every) {
     if (split) {
         HIPCHK(hipEventRecord(h->ev_join, h->aux));
         HIPCHK(hipStreamWaitEvent(h->stream, h->ev_join, 0));
+    }
+    // (slabs and boxes of less than a replica: an odd number of launches)
+    if (h->d_spins_recorded && h->d_spins != h->d_spins_recorded) {
+        HIPCHK(hipMemcpyAsync(h->d_spins_recorded, h->d_spins, (size_t)h->R * h->N, hipMemcpyDeviceToDevice, h->stream));
+        std::swap(h->d_spins, h->d_spins_alt);
+        h->lat_host = h->lattice();
     }
     return RFIM_OK;
 }

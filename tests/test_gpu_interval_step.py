@@ -222,7 +222,7 @@ def test_second_streams_among_batches(rfim_mod, seed):
         g.close()
 
 
-def captured_between_ordinary_calls(rfim_mod, ref, L, R, f):
+def captured_between_ordinary_calls(rfim_mod, ref, L, R, f, shape=None):
     """A captured call, replayed before, between and after ordinary calls of
     one launch an interval and of an odd number of them: all of them are one
     chain, the one that ref runs in ordinary calls alone."""
@@ -230,6 +230,8 @@ def captured_between_ordinary_calls(rfim_mod, ref, L, R, f):
 
     stream = torch.cuda.Stream()
     g = rfim_mod.Rfim(L, R, 1.0, 1.5, f, ladder(R, L), seed=L, stream=stream)
+    if shape:
+        g.set_launch_shape(*shape)
     g.sweep(4, 2)
     ref.sweep(4, 2)
     g.synchronize()
@@ -256,3 +258,18 @@ def captured_between_ordinary_calls(rfim_mod, ref, L, R, f):
 def test_ordinary_calls_between_replays_in_place(rfim_mod, oracle_mod, L, R):
     f = W.bimodal_fields(L, [110, L])
     captured_between_ordinary_calls(rfim_mod, oracle_mod.Oracle(L, R, 1.0, 1.5, f, ladder(R, L), seed=L), L, R, f)
+
+
+@pytest.mark.parametrize("kind", ["b", "g"])
+@pytest.mark.parametrize("L,R", [(16, 3), (32, 3), (24, 3), (28, 2), (40, 3), (48, 30)])
+def test_ordinary_calls_between_replays_two_buffers(rfim_mod, oracle_mod, L, R, kind):
+    """Slabs and boxes, whose ordinary launches go from one spin buffer to the
+    other (L = 16: slabs set by hand; +-1 fields against the oracle, continuous
+    ones against a handle without a captured call)."""
+    if kind == "b":
+        f = W.bimodal_fields(L, [111, L])
+        ref = oracle_mod.Oracle(L, R, 1.0, 1.5, f, ladder(R, L), seed=L)
+    else:
+        f = W.gaussian_fields(L, [111, L])
+        ref = rfim_mod.Rfim(L, R, 1.0, 1.5, f, ladder(R, L), seed=L)
+    captured_between_ordinary_calls(rfim_mod, ref, L, R, f, (2, 2, 512) if L == 16 else None)
