@@ -1890,6 +1890,7 @@ struct rfim_batch {
     uint2 *d_fmap = nullptr;
     size_t fmap_cap = 0;
     int fchunks = 0, freplicas = 0, fmax_l = 0;
+    bool by_item = false;               // the current call is being captured: Fourier launches per item
     // side streams for classes (and halves of large streaming classes) that
     // run concurrently within an exchange interval; events fork them from
     // and join them back into `stream`
@@ -2019,13 +2020,25 @@ int batch_build(rfim_batch *b) {
     return RFIM_OK;
 }
 
+std::vector<int> batch_flags(const rfim_batch *b) {
+    std::vector<int> flags(b->items.size());
+    for (size_t i = 0; i < flags.size(); ++i) flags[i] = b->items[i]->measure;
+    return flags;
+}
+
 // Descriptors and maps of the Fourier launches for the items' measurement
 // flags, when those changed since the last call (a captured interval is then
-// dropped).  Two launches measure every item of the batch.
+// dropped).  Two launches measure every item of the batch.  A call that is
+// being captured can neither wait nor copy here, and its replays may outlive
+// the maps: it records the launches of each item, which take nothing but the
+// item's own buffers.
 int batch_sync_measure(rfim_batch *b) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    HIPCHK(hipStreamIsCapturing(b->stream, &capture));
+    b->by_item = capture != hipStreamCaptureStatusNone;
+    if (b->by_item) return RFIM_OK;
     const int n = (int)b->items.size();
-    std::vector<int> flags(n);
-    for (int i = 0; i < n; ++i) flags[i] = b->items[i]->measure;
+    const std::vector<int> flags = batch_flags(b);
     if (flags == b->measured) return RFIM_OK;
     if (b->measured.empty() && std::all_of(flags.begin(), flags.end(), [](int f) { return f == 0; })) {
         b->measured = flags;        // nothing measured since the descriptors were made
@@ -2271,8 +2284,15 @@ int batch_segment(rfim_batch *b, int m, bool exch) {
             if (!class_fused(b, c))
                 for (int i : c.members) HIPCHK(rfim_dev::launch_energy(b->items[i]->lattice(), b->stream));
         HIPCHK(rfim_dev::launch_exchange(b->d_lats, (int)b->items.size(), m, rfim_dev::StepIn{}, b->stream));
-        HIPCHK(rfim_dev::launch_fourier_batch(b->d_lats, b->d_fmap, b->fchunks, b->d_fmap + b->fchunks, b->freplicas,
-                                              b->fmax_l, b->stream));
+        if (b->by_item) {
+            for (rfim *h : b->items) {
+                int rc;
+                if ((rc = measure_after_exchange(h, b->stream))) return rc;
+            }
+        } else {
+            HIPCHK(rfim_dev::launch_fourier_batch(b->d_lats, b->d_fmap, b->fchunks, b->d_fmap + b->fchunks, b->freplicas,
+                                                  b->fmax_l, b->stream));
+        }
     } else {
         for (rfim *h : b->items) HIPCHK(rfim_dev::launch_advance(h->lattice(), m, b->stream));
     }
@@ -2496,7 +2516,8 @@ int rfim_batch_sweep(rfim_batch_t *b, int64_t n, int exchange_every) {
         const bool exch = every > 0 && m == to_next;
         int rc;
         if (exch && m == every && batch_prefers_graph(b, every)) {
-            if (b->graph_every != every && (rc = batch_capture(b, every))) return rc;
+            const bool stale = b->graph_every != every || (b->by_item && b->measured != batch_flags(b));
+            if (stale && (rc = batch_capture(b, every))) return rc;
             HIPCHK(hipGraphLaunch(b->graph, b->stream));
         } else if ((rc = batch_segment(b, m, exch))) {
             return rc;

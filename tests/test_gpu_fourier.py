@@ -100,3 +100,32 @@ def test_pool_items_measured_across_membership_changes(rfim_mod):
     p.step(2, 2)
     assert np.array_equal(p.item(c).fourier(), _single(rfim_mod, specs[1], 0, 8))
     p.close()
+
+
+def test_captured_step_does_not_depend_on_later_flags(rfim_mod):
+    """A pool step captured right after an item's measurement was turned on,
+    and replayed after another item's was, whose steps lay the launches of the
+    whole pool out anew: the recorded items are measured, at each replay."""
+    import torch
+
+    specs = [_spec(16, 4, 9), _spec(32, 3, 10), _spec(64, 2, 11)]
+    stream = torch.cuda.Stream()
+    p = rfim_mod.Pool(1 << 30, stream=stream)
+    p.set_shape(64, rfim_mod.FIELDS_BIMODAL, 0, 4, 128)
+    ids = [p.admit(w) for w in specs]
+    p.step(4, 2)
+    for q in (0, 2):
+        p.item(ids[q]).set_measure(rfim_mod.MEASURE_FOURIER)
+    p.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream, capture_error_mode="thread_local"):
+        p.step(2, 2)
+    with torch.cuda.stream(stream):         # the replays in order with the pool's own work
+        graph.replay()
+        p.item(ids[1]).set_measure(rfim_mod.MEASURE_FOURIER)
+        p.step(4, 2)
+        graph.replay()
+        graph.replay()
+    for q, before, after in ((0, 4, 10), (1, 6, 4), (2, 4, 10)):
+        assert np.array_equal(p.item(ids[q]).fourier(), _single(rfim_mod, specs[q], before, after)), q
+    p.close()
