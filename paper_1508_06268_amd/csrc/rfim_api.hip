@@ -195,6 +195,14 @@ void release_side_stream(hipStream_t side) {
 constexpr size_t kPinnedBlock = 4u << 20, kPinnedIdle = 1u << 20;
 constexpr size_t kPinnedKept = 8;
 
+// The host reads the words that end a readout, and the results behind them,
+// while kernels run, without a synchronisation: that takes coherent memory,
+// which hipHostMalloc promises only for this flag (other flags alone leave it to
+// the environment).
+constexpr unsigned kPinnedFlags = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
+static_assert((kPinnedFlags & hipHostMallocCoherent) != 0 && (kPinnedFlags & hipHostMallocNonCoherent) == 0,
+              "polled memory is coherent");
+
 struct PinnedBlock {
     void *p;
     size_t bytes;
@@ -251,7 +259,7 @@ class Pinned {
         }
         size_t want = 64u << 10;
         while (want < bytes) want *= 2;
-        const hipError_t e = hipHostMalloc(&b_.p, want, hipHostMallocPortable);
+        const hipError_t e = hipHostMalloc(&b_.p, want, kPinnedFlags);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             b_.p = nullptr;
