@@ -866,21 +866,22 @@ __device__ __forceinline__ uint32_t any_flips(const Lattice &lat, const FastDiv 
     return block_flips<KIND>(lat, sthr, never, a, f, U, Wown, j0 >> 2, c1, r);
 }
 
-// Half-sweep, one thread per block of four sites, grid (blocks, R).
+// Half-sweep, one thread per block of four sites, the workgroups of replicas
+// r0.. in one row.
 // L = 48, R = 32, +-1 fields: 4.5 us a launch against 12.3 with a division
 // per coordinate and site, byte neighbours and the table read from memory;
 // about 3.5 us of it are the launch.  L = 80, R = 32: 11 us (12.2 without the
 // XCD ranges; several replicas per thread were no faster).
 template <int KIND, bool ROWS>
-__global__ __launch_bounds__(256) void sweep_generic(Lattice lat, FastDiv by_row, FastDiv by_l, FastDiv by_blocks, int colour,
-                                                     int toff) {
+__global__ __launch_bounds__(256) void sweep_generic(Lattice lat, FastDiv by_row, FastDiv by_l, FastDiv by_blocks, int r0,
+                                                     int colour, int toff) {
     __shared__ __align__(16) uint32_t sthr[32];
     // a contiguous range of blocks for each of the 8 XCDs (ids go round-robin
     // to them), so that the planes above and below are in its L2
     const uint32_t per = gridDim.x >> 3;
     const uint32_t blk = blockIdx.x < 8u * per ? (blockIdx.x & 7u) * per + (blockIdx.x >> 3) : blockIdx.x;
-    const uint32_t r = div_by(blk, by_blocks), half = (uint32_t)lat.half, col = (uint32_t)colour;
-    const uint32_t j0 = 4u * ((blk - r * by_blocks.d) * 256u + threadIdx.x);
+    const uint32_t rb = div_by(blk, by_blocks), r = (uint32_t)r0 + rb, half = (uint32_t)lat.half, col = (uint32_t)colour;
+    const uint32_t j0 = 4u * ((blk - rb * by_blocks.d) * 256u + threadIdx.x);
     GAS uint8_t *own = gptr(lat.spins) + (size_t)r * lat.N + (size_t)col * half;
     GAS const uint8_t *oth = gptr((const uint8_t *)lat.spins) + (size_t)r * lat.N + (size_t)(1u - col) * half;
     // the block's loads go out first, the slot's table behind them (its two
@@ -2635,12 +2636,17 @@ static void launch_generic_kind(const Lattice &lat, const StepIn &in, int colour
                                s, lat, in, by_row, by_l, nsweep, energy);
         };
         in.part ? go(sweep_generic_resident<KIND, true>) : go(sweep_generic_resident<KIND, false>);
-    } else if (lat.L % 8 == 0)
-        hipLaunchKernelGGL((sweep_generic<KIND, true>), dim3(nb * (unsigned)lat.R), dim3(256), 0, s, lat, by_row, by_l,
-                           fast_div(nb), colour, toff);
-    else
-        hipLaunchKernelGGL((sweep_generic<KIND, false>), dim3(nb * (unsigned)lat.R), dim3(256), 0, s, lat, by_row, by_l,
-                           fast_div(nb), colour, toff);
+        return;
+    }
+    // a launch has fewer than 2^32 threads in a row: R L^3 from 2^35 on takes several
+    const int most = (int)(0xFFFFFFFFu / 256u / nb);
+    for (int r0 = 0; r0 < lat.R; r0 += most) {
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(nb * (unsigned)std::min(most, lat.R - r0)), dim3(256), 0, s, lat, by_row, by_l,
+                               fast_div(nb), r0, colour, toff);
+        };
+        lat.L % 8 == 0 ? go(sweep_generic<KIND, true>) : go(sweep_generic<KIND, false>);
+    }
 }
 
 static hipError_t launch_generic(const Lattice &lat, const StepIn &in, int colour, int toff, int nsweep, int energy,

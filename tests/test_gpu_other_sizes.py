@@ -6,6 +6,7 @@ continuous fields at most one differs (they are FP32 on the device: about 1 in
 import numpy as np
 import pytest
 
+from helpers import energy_numpy, quench_numpy
 from paper_1508_06268_amd import workloads as W
 from parity_util import assert_same_state, make_pair
 
@@ -53,3 +54,32 @@ def test_continuous_decisions_match_oracle(rfim_mod, oracle_mod, L, R):
     assert np.allclose(g.energies(), E, rtol=1e-12, atol=1e-9)
     g.close()
     o.close()
+
+
+def philox_numpy(c0, c1, c2, c3, key):
+    """Philox4x32-10 of many counters, uint64 arrays of 32-bit words."""
+    M = np.uint64(0xFFFFFFFF)
+    c = [np.broadcast_to(np.asarray(v, dtype=np.uint64), np.shape(c0)) for v in (c0, c1, c2, c3)]
+    k0, k1 = key & 0xFFFFFFFF, key >> 32
+    for _ in range(10):
+        a, b = c[0] * np.uint64(0xD2511F53), c[2] * np.uint64(0xCD9E8D57)
+        c = [(b >> np.uint64(32)) ^ c[1] ^ np.uint64(k0), b & M, (a >> np.uint64(32)) ^ c[3] ^ np.uint64(k1), a & M]
+        k0, k1 = (k0 + 0x9E3779B9) & 0xFFFFFFFF, (k1 + 0xBB67AE85) & 0xFFFFFFFF
+    return np.stack(c, axis=-1)
+
+
+def test_more_sites_than_one_launch_takes(rfim_mod):
+    """R L^3 > 2^35 (35 GB of spins): a half-sweep is two launches, from
+    replica 38836 on (of 432 workgroups of 256 threads each).  So cold that a
+    spin flips only where its energy does not rise, each replica ends where its
+    random start leads."""
+    L, R, seed = 96, 40000, 5
+    f = W.bimodal_fields(L, [98, L])
+    g = rfim_mod.Rfim(L, R, 1.0, 1.5, f, np.linspace(0.010, 0.011, R), seed=seed)
+    g.sweep(1, 0)
+    E, M = g.energies(), g.magnetizations()
+    g.close()
+    for r in (0, 38835, 38836, R - 1):
+        w = philox_numpy(np.arange(L ** 3 // 4), 0, r, 1 << 28, seed)
+        s = quench_numpy(np.where(w.reshape(-1) >= 1 << 31, 1, -1).astype(np.int8), f, L, 1.0, 1.5, 1)
+        assert E[r] == energy_numpy(s, f, L, 1.0, 1.5)[0] and M[r] == int(s.sum(dtype=np.int64)), r
