@@ -1034,7 +1034,8 @@ __device__ __forceinline__ uint32_t plane_counts(const uint8_t *oth, const uint8
 // is the whole replica, periodic in z, without halo planes (any nsweep).
 //
 // A thread keeps one place of the plane and takes every G-th of the active
-// planes (blockDim = G blocks-per-plane).  Bound by instruction issue (104
+// planes (blockDim = G blocks-per-plane, rounded up to whole waves, as the sums
+// over a wave take them).  Bound by instruction issue (104
 // VALU instructions per block of four sites with whole-dword rows; 160 with
 // the place worked out for every block) and, for thin slabs, by the launch
 // and the staging: box_plan weighs them.  us a sweep, boxes against
@@ -1065,8 +1066,10 @@ __global__ __launch_bounds__(1024) void sweep_box(Lattice lat, StepIn in, FastDi
         z -= z >= L ? L : 0u;
         return z - (z >= L ? L : 0u);
     };
-    const uint32_t pg = div_by(threadIdx.x, by_plane), G = blockDim.x / bpp;   // this thread's first plane, planes per step
-    const Place<ROWS> place = place_of<ROWS>(4u * (threadIdx.x - pg * bpp), L, by_row);
+    // this thread's first plane, planes per step; the threads that fill up the
+    // last wave have none
+    const uint32_t G = blockDim.x / bpp, tg = div_by(threadIdx.x, by_plane), pg = tg < G ? tg : 0x10000u;
+    const Place<ROWS> place = place_of<ROWS>(4u * (threadIdx.x - tg * bpp), L, by_row);
     // stage the box: the thread's block of its planes, both colours
     for (uint32_t b = pg; b < P; b += G) {
         const uint32_t at = z_of(b) * plane + place.d;
@@ -2720,7 +2723,7 @@ static void launch_box_form(const Lattice &lat, const StepIn &in, const uint8_t 
     const uint32_t L = (uint32_t)lat.L, slabs = (L + (uint32_t)np - 1u) / (uint32_t)np, bpp = L * L / 8u;
     const bool whole = slabs == 1u;
     const uint32_t active = whole ? L : (uint32_t)(np + 4 * nsweep - 2);     // planes of the largest half-sweep
-    const dim3 grid((unsigned)lat.R * slabs), block(bpp * std::min(1024u / bpp, active));
+    const dim3 grid((unsigned)lat.R * slabs), block((bpp * std::min(1024u / bpp, active) + 63u) & ~63u);
     const FastDiv by_row = fast_div(L / 2u), by_plane = fast_div(bpp), by_slab = fast_div(slabs);
     const size_t lds = box_lds_bytes(lat.L, whole ? lat.L : np + 4 * nsweep);
     auto go = [&](auto kernel) {

@@ -56,6 +56,29 @@ def test_continuous_decisions_match_oracle(rfim_mod, oracle_mod, L, R):
     o.close()
 
 
+@pytest.mark.parametrize("L,R", [(12, 40), (12, 2), (20, 3), (28, 60), (28, 3), (36, 25), (36, 2), (40, 25), (40, 3), (48, 5),
+                                 (52, 2), (60, 3), (72, 2), (22, 3), (26, 2), (90, 1)])
+def test_sampled_energies_are_those_of_the_configurations(rfim_mod, L, R):
+    """The energy that the exchange step samples after a sweep (from the sweep
+    kernels' own sums where they have them) against the energies read of the
+    same configurations, and those against sums in another order: FP64 sums of
+    4 N terms of size 1, J and h |f|, so within 4 N eps of their absolute sum
+    (exact for +-1 fields)."""
+    N = L ** 3
+    for kind, f in (("b", W.bimodal_fields(L, [99, L])), ("g", W.gaussian_fields(L, [99, L]))):
+        g = rfim_mod.Rfim(L, R, 1.0, 1.5, f, W.linear_temps(R, 2.0, 5.0) if R > 1 else np.array([2.0]), seed=L)
+        for n, every in ((3, 3), (5, 8), (1, 1)):
+            g.reset_observables()
+            g.sweep(n, every)
+            obs, E = g.observables(), g.energies()
+            bound = 4 * N * 2.0 ** -53 * (3 * N + 1.5 * float(np.abs(f).sum(dtype=np.float64))) if kind == "g" else 0.0
+            assert np.all(obs[:, 0] == 1) and np.abs(obs[:, 1] - E).max() <= bound
+            assert np.array_equal(obs[:, 3], np.abs(g.magnetizations()))
+            s, perm = g.spins(), g.perm()
+            assert abs(E[R - 1] - energy_numpy(s[perm[R - 1]], f, L, 1.0, 1.5)[0]) <= bound
+        g.close()
+
+
 def philox_numpy(c0, c1, c2, c3, key):
     """Philox4x32-10 of many counters, uint64 arrays of 32-bit words."""
     M = np.uint64(0xFFFFFFFF)
