@@ -67,6 +67,14 @@ hipError_t create_lane_stream(hipStream_t *s) {
     return hipStreamCreateWithFlags(s, hipStreamNonBlocking);
 }
 
+// The host reads the words that end a readout, and the results behind them,
+// while kernels run, without a synchronisation: that takes coherent memory,
+// which hipHostMalloc promises only for this flag (other flags alone leave it to
+// the environment).
+constexpr unsigned kPinnedFlags = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
+static_assert((kPinnedFlags & hipHostMallocCoherent) != 0 && (kPinnedFlags & hipHostMallocNonCoherent) == 0,
+              "polled memory is coherent");
+
 // The second stream of the two-stream sweeps, one per (device, handle
 // stream) and shared by every handle issuing on that stream, reference
 // counted.  Each call forks from and joins back into its handle stream, so
@@ -76,11 +84,13 @@ hipError_t create_lane_stream(hipStream_t *s) {
 // that creates and destroys handles one at a time then reuses one hardware
 // queue instead of setting up a new one (4 ms) per handle.  Their number is the
 // largest number of handle streams in use at once on a device, and up to
-// kMaxIdleSides more.  The ones that nobody holds go when a batch or pool is
-// made: beside a stream with a queue of its own, even an idle one, the lanes of
-// batches run worse side by side (with one left over by an L = 64 handle,
-// against without: batch of 64 9.9 and 9.1 ms, served requests 54 and 41 ms,
-// Fourier study 7.1 and 3.8 ms).
+// kMaxIdleSides more.
+//
+// The device deals its hardware queues out to the four pipes of the command
+// processor in the order in which they were made, and queues that share a pipe
+// take turns.  So no second stream is destroyed while another is in use: the
+// queues made after it would move on by a pipe, onto that of the stream they run
+// beside (a sweep of L = 64, R = 128 that took 18 us took 69 from then on).
 struct SideStream {
     hipStream_t main;
     int device;
@@ -91,6 +101,39 @@ std::mutex g_side_mu;
 std::vector<SideStream> g_side;
 
 __global__ void nothing_kernel() {}
+
+// The runtime shares this many hardware queues (GPU_MAX_HW_QUEUES, 4 unless it
+// is set) among its ordinary streams, makes them as streams first need them and
+// keeps them.  Batches run their lanes on ordinary streams, side by side if each
+// queue has a pipe of its own; with a second stream's queue among them, even an
+// idle one, two of them share a pipe (a Fourier study 9.0 ms, 3.5 without).  So
+// the first batch or pool of several lanes has them all made, by one launch on as
+// many new streams, behind no second stream that is not in use; later ones come
+// after them and do no harm.
+constexpr int kOrdinaryQueues = 4;
+std::vector<int> g_ordinary;        // devices where that is done
+
+void make_ordinary_queues() {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return;
+    std::lock_guard<std::mutex> lock(g_side_mu);
+    if (std::find(g_ordinary.begin(), g_ordinary.end(), dev) != g_ordinary.end()) return;
+    g_ordinary.push_back(dev);
+    if (std::none_of(g_side.begin(), g_side.end(), [&](const SideStream &s) { return s.device == dev && s.refs > 0; }))
+        for (size_t q = g_side.size(); q-- > 0;)
+            if (g_side[q].device == dev) {
+                (void)hipStreamDestroy(g_side[q].side);
+                g_side.erase(g_side.begin() + (long)q);
+            }
+    hipStream_t s[kOrdinaryQueues] = {};
+    for (hipStream_t &q : s) {
+        if (hipStreamCreateWithFlags(&q, hipStreamNonBlocking) != hipSuccess) break;
+        hipLaunchKernelGGL(nothing_kernel, dim3(1), dim3(64), 0, q);
+    }
+    for (hipStream_t q : s)
+        if (q) (void)hipStreamDestroy(q);
+    (void)hipGetLastError();
+}
 
 // Whether launches on two streams run side by side.  Hardware queues that share
 // a pipe of the command processor take turns instead, and which do depends on
@@ -129,48 +172,34 @@ hipError_t acquire_side_stream(hipStream_t main, hipStream_t *side) {
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     std::lock_guard<std::mutex> lock(g_side_mu);
-    std::vector<SideStream *> idle;
-    for (auto &s : g_side) {
+    std::vector<size_t> idle;
+    for (size_t q = 0; q < g_side.size(); ++q) {
+        SideStream &s = g_side[q];
         if (s.device != dev) continue;
         if (s.main == main && s.refs > 0) {
             ++s.refs;
             *side = s.side;
             return hipSuccess;
         }
-        if (s.refs == 0) idle.push_back(&s);
+        if (s.refs == 0) idle.push_back(q);
     }
-    std::stable_partition(idle.begin(), idle.end(), [&](const SideStream *s) { return s->main == main; });
-    auto bind = [&](SideStream *s) {
-        s->main = main;
-        s->refs = 1;
-        *side = s->side;
+    std::stable_partition(idle.begin(), idle.end(), [&](size_t q) { return g_side[q].main == main; });
+    auto bind = [&](size_t q) {
+        g_side[q].main = main;
+        g_side[q].refs = 1;
+        *side = g_side[q].side;
         return hipSuccess;
     };
-    for (SideStream *s : idle)
-        if (side_by_side(main, s->side)) return bind(s);
-    // New ones until one does; the others stay, idle, since the queues are dealt
-    // out to the pipes again when one goes.
-    for (size_t waiting = idle.size(); waiting < kMaxIdleSides; ++waiting) {
+    for (size_t q : idle)
+        if (side_by_side(main, g_side[q].side)) return bind(q);
+    // New ones until one does; the others stay, idle.
+    for (; idle.size() < kMaxIdleSides; idle.push_back(g_side.size() - 1)) {
         hipStream_t q = nullptr;
         if ((e = create_lane_stream(&q)) != hipSuccess) break;
         g_side.push_back({main, dev, q, 0});
-        if (side_by_side(main, q)) return bind(&g_side.back());
+        if (side_by_side(main, q)) return bind(g_side.size() - 1);
     }
-    for (auto &s : g_side)
-        if (s.device == dev && s.refs == 0) return bind(&s);
-    return e;
-}
-
-void drop_idle_side_streams() {
-    std::lock_guard<std::mutex> lock(g_side_mu);
-    for (size_t q = 0; q < g_side.size();) {
-        if (g_side[q].refs == 0) {
-            (void)hipStreamDestroy(g_side[q].side);
-            g_side.erase(g_side.begin() + (long)q);
-        } else {
-            ++q;
-        }
-    }
+    return idle.empty() ? e : bind(idle.front());
 }
 
 // Drops one reference; the stream itself stays for reuse (every call that
@@ -194,14 +223,6 @@ void release_side_stream(hipStream_t side) {
 // at a time, which has waited for its work when it gives the block back.
 constexpr size_t kPinnedBlock = 4u << 20, kPinnedIdle = 1u << 20;
 constexpr size_t kPinnedKept = 8;
-
-// The host reads the words that end a readout, and the results behind them,
-// while kernels run, without a synchronisation: that takes coherent memory,
-// which hipHostMalloc promises only for this flag (other flags alone leave it to
-// the environment).
-constexpr unsigned kPinnedFlags = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
-static_assert((kPinnedFlags & hipHostMallocCoherent) != 0 && (kPinnedFlags & hipHostMallocNonCoherent) == 0,
-              "polled memory is coherent");
 
 struct PinnedBlock {
     void *p;
@@ -2138,6 +2159,7 @@ bool class_fused(const rfim_batch *b, const rfim_batch::Class &c) {
 
 int ensure_side_streams(rfim_batch *b, int n) {
     if (!b->ev_fork) HIPCHK(hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming));
+    if ((int)b->aux.size() < n && !b->by_item) make_ordinary_queues();
     while ((int)b->aux.size() < n) {
         hipStream_t q = nullptr;
         hipEvent_t e = nullptr;
@@ -2388,7 +2410,6 @@ rfim_batch_t *rfim_batch_create(int n, const rfim_params_t *items, void *hip_str
             return nullptr;
         }
     }
-    drop_idle_side_streams();
     rfim_batch *b = new (std::nothrow) rfim_batch();
     if (!b) {
         fail(RFIM_ENOMEM, "out of host memory");
@@ -2672,7 +2693,6 @@ size_t rfim_pool_bytes_needed(const rfim_params_t *params) {
 }
 
 rfim_pool_t *rfim_pool_create(size_t hbm_budget_bytes, void *hip_stream) {
-    drop_idle_side_streams();
     rfim_pool *p = new (std::nothrow) rfim_pool();
     if (!p) {
         fail(RFIM_ENOMEM, "out of host memory");

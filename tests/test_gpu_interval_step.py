@@ -273,3 +273,70 @@ def test_ordinary_calls_between_replays_two_buffers(rfim_mod, oracle_mod, L, R, 
         f = W.gaussian_fields(L, [111, L])
         ref = rfim_mod.Rfim(L, R, 1.0, 1.5, f, ladder(R, L), seed=L)
     captured_between_ordinary_calls(rfim_mod, ref, L, R, f, (2, 2, 512) if L == 16 else None)
+
+
+def us_a_sweep(g, n=50):
+    import time
+
+    out = []
+    for _ in range(5):
+        t = time.perf_counter()
+        g.sweep(n, 10)
+        g.synchronize()
+        out.append((time.perf_counter() - t) / n * 1e6)
+    return float(np.median(out))
+
+
+@pytest.mark.parametrize("gone", [(2,), (0, 2), (1, 3)])
+def test_two_stream_handles_stay_side_by_side(rfim_mod, gone):
+    """Handles that stay while others and a batch come and go sweep as fast as
+    before: on a pair of streams that takes turns a sweep takes 3.5 times as
+    long (bound: twice)."""
+    import torch
+
+    f, T = W.bimodal_fields(64, [112]), W.linear_temps(128, 1.0, 6.0)
+    hs = []
+    for q in range(6):
+        hs.append(rfim_mod.Rfim(64, 128, 1.0, 1.5, f, T, seed=q, stream=torch.cuda.Stream() if q % 2 else None))
+        hs[-1].sweep(10, 10)
+    before = [us_a_sweep(g) for g in hs]
+    for q in gone:
+        hs[q].close()
+    specs = [W.Realization(L=L, R=4, J=1.0, h=1.0, fields=W.gaussian_fields(L, [113, L]), temps=W.linear_temps(4, 1.5, 4.0),
+                           seed=1, realization=L, every=10) for L in (8, 16, 32)]
+    b = rfim_mod.Batch(specs)
+    b.sweep(40, 10)
+    b.synchronize()
+    kept = [q for q in range(6) if q not in gone]
+    assert all(us_a_sweep(hs[q]) < 2.0 * before[q] for q in kept), (before, [us_a_sweep(hs[q]) for q in kept])
+    b.close()
+    for q in kept:
+        hs[q].close()
+
+
+def test_batches_between_large_handles_cost_no_new_stream(rfim_mod):
+    """A loop of a two-stream handle and a batch: from the second turn on the
+    handle's first call takes no longer than the next one and what a trial of
+    its streams takes (0.2 ms; setting up a hardware queue takes 4)."""
+    import time
+
+    f, T = W.bimodal_fields(64, [114]), W.linear_temps(128, 1.0, 6.0)
+    specs = [W.Realization(L=L, R=4, J=1.0, h=1.0, fields=W.gaussian_fields(L, [115, L]), temps=W.linear_temps(4, 1.5, 4.0),
+                           seed=1, realization=L, every=10) for L in (8, 16, 32)]
+    extra = []
+    for _ in range(9):
+        g = rfim_mod.Rfim(64, 128, 1.0, 1.5, f, T, seed=3)
+        g.synchronize()
+        took = []
+        for _ in range(2):
+            t = time.perf_counter()
+            g.sweep(20, 10)
+            g.synchronize()
+            took.append((time.perf_counter() - t) * 1e3)
+        extra.append(took[0] - took[1])
+        g.close()
+        b = rfim_mod.Batch(specs)
+        b.sweep(40, 10)
+        b.synchronize()
+        b.close()
+    assert np.median(extra[2:]) < 2.0, extra
