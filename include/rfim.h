@@ -248,7 +248,11 @@ int rfim_get_launch_shape(const rfim_t *h, int *mode, int *nw, int *wg);
  * automatic (two streams when each half holds at least 2^22 sites of one
  * colour, 2^23 for the bit sweep with +-1 fields), 1: always one stream, 2:
  * two streams whenever R >= 2.  Only streaming shapes (mode 0, power-of-two
- * L) and bit storage are affected.  RFIM_EINVAL for other values. */
+ * L) and bit storage are affected.  The first two-stream call on a handle
+ * stream waits for its second stream: about 5 ms to set up a hardware queue, or
+ * 0.2 ms for one that an earlier handle left, in which the library tries with a
+ * few empty launches that the two run side by side (it gives up after 2 ms if
+ * work is queued on the handle stream).  RFIM_EINVAL for other values. */
 int rfim_set_concurrency(rfim_t *h, int streams);
 int rfim_get_concurrency(const rfim_t *h);
 

@@ -135,31 +135,63 @@ void make_ordinary_queues() {
     (void)hipGetLastError();
 }
 
-// Whether launches on two streams run side by side.  Hardware queues that share
-// a pipe of the command processor take turns instead, and which do depends on
-// every stream the process made before: on such a pair a sweep of L = 64,
-// R = 128 takes 69 us, on others 18 to 22 (of 90 handles made among batches 18
-// had one, of 180 none since pairs are tried).  A few empty launches on both in turn tell: 27 us side by side,
-// 110 to 130 in turns.  Taken for good where it cannot be tried (work is
-// queued on `main`, or it is being captured).
+// Two words of pinned memory that the trials below write and the host polls
+// (no stream synchronisation: one would end a capture of another thread).  They
+// are kept, since a trial whose wait was given up may still write them.
+uint32_t *g_trial_words = nullptr;
+uint32_t g_trial = 0;
+
+__global__ void trial_end_kernel(uint32_t *word, uint32_t trial) {
+    __hip_atomic_store(word, trial, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Microseconds of a few empty launches on two streams in turn, negative if they
+// took longer than `limit` (work was queued there).
+double launches_in_turn(hipStream_t a, hipStream_t b, double limit) {
+    const uint32_t trial = ++g_trial;
+    const auto t0 = std::chrono::steady_clock::now();
+    auto us = [&] { return std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count(); };
+    for (int q = 0; q < 12; ++q) {
+        hipLaunchKernelGGL(nothing_kernel, dim3(1), dim3(64), 0, a);
+        hipLaunchKernelGGL(nothing_kernel, dim3(1), dim3(64), 0, b);
+    }
+    hipLaunchKernelGGL(trial_end_kernel, dim3(1), dim3(1), 0, a, g_trial_words, trial);
+    hipLaunchKernelGGL(trial_end_kernel, dim3(1), dim3(1), 0, b, g_trial_words + 1, trial);
+    if (hipGetLastError() != hipSuccess) return -1.0;
+    for (int w = 0; w < 2; ++w)
+        while (__atomic_load_n(g_trial_words + w, __ATOMIC_ACQUIRE) != trial)
+            if (us() > limit) return -1.0;
+    return us();
+}
+
+// Whether launches on two streams run side by side or, their queues on one
+// pipe, in turns: on such a pair a sweep of L = 64, R = 128 takes 69 us, on
+// others 18 to 22 (of 90 handles made among batches 9 to 18 had one, of 120
+// none with the trial).  It compares launches on the two with as many on one,
+// as a slow host (a profiler, a busy machine) issues both alike: 25 to 40 us
+// against 43 side by side, 76 to 215 against 48 to 63 in turns.  Taken for good
+// where it cannot be tried.
 bool side_by_side(hipStream_t main, hipStream_t side) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(main, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone ||
-        hipStreamQuery(main) != hipSuccess) {
+    if (hipStreamIsCapturing(main, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
         return true;
     }
-    for (int tries = 0; tries < 3; ++tries) {       // the first may wait for a queue to be set up
-        const auto t0 = std::chrono::steady_clock::now();
-        for (int q = 0; q < 6; ++q) {
-            hipLaunchKernelGGL(nothing_kernel, dim3(1), dim3(64), 0, main);
-            hipLaunchKernelGGL(nothing_kernel, dim3(1), dim3(64), 0, side);
-        }
-        if (hipStreamSynchronize(main) != hipSuccess || hipStreamSynchronize(side) != hipSuccess) {
+    if (!g_trial_words) {
+        if (hipHostMalloc((void **)&g_trial_words, 2 * sizeof(uint32_t), kPinnedFlags) != hipSuccess) {
             (void)hipGetLastError();
+            g_trial_words = nullptr;
             return true;
         }
-        if (std::chrono::steady_clock::now() - t0 < std::chrono::microseconds(60)) return true;
+        g_trial_words[0] = g_trial_words[1] = 0;
+    }
+    constexpr double kBusy = 2000.0, kSetUp = 100000.0;
+    (void)launches_in_turn(side, side, kSetUp);     // a new queue takes 4 ms before its first launch
+    for (int tries = 0; tries < 3; ++tries) {
+        const double pair = launches_in_turn(main, side, kBusy);
+        if (pair < 0.0) return true;
+        const double one = launches_in_turn(main, main, kBusy);
+        if (one < 0.0 || pair < 1.25 * one) return true;
     }
     return false;
 }
