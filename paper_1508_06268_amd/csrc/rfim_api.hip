@@ -396,8 +396,6 @@ struct rfim {
     double *d_beta = nullptr, *d_part = nullptr, *d_E = nullptr, *d_Mr = nullptr, *d_obs = nullptr;
     int32_t *d_t2r = nullptr, *d_r2t = nullptr;
     uint64_t *d_att = nullptr, *d_acc = nullptr, *d_ctrs = nullptr;
-    int64_t *d_B = nullptr, *d_M = nullptr;
-    double *d_F = nullptr;
     int nblk = 1;
     int mode = 0, nw = 0, wg = 0;   // launch shape (see rfim_set_launch_shape)
     rfim_dev::BoxPlan box = {0, 0}; // boxes (L not a power of two), planes = 0: none
@@ -584,8 +582,8 @@ int upload_tables(rfim *h) {
 // A handle's device buffers live in one allocation, in this order, each
 // piece on a 256-byte boundary (byte offsets; absent pieces have size 0).
 struct ArenaLayout {
-    size_t spins, fbits, fhf, fraw, thr, betaf, beta, t2r, r2t, att, acc, ctrs, part, E, Mr, obs, B, M, F,
-        lat, rmap, smap, total;
+    size_t spins, fbits, fhf, fraw, thr, betaf, beta, t2r, r2t, att, acc, ctrs, part, E, Mr, obs, lat, rmap,
+        smap, total;
     size_t smap_cap;   // streaming workgroup-map entries (0 for other L)
 };
 
@@ -625,9 +623,6 @@ ArenaLayout arena_layout(int L, int R_cap, int kind) {
     a.E = take(Rc * sizeof(double));
     a.Mr = take(Rc * sizeof(double));
     a.obs = take(Rc * 6 * sizeof(double));
-    a.B = take(Rc * sizeof(int64_t));
-    a.M = take(Rc * sizeof(int64_t));
-    a.F = take(Rc * sizeof(double));
     a.lat = take(sizeof(Lattice));
     a.rmap = take(Rc * sizeof(uint2));
     a.smap_cap = pow2 ? Rc * maxw : 0;
@@ -661,9 +656,6 @@ int alloc_device(rfim *h) {
     h->d_E = (double *)(b + a.E);
     h->d_Mr = (double *)(b + a.Mr);
     h->d_obs = (double *)(b + a.obs);
-    h->d_B = (int64_t *)(b + a.B);
-    h->d_M = (int64_t *)(b + a.M);
-    h->d_F = (double *)(b + a.F);
     h->d_lat = (Lattice *)(b + a.lat);
     h->d_rmap = (uint2 *)(b + a.rmap);
     h->smap_cap = a.smap_cap;
@@ -1032,7 +1024,7 @@ struct StepBuffers {
         r2t_[1] = (int32_t *)(h->d_part + 2 * rfim_dev::kMaxStepPartials * row);
         t2r_[1] = (int32_t *)(h->d_part + (2 * rfim_dev::kMaxStepPartials + 1) * row);
         in.nblk = h->nblk;
-        rfim_dev::partial_groups(h->R, h->nblk, &in.groups, &in.per);
+        in.per = rfim_dev::partials_per_range(h->R, h->nblk);
     }
     bool pending() const { return in.part != nullptr; }
     // An interval that ends in a step starts at sweep t.

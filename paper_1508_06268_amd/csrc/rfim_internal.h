@@ -118,11 +118,11 @@ struct StepIn {
     int32_t *r2t_out = nullptr, *t2r_out = nullptr; // the permutation after it
     double *part_out = nullptr;                     // where this interval's partials go
     uint32_t k = 0, t0 = 0;                         // the step's exchange counter; the sweep counter
-    int nblk = 1, groups = 1, per = 1;              // the order the partials are added in (partial_groups)
+    int nblk = 1, per = 1;                          // the order the partials are added in (partials_per_range)
 };
-// Workgroups' ranges the totals of nblk partials of R replicas are added in:
-// `groups` ranges of `per`, each in order, then the ranges in order.
-void partial_groups(int R, int nblk, int *groups, int *per);
+// The totals of nblk partials of R replicas are added in ranges of this many,
+// each in order, then the ranges in order.
+int partials_per_range(int R, int nblk);
 // Most replicas whose exchange step runs in one pass of a workgroup, and most
 // partials per replica a step before the sweeps adds.
 constexpr int kExchangeThreads = 1024, kMaxStepPartials = 8;

@@ -2983,7 +2983,11 @@ hipError_t launch_fields_in(const Lattice &lat, size_t first, size_t count, cons
     return hipGetLastError();
 }
 
-void partial_groups(int R, int nblk, int *groups, int *per) { partial_ranges(R, nblk, groups, per); }
+int partials_per_range(int R, int nblk) {
+    int groups, per;
+    partial_ranges(R, nblk, &groups, &per);
+    return per;
+}
 
 hipError_t launch_exchange(const Lattice *lats, int n, int tadv, const StepIn &in, hipStream_t s) {
     if (n == 0) return hipSuccess;
