@@ -1047,7 +1047,7 @@ struct StepBuffers {
     // The interval's last launch was issued: its step k is pending.
     void end(uint64_t k) {
         in.part = part_[next_];
-        in.k = (uint32_t)k;
+        in.k = k;
         next_ ^= 1;
     }
     // An exchange launch took the step and wrote the handle's own arrays.

@@ -117,7 +117,8 @@ struct StepIn {
     const double *part = nullptr;                   // null: no step is pending
     int32_t *r2t_out = nullptr, *t2r_out = nullptr; // the permutation after it
     double *part_out = nullptr;                     // where this interval's partials go
-    uint32_t k = 0, t0 = 0;                         // the step's exchange counter; the sweep counter
+    uint64_t k = 0;                                 // the step's exchange counter
+    uint32_t t0 = 0;                                // the sweep counter
     int nblk = 1, per = 1;                          // the order the partials are added in (partials_per_range)
 };
 // The totals of nblk partials of R replicas are added in ranges of this many,

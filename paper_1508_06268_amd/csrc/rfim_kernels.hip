@@ -2342,7 +2342,7 @@ __global__ __launch_bounds__(kExchangeThreads) void exchange_kernel(const Lattic
     __shared__ int32_t st2r[kExchangeThreads];
     const Lattice &lat = lats[blockIdx.x];
     const bool pending = in.part != nullptr;      // then R <= kExchangeThreads
-    const uint64_t k = pending ? (uint64_t)in.k : lat.ctrs[1];
+    const uint64_t k = pending ? in.k : lat.ctrs[1];
     const int R = lat.R, t = (int)threadIdx.x;
     if (R <= kExchangeThreads) {
         // inputs that do not depend on the energies, fetched first

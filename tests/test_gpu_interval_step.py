@@ -222,6 +222,22 @@ def test_second_streams_among_batches(rfim_mod, seed):
         g.close()
 
 
+@pytest.mark.parametrize("L,R", [(8, 5), (32, 3), (40, 3)])
+def test_exchange_counter_beyond_32_bits(rfim_mod, oracle_mod, L, R):
+    """From the largest counter that can be set: the random words take its low
+    half, the counter itself goes on."""
+    f = W.bimodal_fields(L, [116, L])
+    g, o = make_pair(rfim_mod, oracle_mod, L, R, 1.0, 1.5, f, ladder(R, L), seed=L)
+    for h in (g, o):
+        h.set_counters(7, 2 ** 32 - 1)
+    for n, every in ((9, 2), (4, 4), (3, 1)):
+        g.sweep(n, every)
+        o.sweep(n, every)
+        assert_same_state(g, o, "(%d, %d)" % (n, every))
+    g.close()
+    o.close()
+
+
 def captured_between_ordinary_calls(rfim_mod, ref, L, R, f, shape=None):
     """A captured call, replayed before, between and after ordinary calls of
     one launch an interval and of an odd number of them: all of them are one
