@@ -252,7 +252,9 @@ void release_side_stream(hipStream_t side) {
 // wait for every array (15 to 20 us each).  Blocks are kept for the next call:
 // at most kPinnedKept of them, of at most kPinnedBlock bytes, and no more
 // than kPinnedIdle bytes once no handle is left.  A block belongs to one call
-// at a time, which has waited for its work when it gives the block back.
+// at a time, which has waited for its work when it gives the block back; where
+// that wait failed, kernels may still read or write the block, and it is given
+// up.
 constexpr size_t kPinnedBlock = 4u << 20, kPinnedIdle = 1u << 20;
 constexpr size_t kPinnedKept = 8;
 
@@ -287,7 +289,7 @@ class Pinned {
     Pinned(const Pinned &) = delete;
     Pinned &operator=(const Pinned &) = delete;
     ~Pinned() {
-        if (!b_.p) return;
+        if (!b_.p || pending_) return;
         if (b_.bytes <= kPinnedBlock) {
             std::lock_guard<std::mutex> lock(g_pinned_mu);
             if (g_pinned.size() < kPinnedKept) {
@@ -322,9 +324,12 @@ class Pinned {
         return RFIM_OK;
     }
     char *at(size_t off = 0) const { return (char *)b_.p + off; }
+    // Whether queued work may use the block.
+    void pending(bool yes) { pending_ = yes; }
 
   private:
     PinnedBlock b_ = {nullptr, 0};
+    bool pending_ = false;
 };
 
 }  // namespace
@@ -674,8 +679,10 @@ int upload_fields(rfim *h) {
     for (size_t i = 0; i < N; i += chunk) {
         const size_t n = std::min(chunk, N - i);
         std::memcpy(buf.at(), h->fields.data() + i, n * sizeof(float));
+        buf.pending(true);
         HIPCHK(rfim_dev::launch_fields_in(lat, i, n, (const float *)buf.at(), h->stream));
         HIPCHK(hipStreamSynchronize(h->stream));
+        buf.pending(false);
     }
     return RFIM_OK;
 }
@@ -794,8 +801,10 @@ int fetch(rfim *h, std::initializer_list<Fetch> parts) {
         c.dst[q] = buf.at(off[q]);
         ++q;
     }
+    buf.pending(true);
     HIPCHK(rfim_dev::launch_copy_out(c, h->stream));
     if ((rc = wait_done(h->stream, c.done, nflags))) return rc;
+    buf.pending(false);
     q = 0;
     for (const Fetch &f : parts) std::memcpy(f.dst, buf.at(off[q++]), f.bytes);
     return RFIM_OK;
@@ -808,13 +817,16 @@ int download_perm(rfim *h, std::vector<int32_t> &t2r) {
 
 // Energies and magnetisations of the current state, straight into the
 // caller's pinned block, which has the flags at flags_at.
-int read_state(rfim *h, rfim_dev::Readout &out, const Pinned &buf, size_t flags_at) {
+int read_state(rfim *h, rfim_dev::Readout &out, Pinned &buf, size_t flags_at) {
     const Lattice lat = h->lattice();
     const unsigned n = rfim_dev::readout_flags(lat);
     out.done = (uint32_t *)buf.at(flags_at);
     std::memset(out.done, 0, n * sizeof(uint32_t));
+    buf.pending(true);
     HIPCHK(rfim_dev::launch_readout(lat, out, h->stream));
-    return wait_done(h->stream, out.done, n);
+    const int rc = wait_done(h->stream, out.done, n);
+    buf.pending(rc != RFIM_OK);
+    return rc;
 }
 
 // By temperature slot: energies and magnetisations, each if asked for.
@@ -1410,13 +1422,15 @@ int rfim_get_spins(rfim_t *h, int8_t *s) {
         if ((rc = buf[q].get(p.piece))) return rc;
     hipEvent_t ev[2] = {nullptr, nullptr};
     auto leave = [&](int code) {
-        (void)hipStreamSynchronize(h->stream);      // the blocks go back: nothing may still write them
+        const bool busy = hipStreamSynchronize(h->stream) != hipSuccess;
+        for (Pinned &b : buf) b.pending(busy);
         for (hipEvent_t e : ev)
             if (e) (void)hipEventDestroy(e);
         return code;
     };
     auto start = [&](size_t k) {
         const size_t at = k * p.piece, n = std::min(p.piece, p.total - at);
+        buf[k & 1].pending(true);
         hipError_t e = rfim_dev::launch_spins_out(lat, at, n, (int8_t *)buf[k & 1].at(), h->stream);
         if (e == hipSuccess && two) {
             if (!ev[k & 1]) e = hipEventCreateWithFlags(&ev[k & 1], hipEventDisableTiming);
@@ -1461,9 +1475,11 @@ int rfim_set_spins(rfim_t *h, const int8_t *s) {
         if (k >= 2 && (k & 1) == 0) e = hipStreamSynchronize(h->stream);    // both blocks are free again
         if (e != hipSuccess) break;
         std::memcpy(buf[k & 1].at(), s + at, n);
+        buf[k & 1].pending(true);
         e = rfim_dev::launch_spins_in(lat, at, n, (const int8_t *)buf[k & 1].at(), h->stream);
     }
     const hipError_t e2 = hipStreamSynchronize(h->stream);
+    for (Pinned &b : buf) b.pending(e2 != hipSuccess);
     if (e == hipSuccess) e = e2;
     if (e != hipSuccess) return fail(RFIM_EDEVICE, "writing spins: %s", hipGetErrorString(e));
     return RFIM_OK;

@@ -63,3 +63,46 @@ def test_configurations_round_trip(rfim_mod, L, R):
     assert np.array_equal(np.asarray(g2.spins()).reshape(R, -1), s)
     g.close()
     g2.close()
+
+
+def test_readouts_that_fail_leave_later_ones_alone(rfim_mod):
+    """A readout behind 20 ms of sweeps, in a thread that captures another
+    stream: its wait is refused and the call fails.  When its kernels end, they
+    write into no other call's results."""
+    import ctypes
+    import time
+
+    import torch
+
+    hip = ctypes.CDLL("libamdhip64.so")
+    L, R = 16, 32
+    f = W.bimodal_fields(L, [94, L])
+    far, near = (rfim_mod.Rfim(L, R, 1.0, 1.5, f, W.linear_temps(R, 1.5, 4.0), seed=q) for q in (1, 2))
+    near.sweep(5, 1)
+    E = near.energies()
+    far.sweep(1, 1)
+    far.synchronize()
+    t = time.perf_counter()
+    far.sweep(1000, 0)
+    far.synchronize()
+    n = int(20e-3 / (time.perf_counter() - t) * 1000)
+    other = torch.cuda.Stream()
+    for _ in range(12):
+        torch.cuda.synchronize()
+        far.sweep(n, 0)
+        assert hip.hipStreamBeginCapture(ctypes.c_void_p(other.cuda_stream), 1) == 0
+        failed = False
+        try:
+            far.energies()
+        except rfim_mod.RfimError:
+            failed = True
+        graph = ctypes.c_void_p()
+        hip.hipStreamEndCapture(ctypes.c_void_p(other.cuda_stream), ctypes.byref(graph))
+        hip.hipGetLastError()
+        until = time.perf_counter() + 30e-3
+        while failed and time.perf_counter() < until:
+            assert np.array_equal(near.energies(), E)
+    far.synchronize()
+    check_state(far, f, L, R, 1.5)
+    far.close()
+    near.close()
