@@ -262,25 +262,26 @@ struct PinnedBlock {
     void *p;
     size_t bytes;
 };
+// (a plain array: giving a block back must not throw)
 std::mutex g_pinned_mu;
-std::vector<PinnedBlock> g_pinned;
-size_t g_handles = 0;
+PinnedBlock g_pinned[kPinnedKept];
+size_t g_pinned_n = 0, g_handles = 0;
 
 void note_handle(int step) {
     std::lock_guard<std::mutex> lock(g_pinned_mu);
     g_handles += (size_t)step;
     if (g_handles != 0) return;
-    size_t kept = 0;
-    std::vector<PinnedBlock> keep;
-    for (const PinnedBlock &b : g_pinned) {
+    size_t kept = 0, n = 0;
+    for (size_t q = 0; q < g_pinned_n; ++q) {
+        const PinnedBlock b = g_pinned[q];
         if (kept + b.bytes <= kPinnedIdle) {
             kept += b.bytes;
-            keep.push_back(b);
+            g_pinned[n++] = b;
         } else {
             (void)hipHostFree(b.p);
         }
     }
-    g_pinned.swap(keep);
+    g_pinned_n = n;
 }
 
 class Pinned {
@@ -292,8 +293,8 @@ class Pinned {
         if (!b_.p || pending_) return;
         if (b_.bytes <= kPinnedBlock) {
             std::lock_guard<std::mutex> lock(g_pinned_mu);
-            if (g_pinned.size() < kPinnedKept) {
-                g_pinned.push_back(b_);
+            if (g_pinned_n < kPinnedKept) {
+                g_pinned[g_pinned_n++] = b_;
                 return;
             }
         }
@@ -302,13 +303,12 @@ class Pinned {
     int get(size_t bytes) {
         {
             std::lock_guard<std::mutex> lock(g_pinned_mu);
-            size_t best = g_pinned.size();
-            for (size_t q = 0; q < g_pinned.size(); ++q)
-                if (g_pinned[q].bytes >= bytes && (best == g_pinned.size() || g_pinned[q].bytes < g_pinned[best].bytes))
-                    best = q;
-            if (best < g_pinned.size()) {
+            size_t best = g_pinned_n;
+            for (size_t q = 0; q < g_pinned_n; ++q)
+                if (g_pinned[q].bytes >= bytes && (best == g_pinned_n || g_pinned[q].bytes < g_pinned[best].bytes)) best = q;
+            if (best < g_pinned_n) {
                 b_ = g_pinned[best];
-                g_pinned.erase(g_pinned.begin() + (long)best);
+                g_pinned[best] = g_pinned[--g_pinned_n];
                 return RFIM_OK;
             }
         }
