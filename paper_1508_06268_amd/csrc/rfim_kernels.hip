@@ -210,6 +210,17 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// The same in a workgroup whose last wave may be partly empty: what a shuffle
+// gives for a lane that is not there counts as 0.
+__device__ __forceinline__ double part_wave_sum(double v) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const double o = __shfl_xor(v, off, 64);
+        v += (threadIdx.x ^ (uint32_t)off) < blockDim.x ? o : 0.0;
+    }
+    return v;
+}
+
 // Offsets (in sublattice bytes) of the other-colour words around a chunk.
 struct Chunk {
     uint32_t p, jxw, jyp, jym, jzp, jzm;
@@ -599,8 +610,9 @@ __device__ __forceinline__ void chunk_energy(const Lattice &lat, const uint32_t 
     }
 }
 
-// Block-wide (B, F, M) partial in a fixed order; thread 0..2 write it.
-template <int KIND, class PD>
+// Block-wide (B, F, M) partial in a fixed order; thread 0..2 write it.  WAVES:
+// the workgroup is whole waves.
+template <int KIND, bool WAVES = true, class PD>
 __device__ __forceinline__ void block_partial(PD dst, int nsite, int ksum, int upsum, int eqsum,
                                               double fsum) {
     __shared__ double red[3][16];
@@ -610,7 +622,8 @@ __device__ __forceinline__ void block_partial(PD dst, int nsite, int ksum, int u
     // integer sums over the wave's active lanes (DPP reduction in the
     // device library; exact, so the order does not matter)
     const int vb = __ockl_wfred_add_i32(bpart), vm = __ockl_wfred_add_i32(mpart);
-    const double vf = KIND == 0 ? (double)__ockl_wfred_add_i32(2 * eqsum - 2 * nsite) : wave_sum(fsum);
+    const double vf = KIND == 0 ? (double)__ockl_wfred_add_i32(2 * eqsum - 2 * nsite)
+                                : (WAVES ? wave_sum(fsum) : part_wave_sum(fsum));
     if (lane == 0) {
         red[0][wave] = (double)vb;
         red[1][wave] = vf;
@@ -1034,8 +1047,8 @@ __device__ __forceinline__ uint32_t plane_counts(const uint8_t *oth, const uint8
 // is the whole replica, periodic in z, without halo planes (any nsweep).
 //
 // A thread keeps one place of the plane and takes every G-th of the active
-// planes (blockDim = G blocks-per-plane, rounded up to whole waves, as the sums
-// over a wave take them).  Bound by instruction issue (104
+// planes (blockDim = G blocks-per-plane; the last wave may be partly empty).
+// Bound by instruction issue (104
 // VALU instructions per block of four sites with whole-dword rows; 160 with
 // the place worked out for every block) and, for thin slabs, by the launch
 // and the staging: box_plan weighs them.  us a sweep, boxes against
@@ -1066,10 +1079,8 @@ __global__ __launch_bounds__(1024) void sweep_box(Lattice lat, StepIn in, FastDi
         z -= z >= L ? L : 0u;
         return z - (z >= L ? L : 0u);
     };
-    // this thread's first plane, planes per step; the threads that fill up the
-    // last wave have none
-    const uint32_t G = blockDim.x / bpp, tg = div_by(threadIdx.x, by_plane), pg = tg < G ? tg : 0x10000u;
-    const Place<ROWS> place = place_of<ROWS>(4u * (threadIdx.x - tg * bpp), L, by_row);
+    const uint32_t pg = div_by(threadIdx.x, by_plane), G = blockDim.x / bpp;   // this thread's first plane, planes per step
+    const Place<ROWS> place = place_of<ROWS>(4u * (threadIdx.x - pg * bpp), L, by_row);
     // stage the box: the thread's block of its planes, both colours
     for (uint32_t b = pg; b < P; b += G) {
         const uint32_t at = z_of(b) * plane + place.d;
@@ -1116,8 +1127,8 @@ __global__ __launch_bounds__(1024) void sweep_box(Lattice lat, StepIn in, FastDi
             if (KIND == 0) load_words<1>(fbits + half, j0, F1);
             chunk_energy<KIND, 1>(lat, S1, W, U, F1, fbits, fraw + half, fraw, j0, ksum, upsum, eqsum, fsum);
         }
-        block_partial<KIND>(gptr(in.r2t ? in.part_out : lat.part) + ((size_t)sl * lat.pstride + r) * 3, 4 * cnt, ksum, upsum,
-                            eqsum, fsum);
+        block_partial<KIND, false>(gptr(in.r2t ? in.part_out : lat.part) + ((size_t)sl * lat.pstride + r) * 3, 4 * cnt, ksum,
+                                   upsum, eqsum, fsum);
     }
     GAS uint8_t *rdst = gptr(dst) + (size_t)r * lat.N;
     for (uint32_t k = pg; k < np; k += G) {
@@ -2723,7 +2734,7 @@ static void launch_box_form(const Lattice &lat, const StepIn &in, const uint8_t 
     const uint32_t L = (uint32_t)lat.L, slabs = (L + (uint32_t)np - 1u) / (uint32_t)np, bpp = L * L / 8u;
     const bool whole = slabs == 1u;
     const uint32_t active = whole ? L : (uint32_t)(np + 4 * nsweep - 2);     // planes of the largest half-sweep
-    const dim3 grid((unsigned)lat.R * slabs), block((bpp * std::min(1024u / bpp, active) + 63u) & ~63u);
+    const dim3 grid((unsigned)lat.R * slabs), block(bpp * std::min(1024u / bpp, active));
     const FastDiv by_row = fast_div(L / 2u), by_plane = fast_div(bpp), by_slab = fast_div(slabs);
     const size_t lds = box_lds_bytes(lat.L, whole ? lat.L : np + 4 * nsweep);
     auto go = [&](auto kernel) {
