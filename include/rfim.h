@@ -46,6 +46,13 @@
  * return NULL.  rfim_last_error() gives a thread-local message for the last
  * failure.  Arguments are validated before any device work.  A kernel fault
  * surfaces as RFIM_EDEVICE at the next call that synchronizes.
+ *
+ * Synchronizing calls that fill host arrays return once the handle's work
+ * queued before them is done and their results are there; the stream itself may
+ * report its end some microseconds later.  They, the constructors and
+ * rfim_set_spins pass data through pinned host memory that the library keeps
+ * for the next call (per process at most 8 blocks of up to 4 MiB, and 1 MiB in
+ * all once no handle is left), and fail with RFIM_ENOMEM where none can be had.
  */
 #ifndef RFIM_H
 #define RFIM_H
@@ -198,8 +205,9 @@ int rfim_reset_observables(rfim_t *h);
  * RFIM_MEASURE_FOURIER set, every exchange step also adds, per slot,
  *   F = (1/(3N)) sum_mu [(sum_i s_i cos(K x_mu,i))^2 + (sum_i s_i sin(K x_mu,i))^2]
  * of the configuration now at that slot (K = 2 pi / L, mu over the three
- * axes; the printed formula's field h_i read as the spin s_i).  Costs two
- * small launches per exchange step and reads every spin once.  flags = 0
+ * axes; the printed formula's field h_i read as the spin s_i).  Costs one
+ * small launch per exchange step up to L = 32, two above, and reads every spin
+ * once.  flags = 0
  * turns it off.  The first call with the flag allocates R_cap * L * 2L * 4
  * + (2L + 2 R_cap) * 8 bytes of device memory (RFIM_ENOMEM if that fails).
  * Works for standalone handles and for batch and pool items (their
@@ -233,7 +241,8 @@ int rfim_fourier(rfim_t *h, double *fourier);
  * be allocated, on the slab shape (4, 8, 1024) at L = 32 and R_cap <= 32 or
  * (3, 4, 1024) at L = 32 and R_cap <= 64 with continuous fields.  A call made
  * while the handle's stream is being captured runs the shape of the class
- * instead of slabs.
+ * instead of slabs; its replays and the handle's other calls, in any order on
+ * the stream, go on with one chain.
  * RFIM_EINVAL for a shape not valid for the handle's L. */
 int rfim_set_launch_shape(rfim_t *h, int mode, int nw, int wg);
 int rfim_get_launch_shape(const rfim_t *h, int *mode, int *nw, int *wg);

@@ -1047,8 +1047,8 @@ __device__ __forceinline__ uint32_t plane_counts(const uint8_t *oth, const uint8
 // is the whole replica, periodic in z, without halo planes (any nsweep).
 //
 // A thread keeps one place of the plane and takes every G-th of the active
-// planes (blockDim = G blocks-per-plane; the last wave may be partly empty).
-// Bound by instruction issue (104
+// planes (blockDim = G blocks-per-plane; the last wave may be partly empty,
+// and filling it up cost 1 % at L = 48, R = 32).  Bound by instruction issue (104
 // VALU instructions per block of four sites with whole-dword rows; 160 with
 // the place worked out for every block) and, for thin slabs, by the launch
 // and the staging: box_plan weighs them.  us a sweep, boxes against
@@ -2335,8 +2335,10 @@ __device__ __forceinline__ void replica_totals(const Lattice &lat, const double 
     }
 }
 
-// Totals per replica id for the observables calls (same reduction as the
-// exchange step, so both give the same bits).
+// Totals per replica id for the calls that read energies.  The sums are the
+// exchange step's, but over partials of their own (energy_blocks): with
+// continuous fields the energies read and those of a step may differ in the last
+// bits, with +-1 fields both are exact.
 __global__ __launch_bounds__(kExchangeThreads) void reduce_kernel(Lattice lat, Readout out) {
     replica_totals(lat, lat.part, out);
     signal_done(out.done, (int)threadIdx.x < lat.R);

@@ -116,15 +116,14 @@ __device__ __forceinline__ void write_sums(const int (&bsum)[RB], const double (
 // FP64.  A thread takes V consecutive sites of a row at a time (V divides L)
 // and steps kThreads * V sites through the chunk, its coordinates carried
 // along without divisions; the field of those sites is read and converted
-// once for the RB replicas.  Per thread in site order, then the wave's
-// butterfly, then the four waves in order: the same sum on every call.
+// once for the RB replicas.  Per thread in site order, then over the wave
+// (wave_total), then the four waves in order: the same sum on every call.
 // nb = 1 writes the energies themselves.
 //
 // Bound: load latency and the L1 (each spin row is read for its own sites and
 // as the forward row of two others); the spins are read from memory about
-// once.  For the rows that are not whole 16-site units, and arrays without
-// their alignment: L = 100, R = 50
-// (also 50 MB) 32 us.
+// once.  It takes the sizes whose rows are not whole 16-site units and arrays
+// without their alignment: 32 us at L = 100, R = 50 (50 MB of spins).
 template <int V, int RB>
 __global__ __launch_bounds__(kThreads) void site_energy_partials(int L, int R, int nb, int N, int chunk, double J,
                                                                  double h, const int8_t *__restrict__ spins,
@@ -287,8 +286,8 @@ __global__ __launch_bounds__(kThreads) void site_energy_columns(int L, int R, in
 }
 
 // E_r = -(J B_r) - (h F_r): one wave per replica, lane l adds blocks l,
-// l + 64, ... in order, then the butterfly.  (One thread per replica waited
-// for its nb loads one after another.)
+// l + 64, ... in order, then over the wave (wave_total).  (One thread per replica
+// waited for its nb loads one after another.)
 __global__ __launch_bounds__(kThreads) void site_energy_totals(int R, int nb, double J, double h,
                                                                const double *__restrict__ part,
                                                                double *__restrict__ E) {
