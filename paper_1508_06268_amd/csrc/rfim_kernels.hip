@@ -2113,13 +2113,30 @@ __global__ __launch_bounds__(256) void clear_kernel(uint64_t *a, uint32_t na, ui
     if (i < nb) b[i] = 0ull;
 }
 
-// Device arrays to pinned host memory, in one launch.
+// Workgroups that copy one array: 16 bytes a thread and step, and few of them,
+// since each ends its writes to the host for itself (13 ns).
+constexpr uint32_t kCopyUnit = 4u * 256u, kCopyBlocks = 32;
+__host__ __device__ inline uint32_t copy_blocks(uint32_t words) {
+    const uint32_t n = (words + kCopyUnit - 1u) / kCopyUnit;
+    return n < kCopyBlocks ? n : kCopyBlocks;
+}
+
+// Device arrays to pinned host memory (both 16-byte aligned), in one launch.
+// Observables of R = 3000 (144 KB) 30.3 us a call with a dword a thread and 141
+// workgroups for each of the three arrays, empty ones too; a staged copy took
+// 17.3.
 __global__ __launch_bounds__(256) void copy_out_kernel(CopyOut c) {
-    const uint32_t q = blockIdx.y, n = c.words[q];
+    uint32_t q = 0, b = blockIdx.x;
+    while (b >= copy_blocks(c.words[q])) b -= copy_blocks(c.words[q++]);
+    const uint32_t n = c.words[q], n4 = n / 4u, step = 256u * copy_blocks(n);
     GAS const uint32_t *src = (GAS const uint32_t *)c.src[q];
     uint32_t *dst = (uint32_t *)c.dst[q];
-    for (uint32_t w = blockIdx.x * 256u + threadIdx.x; w < n; w += 256u * gridDim.x) dst[w] = src[w];
-    signal_done(c.done + blockIdx.y * gridDim.x + blockIdx.x, blockIdx.x * 256u + threadIdx.x < n);
+    uint32_t w = b * 256u + threadIdx.x;
+    const bool wrote = 4u * w < n;
+    for (; w < n4; w += step) ((u32x4 *)dst)[w] = ((GAS const u32x4 *)src)[w];
+    if (w == n4)                            // the one thread whose turn the last 1 to 3 words are
+        for (uint32_t i = 4u * n4; i < n; ++i) dst[i] = src[i];
+    signal_done(c.done + blockIdx.x, wrote);
 }
 
 // ---------------------------------------------------------------------
@@ -2943,18 +2960,16 @@ hipError_t launch_clear(void *a, size_t na, void *b, size_t nb, hipStream_t s) {
     return hipGetLastError();
 }
 
-static unsigned copy_out_blocks(const CopyOut &c) {
-    uint32_t most = 0;
-    for (int q = 0; q < CopyOut::kMax; ++q) most = std::max(most, c.words[q]);
-    return std::min((most + 255u) / 256u, 256u);
+unsigned copy_out_flags(const CopyOut &c) {
+    unsigned n = 0;
+    for (const uint32_t w : c.words) n += copy_blocks(w);
+    return n;
 }
 
-unsigned copy_out_flags(const CopyOut &c) { return copy_out_blocks(c) * (unsigned)CopyOut::kMax; }
-
 hipError_t launch_copy_out(const CopyOut &c, hipStream_t s) {
-    const unsigned nb = copy_out_blocks(c);
+    const unsigned nb = copy_out_flags(c);
     if (nb == 0) return hipSuccess;
-    hipLaunchKernelGGL(copy_out_kernel, dim3(nb, (unsigned)CopyOut::kMax), dim3(256), 0, s, c);
+    hipLaunchKernelGGL(copy_out_kernel, dim3(nb), dim3(256), 0, s, c);
     return hipGetLastError();
 }
 

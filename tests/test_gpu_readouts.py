@@ -65,6 +65,27 @@ def test_configurations_round_trip(rfim_mod, L, R):
     g2.close()
 
 
+@pytest.mark.parametrize("R", [1, 2, 3, 5, 170, 171, 255, 1023, 1024, 1025, 2731, 4099, 5000])
+def test_arrays_of_every_length(rfim_mod, R):
+    """Permutations (R words), counters and per-slot sums (2 to 12 words a
+    replica): lengths around a workgroup's share, of several steps and with
+    one to three words at the end."""
+    f = W.bimodal_fields(2, [95])
+    g = rfim_mod.Rfim(2, R, 1.0, 1.5, f, W.linear_temps(R, 1.5, 4.0) if R > 1 else np.array([2.0]), seed=3)
+    p = np.random.default_rng(R).permutation(R).astype(np.int32)
+    g.set_perm(p)
+    assert np.array_equal(g.perm(), p)
+    g.sweep(1, 1)
+    E, M, obs = g.energies(), g.magnetizations(), g.observables()
+    want = np.stack([np.ones(R), E, E * E, np.abs(M), 1.0 * M * M, 1.0 * M ** 4], axis=1)
+    assert np.array_equal(obs, want)
+    att, acc = g.exchange_stats()
+    assert np.array_equal(att, (np.arange(R - 1) + 1) % 2) and np.all(acc <= att)
+    assert sorted(g.perm()) == list(range(R)) and (g.perm() != p).sum() == 2 * acc.sum()
+    assert g.counters() == (1, 1)
+    g.close()
+
+
 def test_readouts_that_fail_leave_later_ones_alone(rfim_mod):
     """A readout behind 20 ms of sweeps, in a thread that captures another
     stream: its wait is refused and the call fails.  When its kernels end, they
